@@ -14,11 +14,12 @@
 // ds_read_b64_tr_b16. The SwiGLU activation and its derivative are fused into
 // the epilogues.
 //
-// f32 path: plain per-element kernels (small shapes only; no MFMA).
+// f32 path: ffn_f32.hip.
 #include <climits>
 #include <type_traits>
 
 #include "common.h"
+#include "ffn_f32.h"
 
 namespace foremoe {
 namespace {
@@ -1613,97 +1614,6 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// fp32 path: one thread per output element (small shapes).
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ int find_slot(const int32_t* __restrict__ off, int S, int64_t row) {
-  // last slot j with off[j] <= row (row < off[S] is guaranteed by the caller)
-  int lo = 0, hi = S - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (off[mid] <= row) lo = mid;
-    else hi = mid - 1;
-  }
-  return lo;
-}
-
-enum F32Op { kF32GateUpFwd = 0, kF32DownFwd = 1, kF32DownDgrad = 2, kF32GateUpDgrad = 3 };
-
-template <int OP>
-__global__ __launch_bounds__(256) void f32_rows_kernel(const float* __restrict__ A, const float* __restrict__ Wt,
-                                                       const float* __restrict__ AU, int d, int F, int W,
-                                                       const int32_t* __restrict__ off, const int32_t* __restrict__ widx,
-                                                       int S, int64_t n_cap, float* __restrict__ C,
-                                                       float* __restrict__ C2) {
-  const int col = blockIdx.x * 16 + (threadIdx.x & 15);
-  const int64_t row = (int64_t)blockIdx.y * 16 + (threadIdx.x >> 4);
-  if (S <= 0) return;
-  int64_t N = off[S];
-  if (N > n_cap) N = n_cap;
-  if (row >= N) return;
-  const int ncols = (OP == kF32GateUpFwd || OP == kF32DownDgrad) ? F : d;
-  if (col >= ncols) return;
-  const int j = find_slot(off, S, row);
-  const int w = widx[j];
-  if (w < 0 || w >= W) return;
-  if constexpr (OP == kF32GateUpFwd) {
-    const float* x = A + row * d;
-    const float* wg = Wt + (int64_t)w * 2 * F * d + (int64_t)col * d;
-    const float* wu = wg + (int64_t)F * d;
-    float av = 0.f, uv = 0.f;
-    for (int k = 0; k < d; ++k) {
-      av += x[k] * wg[k];
-      uv += x[k] * wu[k];
-    }
-    C[row * F + col] = silu_f(av) * uv;
-    if (C2) {
-      C2[row * 2 * F + col] = av;
-      C2[row * 2 * F + F + col] = uv;
-    }
-  } else if constexpr (OP == kF32DownFwd) {
-    const float* h = A + row * F;
-    const float* wd = Wt + (int64_t)w * d * F + (int64_t)col * F;
-    float s = 0.f;
-    for (int k = 0; k < F; ++k) s += h[k] * wd[k];
-    C[row * d + col] = s;
-  } else if constexpr (OP == kF32DownDgrad) {
-    const float* dy = A + row * d;
-    const float* wd = Wt + (int64_t)w * d * F + col;
-    float dh = 0.f;
-    for (int k = 0; k < d; ++k) dh += dy[k] * wd[(int64_t)k * F];
-    const float av = AU[row * 2 * F + col], uv = AU[row * 2 * F + F + col];
-    const float s = 1.0f / (1.0f + __expf(-av));
-    C[row * 2 * F + col] = dh * uv * (s + av * s * (1.0f - s));
-    C[row * 2 * F + F + col] = dh * av * s;
-  } else {
-    const float* dau = A + row * 2 * F;
-    const float* wgu = Wt + (int64_t)w * 2 * F * d + col;
-    float s = 0.f;
-    for (int k = 0; k < 2 * F; ++k) s += dau[k] * wgu[(int64_t)k * d];
-    C[row * d + col] = s;
-  }
-}
-
-// dW[g][m][n] += sum over rows of slots with gidx g of A[row][m] * B[row][n]
-__global__ __launch_bounds__(256) void f32_wgrad_kernel(const float* __restrict__ A, int lda, const float* __restrict__ B,
-                                                        int ldb, int M, int N, const int32_t* __restrict__ off,
-                                                        const int32_t* __restrict__ gidx, int S, int G, int64_t n_cap,
-                                                        int part, int parts, float* __restrict__ C) {
-  const int n = blockIdx.x * 16 + (threadIdx.x & 15);
-  const int m = blockIdx.y * 16 + (threadIdx.x >> 4);
-  const int g = blockIdx.z;
-  if (n >= N || m >= M || m % parts != part) return;
-  float s = 0.f;
-  for (int j = 0; j < S; ++j) {
-    if (gidx[j] != g) continue;
-    int64_t lo = off[j], hi = off[j + 1];
-    lo = lo < 0 ? 0 : (lo > n_cap ? n_cap : lo);
-    hi = hi < 0 ? 0 : (hi > n_cap ? n_cap : hi);
-    for (int64_t r = lo; r < hi; ++r) s += A[r * lda + m] * B[r * ldb + n];
-  }
-  C[((int64_t)g * M + m) * N + n] += s;
-}
-
-// ---------------------------------------------------------------------------
 // Host launchers
 // ---------------------------------------------------------------------------
 int persistent_grid() { return num_cus(); }
@@ -1787,10 +1697,6 @@ static int no_launch(hipEvent_t e0, hipEvent_t e1, void* stream) {
   return FOREMOE_OK;
 }
 
-static dim3 f32_grid(int cols, int64_t rows) {
-  return dim3((unsigned)((cols + 15) / 16), (unsigned)((rows + 15) / 16 > 0 ? (rows + 15) / 16 : 1));
-}
-
 extern "C" {
 
 static int ffn_gate_up_fwd_impl(const void* x_perm, foremoe_dtype dtype, int32_t d, int32_t F, int32_t S,
@@ -1824,9 +1730,10 @@ static int ffn_gate_up_fwd_impl(const void* x_perm, foremoe_dtype dtype, int32_t
     a.ldc2 = 2 * (int64_t)F;
     launch_rows<256, true, kEpiSwigluFwd>(a, workspace, st, e0, e1);
   } else {
-    hipExtLaunchKernelGGL(f32_rows_kernel<kF32GateUpFwd>, f32_grid(F, n_cap), dim3(256), 0, st, e0, e1, 0, (const float*)x_perm,
-                       (const float*)w_gate_up, nullptr, d, F, W, slot_offset, slot_widx, S, n_cap, (float*)h,
-                       (float*)save_au);
+    launch_f32_rows(kF32GateUpFwd,
+                    {(const float*)x_perm, (const float*)w_gate_up, nullptr, d, F, W, slot_offset, slot_widx, S, n_cap,
+                     (float*)h, (float*)save_au},
+                    st, e0, e1);
   }
   return check_launch("foremoe_ffn_gate_up_fwd");
 }
@@ -1861,9 +1768,10 @@ static int ffn_down_fwd_impl(const void* h, foremoe_dtype dtype, int32_t d, int3
     if (d % 256 == 0) launch_rows<256, true, kEpiStore>(a, workspace, st, e0, e1);
     else launch_rows<128, true, kEpiStore>(a, workspace, st, e0, e1);
   } else {
-    hipExtLaunchKernelGGL(f32_rows_kernel<kF32DownFwd>, f32_grid(d, n_cap), dim3(256), 0, st, e0, e1, 0, (const float*)h,
-                       (const float*)w_down, nullptr, d, F, W, slot_offset, slot_widx, S, n_cap, (float*)y_perm,
-                       nullptr);
+    launch_f32_rows(kF32DownFwd,
+                    {(const float*)h, (const float*)w_down, nullptr, d, F, W, slot_offset, slot_widx, S, n_cap,
+                     (float*)y_perm, nullptr},
+                    st, e0, e1);
   }
   return check_launch("foremoe_ffn_down_fwd");
 }
@@ -1910,9 +1818,10 @@ static int ffn_down_dgrad_impl(const void* dy_perm, const void* save_au, foremoe
     if (F % 256 == 0) launch_rows<256, false, kEpiSwigluBwd>(a, workspace, st, e0, e1);
     else launch_rows<128, false, kEpiSwigluBwd>(a, workspace, st, e0, e1);
   } else {
-    hipExtLaunchKernelGGL(f32_rows_kernel<kF32DownDgrad>, f32_grid(F, n_cap), dim3(256), 0, st, e0, e1, 0, (const float*)dy_perm,
-                       (const float*)w_down, (const float*)save_au, d, F, W, slot_offset, slot_widx, S, n_cap,
-                       (float*)d_au, nullptr);
+    launch_f32_rows(kF32DownDgrad,
+                    {(const float*)dy_perm, (const float*)w_down, (const float*)save_au, d, F, W, slot_offset,
+                     slot_widx, S, n_cap, (float*)d_au, nullptr},
+                    st, e0, e1);
   }
   return check_launch("foremoe_ffn_down_dgrad");
 }
@@ -1947,9 +1856,10 @@ static int ffn_gate_up_dgrad_impl(const void* d_au, foremoe_dtype dtype, int32_t
     if (d % 256 == 0) launch_rows<256, false, kEpiStore>(a, workspace, st, e0, e1);
     else launch_rows<128, false, kEpiStore>(a, workspace, st, e0, e1);
   } else {
-    hipExtLaunchKernelGGL(f32_rows_kernel<kF32GateUpDgrad>, f32_grid(d, n_cap), dim3(256), 0, st, e0, e1, 0, (const float*)d_au,
-                       (const float*)w_gate_up, nullptr, d, F, W, slot_offset, slot_widx, S, n_cap, (float*)dx_perm,
-                       nullptr);
+    launch_f32_rows(kF32GateUpDgrad,
+                    {(const float*)d_au, (const float*)w_gate_up, nullptr, d, F, W, slot_offset, slot_widx, S, n_cap,
+                     (float*)dx_perm, nullptr},
+                    st, e0, e1);
   }
   return check_launch("foremoe_ffn_gate_up_dgrad");
 }
@@ -2106,9 +2016,8 @@ static int wgrad_common(const char* who, const foremoe_wgrad_step* steps, int32_
     for (int m = 0; m < n; ++m) {
       const foremoe_wgrad_step& t = steps[m];
       if (t.S == 0 || t.n_cap == 0) continue;
-      hipLaunchKernelGGL(f32_wgrad_kernel, dim3((N + 15) / 16, (M + 15) / 16, G), dim3(256), 0, st,
-                         (const float*)t.a, lda, (const float*)t.b, ldb, M, N, t.slot_offset, t.slot_gidx, t.S, G,
-                         t.n_cap, part, parts, dw);
+      launch_f32_wgrad((const float*)t.a, lda, (const float*)t.b, ldb, M, N, t.slot_offset, t.slot_gidx, t.S, G,
+                       t.n_cap, part, parts, dw, st);
     }
   }
   return check_launch(who);
