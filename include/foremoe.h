@@ -261,21 +261,25 @@ int foremoe_dispatch_static(const int32_t* ids, int64_t T, int32_t K, const fore
  * and needs d % 128 == 0, F % 128 == 0 and (n_cap + 256) * max(d, 2F) * 2
  * below 2^32 (else FOREMOE_EUNSUPPORTED); f32 accepts any d, F >= 1.
  * 0 <= S <= FOREMOE_MAX_SLOTS.
- * foremoe_grouped_ffn_fwd = foremoe_ffn_gate_up_fwd then foremoe_ffn_down_fwd;
- * each of these two is a single kernel launch.
+ * foremoe_grouped_ffn_fwd = foremoe_ffn_gate_up_fwd then foremoe_ffn_down_fwd.
+ * Each of these two is a single kernel launch; the first is one launch for
+ * both in bf16 with a workspace (a row of Y is started once its row of H is
+ * done, so the second product fills the CUs that the first one's last round
+ * of tiles leaves idle), else two.
  *
  * workspace (optional, these and the input-gradient calls below): NULL, or
  * caller-owned device memory of at least foremoe_ffn_workspace_size()
  * bytes, 256-byte aligned, zero-filled before its first use (the library
- * leaves its counters at zero after every call). A last round of output
- * tiles that would occupy at most 7/16 of the GPU's CUs is cut along N into
- * half-width tiles when the tiles are 256 wide (with or without a
- * workspace). With the workspace, the (half) tiles of such a round are also
- * cut along K (in GEMMs whose K is at least 2048) into up to 4 pieces (as
- * many as keep at most 7/8 of the CUs busy), each computed by its own
- * workgroup; the last piece to finish adds the pieces' fp32 partial sums in
- * piece order and writes the tile. Results are deterministic either way and
- * equal with and without the workspace up to the fp32 summation order.
+ * leaves its counters at zero after every call). Rows are cut into tiles of
+ * 256; what a slot has left over is a tile of 256, 128 or 64 rows. A last
+ * round of output tiles that would occupy less than half of the GPU's CUs is
+ * cut along N into half-width tiles (with or without a workspace). With the
+ * workspace, the tiles of such a round are also cut along K into up to 4
+ * pieces (as many as keep at most 7/8 of the CUs busy), each computed by its
+ * own workgroup; the last piece to finish adds the pieces' fp32 partial sums
+ * in piece order and writes the tile. Results are deterministic either way
+ * and equal with and without the workspace, and in one launch or two, up to
+ * the fp32 summation order.
  * Calls that share a workspace
  * must not overlap in time (same stream, or ordered by events); after a
  * call that did not complete, zero the workspace again. Too small or
@@ -304,7 +308,8 @@ int foremoe_ffn_down_fwd(const void* h, foremoe_dtype dtype, int32_t d, int32_t 
  * d_au    [n_cap, 2F] out: dA in columns [0, F), dU in [F, 2F);
  * dx_perm [n_cap, d] out. Same dtype, shape and workspace rules as the
  * forward.
- * = foremoe_ffn_down_dgrad then foremoe_ffn_gate_up_dgrad (one launch each).
+ * = foremoe_ffn_down_dgrad then foremoe_ffn_gate_up_dgrad (one launch each;
+ * here one for both in bf16 with a workspace).
  */
 int foremoe_grouped_ffn_dgrad(const void* dy_perm, const void* save_au, foremoe_dtype dtype,
                               int32_t d, int32_t F, int32_t S, const int32_t* slot_offset,

@@ -55,14 +55,15 @@ inline size_t ws_bytes_needed(int64_t T, int32_t K, int32_t E) {
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float bf2f(uint32_t b16) { return __uint_as_float(b16 << 16); }
 
-__device__ __forceinline__ uint32_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7F800000u) == 0x7F800000u && (u & 0x007FFFFFu)) return 0x7FC0u;  // NaN
-  u += 0x7FFFu + ((u >> 16) & 1u);  // round to nearest, ties to even
-  return u >> 16;
+// Two floats rounded to nearest even in one instruction (v_cvt_pk_bf16_f32;
+// a NaN stays a NaN). Rounding in integer arithmetic takes 14, which made the
+// row GEMMs' epilogues and the combine wait for the vector ALU.
+__device__ __forceinline__ uint32_t pack_bf2(float lo, float hi) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const f32x2 v = {lo, hi};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
-
-__device__ __forceinline__ uint32_t pack_bf2(float lo, float hi) { return f2bf(lo) | (f2bf(hi) << 16); }
 
 // Lanes below this one in a 64-bit lane mask.
 __device__ __forceinline__ int lanes_below(uint64_t mask) {

@@ -1,9 +1,9 @@
 // Step 4: grouped SwiGLU expert FFN over the local slots (App. A), forward,
 // input gradient and weight gradient.
 //
-// bf16 path: persistent workgroups of 8 wavefronts (4 for 128-wide output
-// tiles) walk a tile list built on the device from the slot offsets (no
-// host sync). Operand tiles stream from
+// bf16 path: persistent workgroups of 8 wavefronts (4 for 128-wide weight
+// gradient tiles) walk a tile list built on the device from the slot offsets
+// (no host sync). Operand tiles stream from
 // HBM straight into LDS with range-checked buffer loads (buffer_load ... lds:
 // no staging registers; rows outside the current slot read as zero and no
 // load can leave its operand) through a ring of LDS stages, and are
@@ -69,9 +69,19 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 enum Epi { kEpiStore = 0, kEpiSwigluFwd = 1, kEpiSwigluBwd = 2 };
 
-__device__ __forceinline__ float silu_f(float a) { return a / (1.0f + __expf(-a)); }
+// 1 / (1 + exp(-a)), by the hardware reciprocal (within 1 ulp in fp32; the
+// results are rounded to bf16).
+__device__ __forceinline__ float sigmoid_f(float a) { return __builtin_amdgcn_rcpf(1.0f + __expf(-a)); }
 
 __device__ __forceinline__ int lane64() { return threadIdx.x & 63; }
+// The same, recomputed where it stands: a kernel with several tile shapes in
+// one loop would otherwise keep the lane offsets of all of them in registers
+// across the loop (and spill).
+__device__ __forceinline__ int lane64_here() {
+  int l = threadIdx.x & 63;
+  asm volatile("" : "+v"(l));
+  return l;
+}
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
 // Virtual workgroup id: workgroups are dispatched round-robin over the 8 XCDs,
@@ -84,27 +94,6 @@ __device__ __forceinline__ int xcd_virtual_id() {
   const int b = blockIdx.x, n = gridDim.x;
   if (!FM_XCD_MAP || n % 8 != 0) return b;
   return (b % 8) * (n / 8) + b / 8;
-}
-
-// Block-wide inclusive scan (up to 16 wavefronts; s_tmp holds one int per wave).
-__device__ int block_scan(int v, int* s_tmp, int& total) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int n = __shfl_up(v, o, 64);
-    if (lane >= o) v += n;
-  }
-  if (lane == 63) s_tmp[w] = v;
-  __syncthreads();
-  int before = 0;
-  total = 0;
-  for (int i = 0; i < nw; ++i) {
-    const int t = s_tmp[i];
-    if (i < w) before += t;
-    total += t;
-  }
-  __syncthreads();
-  return v + before;
 }
 
 // ---------------------------------------------------------------------------
@@ -178,8 +167,8 @@ struct KTile {
   // is the byte offset of tile row r. Fixed for a whole tile: each stage
   // moves the buffer resource instead.
   template <class RowOff>
-  __device__ __forceinline__ static uint32_t voff(RowOff rowoff, int i) {
-    const int l = lane64(), w = wave_id();
+  __device__ __forceinline__ static uint32_t voff(int l, RowOff rowoff, int i) {
+    const int w = wave_id();
     const int r = (w + NW * i) * RPI + l / CPR;
     const int c = (l % CPR) ^ swz(r);
     return rowoff(r) + (uint32_t)c * 16u;
@@ -196,11 +185,10 @@ struct KTile {
   // lane l gets row mn0 + l % 32, k = 16 kk + 8 (l / 32) + 0..7. The swizzle
   // only depends on l % 32 (mn0 is a multiple of 32), so the address splits
   // into a per-block lane offset and a per-k-step lane offset.
-  __device__ __forceinline__ static uint32_t lane_off(int mn0) {
-    return (uint32_t)(mn0 + (lane64() & 31)) * (BK * 2);
+  __device__ __forceinline__ static uint32_t lane_off(int l, int mn0) {
+    return (uint32_t)(mn0 + (l & 31)) * (BK * 2);
   }
-  __device__ __forceinline__ static uint32_t kstep_off(int kk) {
-    const int l = lane64();
+  __device__ __forceinline__ static uint32_t kstep_off(int l, int kk) {
     return (uint32_t)(((2 * kk + (l >> 5)) ^ swz(l & 31)) * 16);
   }
   __device__ __forceinline__ static bf16x8 frag(const char* lds, uint32_t off, const uint32_t* koff, int kk) {
@@ -221,8 +209,8 @@ struct MTile {
   // wavefront's share of the tile; koff(k) is the byte offset of the tile's
   // k-row k (relative to the stage's first k row) at the tile's first m/n.
   template <class KOff>
-  __device__ __forceinline__ static uint32_t voff(KOff koff, int i) {
-    const int l = lane64(), w = wave_id();
+  __device__ __forceinline__ static uint32_t voff(int l, KOff koff, int i) {
+    const int w = wave_id();
     const int k = (w + NW * i) * KPI + (l * 16) / RB;
     const int c = ((l * 16) % RB) / 16 ^ swz(k);
     return koff(k) + (uint32_t)c * 16u;
@@ -240,14 +228,13 @@ struct MTile {
   // and lane j receives one m/n at 4 consecutive k. The k row's low two bits
   // (which pick the swizzle) come from the lane alone, so the address is a
   // per-block lane offset plus an immediate (16 kk + 4 h) * RB.
-  __device__ __forceinline__ static uint32_t lane_off(int mn0) {
-    const int l = lane64();
+  __device__ __forceinline__ static uint32_t lane_off(int l, int mn0) {
     const int g = l >> 4, j = l & 15;
     const int krow = 8 * (g >> 1) + (j >> 2);
     const int mn = mn0 + 16 * (g & 1) + 4 * (j & 3);
     return (uint32_t)(krow * RB + (((mn >> 3) ^ swz(krow)) << 4) + (mn & 7) * 2);
   }
-  __device__ __forceinline__ static uint32_t kstep_off(int) { return 0; }
+  __device__ __forceinline__ static uint32_t kstep_off(int, int) { return 0; }
   __device__ __forceinline__ static bf16x8 frag(const char* lds, uint32_t off, const uint32_t*, int kk) {
     s16x4 v[2];
 #pragma unroll
@@ -299,15 +286,15 @@ struct Core {
   template <class AT, class BT, int BK>
   struct Offsets {
     uint32_t a[MB], b[NB], ka[BK / 16], kb[BK / 16];
-    __device__ __forceinline__ Offsets(int wm, int wn) {
+    __device__ __forceinline__ Offsets(int lane, int wm, int wn) {
 #pragma unroll
-      for (int i = 0; i < MB; ++i) a[i] = AT::lane_off(wm * WM + i * 32);
+      for (int i = 0; i < MB; ++i) a[i] = AT::lane_off(lane, wm * WM + i * 32);
 #pragma unroll
-      for (int j = 0; j < NB; ++j) b[j] = BT::lane_off(bcol(wn, j));
+      for (int j = 0; j < NB; ++j) b[j] = BT::lane_off(lane, bcol(wn, j));
 #pragma unroll
       for (int kk = 0; kk < BK / 16; ++kk) {
-        ka[kk] = AT::kstep_off(kk);
-        kb[kk] = BT::kstep_off(kk);
+        ka[kk] = AT::kstep_off(lane, kk);
+        kb[kk] = BT::kstep_off(lane, kk);
       }
     }
   };
@@ -330,8 +317,8 @@ struct Core {
 
   // The MFMAs of one k-step from register set CUR, with the LDS reads of a
   // later k-step's fragments (k-step nkk of the stage at nAs/nBs, into set
-  // NXT) interleaved: one read after each of the first MB + NB MFMAs, so the
-  // reads complete under the matrix work. extra(q), q < NX, runs right after
+  // NXT) interleaved: one read (two in the smallest wave tiles) after each of the
+  // first MFMAs, so the reads complete under the matrix work. extra(q), q < NX, runs right after
   // MFMA s when q < (s + 1) NX / (MB NB) and q >= s NX / (MB NB), evenly
   // over the k-step: the loads of a later stage, spread over the k-step so
   // that the address unit drains them while the matrix cores keep working.
@@ -339,6 +326,7 @@ struct Core {
   __device__ __forceinline__ void mfma_step(FragsT& f, const char* nAs, const char* nBs, const Offsets<AT, BT, BK>& o,
                                             int nkk, Extra&& extra) {
     constexpr int NM = MB * NB;
+    constexpr int RPM = (MB + NB + NM - 1) / NM;  // reads after each MFMA: one, or two in the smallest wave tiles
     static_assert(NX >= 0 && NX <= NM, "loads per k-step");
     static_assert(CUR != NXT, "the fragments being read go to another set");
     if constexpr (FM_SETPRIO > 0) __builtin_amdgcn_s_setprio(FM_SETPRIO);
@@ -347,9 +335,10 @@ struct Core {
       const int i = s / NB, j = s % NB;
       acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[CUR][j], f.a[CUR][i], acc[i][j], 0, 0, 0);
       if (FM_SETPRIO > 0 && s == NM - 1) __builtin_amdgcn_s_setprio(0);
-      if (s < MB + NB) {
-        if (s < MB) f.a[NXT][s] = AT::frag(nAs, o.a[s], o.ka, nkk);
-        else f.b[NXT][s - MB] = BT::frag(nBs, o.b[s - MB], o.kb, nkk);
+#pragma unroll
+      for (int t = s * RPM; t < (s + 1) * RPM && t < MB + NB; ++t) {
+        if (t < MB) f.a[NXT][t] = AT::frag(nAs, o.a[t], o.ka, nkk);
+        else f.b[NXT][t - MB] = BT::frag(nBs, o.b[t - MB], o.kb, nkk);
       }
       if constexpr (NX > 0) {
 #pragma unroll
@@ -359,24 +348,7 @@ struct Core {
 #pragma unroll
     for (int s = 0; s < NM; ++s) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-      if (s < MB + NB) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // one LDS read
-    }
-  }
-
-  template <class AT, class BT, int BK>
-  __device__ __forceinline__ void compute(const char* As, const char* Bs, const Offsets<AT, BT, BK>& o) {
-#pragma unroll
-    for (int kk = 0; kk < BK / 16; ++kk) {
-      bf16x8 af[MB], bfr[NB];
-#pragma unroll
-      for (int i = 0; i < MB; ++i) af[i] = AT::frag(As, o.a[i], o.ka, kk);
-#pragma unroll
-      for (int j = 0; j < NB; ++j) bfr[j] = BT::frag(Bs, o.b[j], o.kb, kk);
-#pragma unroll
-      for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
+      if (s * RPM < MB + NB) __builtin_amdgcn_sched_group_barrier(0x100, RPM, 0);  // its LDS reads
     }
   }
 };
@@ -431,21 +403,21 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-// Fragment read distance of the row GEMMs: 2 for the gate/up forward (2%
-// faster than 1 on the benchmark), 1 for the others (with a third register
-// set they spill, and run 4-6% slower).
-#ifndef FM_FRAG_DIST_FWD
-#define FM_FRAG_DIST_FWD 2
-#endif
+// Fragment read distance: 2 in the row GEMMs' 256-row tiles (gate/up forward
+// 2% faster than with 1, the others the same), 1 in their smaller tiles and
+// in the weight gradients (a third register set makes those spill).
 #ifndef FM_FRAG_DIST
 #define FM_FRAG_DIST 1
 #endif
+#ifndef FM_FRAG_DIST_ROWS
+#define FM_FRAG_DIST_ROWS 2
+#endif
 
 // Fragments read one k-step ahead (two register sets).
-template <class CoreT, class AT, class BT, int BK, int NS, class Issue>
+template <class CoreT, class AT, class BT, int BK, int NS, class Issue, class Started>
 __device__ __forceinline__ void pipelined_k_loop_d1(CoreT& core, char* lds, int KT,
                                                     const typename CoreT::template Offsets<AT, BT, BK>& o,
-                                                    Issue&& issue) {
+                                                    Issue&& issue, bool drain, Started&& started) {
   static_assert(BK % 32 == 0, "the last k-step's fragments must be read before the barrier");
   constexpr int KK = BK / 16;
   constexpr int STAGE = AT::BYTES + BT::BYTES;
@@ -453,8 +425,11 @@ __device__ __forceinline__ void pipelined_k_loop_d1(CoreT& core, char* lds, int 
   // the loads of a stage ride on SPREAD k-steps: the last one of the stage
   // before and the first SPREAD - 1 of the next; load p goes with k-step
   // j when lo(j) <= p < lo(j + 1)
-  constexpr int SPREAD = FM_LOAD_SPREAD < KK ? FM_LOAD_SPREAD : KK;
-  static_assert(SPREAD >= 1, "load spread");
+  // (and no k-step carries more loads than it has MFMAs)
+  constexpr int MIN_SPREAD = (PER + CoreT::MB * CoreT::NB - 1) / (CoreT::MB * CoreT::NB);
+  constexpr int WANT = FM_LOAD_SPREAD > MIN_SPREAD ? FM_LOAD_SPREAD : MIN_SPREAD;
+  constexpr int SPREAD = WANT < KK ? WANT : KK;
+  static_assert(SPREAD >= MIN_SPREAD, "load spread");
   auto lo = [](int j) constexpr { return j * PER / SPREAD; };
   typename CoreT::template Frags<2> f;
   // stages 0 .. NS-2 whole, and the part of stage NS-1 that a previous
@@ -464,8 +439,10 @@ __device__ __forceinline__ void pipelined_k_loop_d1(CoreT& core, char* lds, int 
 #pragma unroll
     for (int p = 0; p < (s < NS - 1 ? PER : lo(1)); ++p) issue(s, p);
   }
-  wait_vm<(NS - 2) * PER + lo(1)>();
+  if (drain) wait_vm<0>();
+  else wait_vm<(NS - 2) * PER + lo(1)>();
   __syncthreads();
+  started();
   CoreT::template load_frags<AT, BT, BK>(f, 0, lds, lds + AT::BYTES, o, 0);
   for (int kt = 0; kt < KT; ++kt) {
     const char* st = lds + (kt % NS) * STAGE;
@@ -497,10 +474,10 @@ __device__ __forceinline__ void pipelined_k_loop_d1(CoreT& core, char* lds, int 
 // stage kt+NS go into it during k-steps KK - D .. KK - D + SPREAD - 1. The
 // set of global k-step g is g % (D + 1); the stage loop is unrolled U times
 // so that every set index is a compile-time constant.
-template <class CoreT, class AT, class BT, int BK, int NS, int D, class Issue>
+template <class CoreT, class AT, class BT, int BK, int NS, int D, class Issue, class Started>
 __device__ __forceinline__ void pipelined_k_loop_deep(CoreT& core, char* lds, int KT,
                                                       const typename CoreT::template Offsets<AT, BT, BK>& o,
-                                                      Issue&& issue) {
+                                                      Issue&& issue, bool drain, Started&& started) {
   constexpr int KK = BK / 16;
   constexpr int FS = D + 1;
   constexpr int STAGE = AT::BYTES + BT::BYTES;
@@ -520,8 +497,9 @@ __device__ __forceinline__ void pipelined_k_loop_deep(CoreT& core, char* lds, in
 #pragma unroll
     for (int p = 0; p < PER; ++p) issue(s, p);
   }
-  wait_stage<NS, PER>(NS - 1);  // stage 0 has landed
+  wait_stage<NS, PER>(drain ? 0 : NS - 1);  // stage 0 has landed
   __syncthreads();
+  started();
   static_for<0, D>([&](auto kc) {
     constexpr int k = decltype(kc)::value;
     CoreT::template load_frags<AT, BT, BK>(f, k, lds, lds + AT::BYTES, o, k);
@@ -558,14 +536,16 @@ __device__ __forceinline__ void pipelined_k_loop_deep(CoreT& core, char* lds, in
   wait_vm<0>();  // the (empty) loads of stages past the last have landed too
 }
 
-template <class CoreT, class AT, class BT, int BK, int NS, int D = FM_FRAG_DIST, class Issue>
+// drain: the first wait is for every vector-memory operation of the
+// wavefront, older stores included. started() runs after the first barrier.
+template <class CoreT, class AT, class BT, int BK, int NS, int D, class Issue, class Started>
 __device__ __forceinline__ void pipelined_k_loop(CoreT& core, char* lds, int KT,
                                                  const typename CoreT::template Offsets<AT, BT, BK>& o,
-                                                 Issue&& issue) {
+                                                 Issue&& issue, bool drain, Started&& started) {
   if constexpr (D >= 2 && BK / 16 >= D)
-    pipelined_k_loop_deep<CoreT, AT, BT, BK, NS, D>(core, lds, KT, o, issue);
+    pipelined_k_loop_deep<CoreT, AT, BT, BK, NS, D>(core, lds, KT, o, issue, drain, started);
   else
-    pipelined_k_loop_d1<CoreT, AT, BT, BK, NS>(core, lds, KT, o, issue);
+    pipelined_k_loop_d1<CoreT, AT, BT, BK, NS>(core, lds, KT, o, issue, drain, started);
 }
 
 // ---------------------------------------------------------------------------
@@ -578,43 +558,126 @@ struct RowsArgs {
   const uint16_t* B;  // weights; matrix w starts at B + w * wstride
   int64_t ldb;
   int64_t wstride;
-  int W;
   int K;
   int N;   // output columns of the tile grid (2F for the fused gate/up)
   int F;   // SwiGLU width
-  const int32_t* slot_offset;
-  const int32_t* slot_widx;
-  int S;
-  int64_t n_cap;
   uint16_t* C;  // main output
   int64_t ldc;
   uint16_t* C2;  // forward: saved [A | U] or NULL
   int64_t ldc2;
   const uint16_t* AU;  // input gradient: saved [A | U]
   int64_t ldau;
-  float* sk_part;      // split workspace: one partial tile per workgroup, or NULL
-  unsigned* sk_count;  // arrival count per tile of the split round (zero between calls)
 };
 
-// Per-slot m-tile prefix in LDS: s_mt[j] = m-tiles of slots before j.
-template <int BM>
-__device__ void build_slot_tiles(const int32_t* __restrict__ off, int S, int64_t n_cap, int* s_mt, int* s_tmp) {
-  int carry = 0;
-  for (int j0 = 0; j0 < S; j0 += (int)blockDim.x) {
-    const int j = j0 + threadIdx.x;
-    int n = 0;
-    if (j < S) {
-      int64_t lo = off[j], hi = off[j + 1];
-      lo = lo < 0 ? 0 : (lo > n_cap ? n_cap : lo);
-      hi = hi < 0 ? 0 : (hi > n_cap ? n_cap : hi);
-      n = hi > lo ? (int)((hi - lo + BM - 1) / BM) : 0;
+// One launch: one GEMM, or two with the second consuming the first's rows.
+struct FfnArgs {
+  RowsArgs p[2];  // gate/up then down forward, or down then gate/up input gradient
+  int phases;     // bit i: run p[i]
+  int W;
+  const int32_t* slot_offset;
+  const int32_t* slot_widx;
+  int S;
+  int64_t n_cap;
+  float* part;         // workspace: partial tiles of tiles cut along K, or NULL
+  unsigned* arrived;   // workspace: arrival count per (half) tile cut along K
+  unsigned* queue;     // workspace: kQueues counters per GEMM, then the finished workgroups
+  unsigned* row_done;  // workspace: halves of column tiles done per row tile of the first GEMM
+};
+
+// Workspace of the row GEMMs: counters (zero between calls), then the fp32
+// partial tiles of the pieces (at most 128 KiB each).
+constexpr size_t kRowsArrivedOff = 0;            // arrival counters of both GEMMs
+constexpr size_t kRowsQueueOff = 4096;           // queue counters
+constexpr size_t kRowsDoneOff = 12288;           // per row tile
+constexpr size_t kRowsPartOff = 65536;
+constexpr int kMaxRowTiles = (int)((kRowsPartOff - kRowsDoneOff) / 4);
+constexpr int kPieceBytes = 128 * 1024;
+constexpr int kCutUnits = 224;  // units of a GEMM's tiles cut along K, at most (7/8 of 256 workgroups)
+constexpr int kQueues = 8;       // one per XCD
+// Queue counters are 256 bytes apart: in one line, the atomics of all
+// workgroups (they end their tiles together) would queue up behind each other.
+constexpr int kQueueStride = 64;
+
+// Row tiles of a launch, built by every workgroup from the slot offsets. A
+// slot's rows are cut into tiles of 256; what is left over is a tile of its
+// own: of 256 rows if more than 128 are left, of 128 ("short") if more than
+// 64, else of 64 ("thin"). Row tiles are numbered: the 256-row ones slot by
+// slot, then the short ones, then the thin ones.
+struct RowTiles {
+  int full[FOREMOE_MAX_SLOTS + 1];  // 256-row tiles of the slots before
+  uint16_t tail[FOREMOE_MAX_SLOTS];  // slots of the short tiles from the front, of the thin ones from the back
+  int off[FOREMOE_MAX_SLOTS + 1];    // the slots' row offsets, clamped to the buffer
+  int widx[FOREMOE_MAX_SLOTS];
+  int n_short, n_thin;
+};
+
+__device__ __forceinline__ int64_t clamp_row(int32_t v, int64_t n_cap) {
+  return v < 0 ? 0 : (v > n_cap ? n_cap : v);
+}
+
+// Up to 64 slots: one wavefront does it all and no barrier but the last is
+// needed (every launch starts with this).
+__device__ void build_row_tiles(const int32_t* __restrict__ off, const int32_t* __restrict__ widx, int S,
+                                int64_t n_cap, RowTiles& R, int* s_tmp) {
+  const bool one_wave = S <= 64;
+  const int nthreads = one_wave ? 64 : (int)blockDim.x;
+  int full0 = 0, tail0 = 0;  // tail0: short tiles in the low half, thin ones in the high half
+  if (!one_wave || threadIdx.x < 64) {
+    for (int j0 = 0; j0 < S; j0 += nthreads) {
+      const int j = j0 + threadIdx.x, lane = lane64();
+      int full = 0, tail = 0;
+      if (j < S) {
+        const int beg = (int)clamp_row(off[j], n_cap), end = (int)clamp_row(off[j + 1], n_cap), rows = end - beg;
+        R.off[j] = beg;
+        if (j == S - 1) R.off[S] = end;
+        R.widx[j] = widx[j];
+        if (rows > 0) {
+          const int left = rows % 256;
+          full = rows / 256 + (left > 128);
+          tail = left > 128 || left == 0 ? 0 : (left > 64 ? 1 : 1 << 16);
+        }
+      }
+      int fi = full, ti = tail;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int f = __shfl_up(fi, o, 64), t = __shfl_up(ti, o, 64);
+        if (lane >= o) {
+          fi += f;
+          ti += t;
+        }
+      }
+      int full_all = __shfl(fi, 63, 64), tail_all = __shfl(ti, 63, 64);
+      if (!one_wave) {
+        const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+        if (lane == 63) {
+          s_tmp[w] = fi;
+          s_tmp[8 + w] = ti;
+        }
+        __syncthreads();
+        full_all = tail_all = 0;
+        for (int i = 0; i < nw; ++i) {
+          if (i < w) {
+            fi += s_tmp[i];
+            ti += s_tmp[8 + i];
+          }
+          full_all += s_tmp[i];
+          tail_all += s_tmp[8 + i];
+        }
+        __syncthreads();
+      }
+      if (j < S) R.full[j] = full0 + fi - full;
+      const int before = tail0 + ti - tail;
+      if (tail == 1) R.tail[before & 0xFFFF] = (uint16_t)j;
+      if (tail == 1 << 16) R.tail[FOREMOE_MAX_SLOTS - 1 - (before >> 16)] = (uint16_t)j;
+      full0 += full_all;
+      tail0 += tail_all;
     }
-    int total;
-    const int incl = block_scan(n, s_tmp, total);
-    if (j < S) s_mt[j] = carry + incl - n;
-    carry += total;
+    if (threadIdx.x == 0) {
+      R.full[S] = full0;
+      R.n_short = tail0 & 0xFFFF;
+      R.n_thin = tail0 >> 16;
+    }
   }
-  if (threadIdx.x == 0) s_mt[S] = carry;
   __syncthreads();
 }
 
@@ -645,8 +708,8 @@ struct StagedRows {
         make_uint2(pack_bf2(v0, v1), pack_bf2(v2, v3));
   }
   // the 16-byte chunk lane l reads back in instruction it: row, chunk index
-  __device__ __forceinline__ static int row_of(int it) { return it * RPI + lane64() / CPR; }
-  __device__ __forceinline__ static int col_of() { return lane64() % CPR; }
+  __device__ __forceinline__ static int row_of(int lane, int it) { return it * RPI + lane / CPR; }
+  __device__ __forceinline__ static int col_of(int lane) { return lane % CPR; }
   __device__ __forceinline__ static uint4 get(const char* base, int r, int c) {
     return *reinterpret_cast<const uint4*>(base + chunk(r, c));
   }
@@ -666,8 +729,8 @@ struct StagedRowsF32 {
   __device__ __forceinline__ static void put4(char* base, int r, int col, float v0, float v1, float v2, float v3) {
     *reinterpret_cast<float4*>(base + chunk(r, col >> 2)) = make_float4(v0, v1, v2, v3);
   }
-  __device__ __forceinline__ static int row_of(int it) { return it * RPI + lane64() / LPR; }
-  __device__ __forceinline__ static int col_of() { return lane64() % LPR; }  // in units of 8 values
+  __device__ __forceinline__ static int row_of(int lane, int it) { return it * RPI + lane / LPR; }
+  __device__ __forceinline__ static int col_of(int lane) { return lane % LPR; }  // in units of 8 values
   __device__ __forceinline__ static void get8(const char* base, int r, int c8, float* f) {
     const float4 lo = *reinterpret_cast<const float4*>(base + chunk(r, 2 * c8));
     const float4 hi = *reinterpret_cast<const float4*>(base + chunk(r, 2 * c8 + 1));
@@ -698,18 +761,57 @@ __device__ __forceinline__ uint4 pack8(const float* f) {
   return make_uint4(pack_bf2(f[0], f[1]), pack_bf2(f[2], f[3]), pack_bf2(f[4], f[5]), pack_bf2(f[6], f[7]));
 }
 
+template <class T>
+__device__ __forceinline__ T* uniform_ptr(T* p) {
+  const uint64_t v = (uint64_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return (T*)(((uint64_t)hi << 32) | lo);
+}
+
+// 16-byte buffer accesses. kCoherentDevice (the SC1 cache-policy bit) writes
+// through to memory, so that a workgroup of another XCD can read the bytes
+// in the same launch.
+constexpr int kCoherentDevice = 16;
+template <int AUX>
+__device__ __forceinline__ void buffer_store16(__amdgpu_buffer_rsrc_t rs, uint32_t off, uint4 v) {
+  i32x4 t;
+  t.x = (int)v.x;
+  t.y = (int)v.y;
+  t.z = (int)v.z;
+  t.w = (int)v.w;
+  __builtin_amdgcn_raw_buffer_store_b128(t, rs, off, 0, AUX);
+}
+__device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+  const auto v = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+  return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
 // Writes this wave's output block: rows wrow0 .. wrow0 + WM - 1 (those below
 // rend), output columns n0 + wn * WN .. (SwiGLU forward: H columns
 // f0 + wn * GW ..). `ep` is the wave's private LDS region.
+// Columns past the output's width (the last tile of a width that is no
+// multiple of 256) are not stored.
 template <class CoreT, int EPI>
 __device__ __forceinline__ void rows_epilogue(const RowsArgs& a, const CoreT& core, char* ep, int64_t wrow0,
                                               int64_t rend, int n0, int f0, int wn) {
-  const int lane = lane64();
+  const int lane = lane64_here();
   const int l32 = lane & 31, c4 = (lane >> 5) * 4;
+  // Buffer resources over this wave's rows: those past the slot, and columns
+  // past the width (moved past the resource's end), fall outside and are
+  // neither loaded nor stored. No access is behind a branch, so the compiler
+  // can count them.
+  const int64_t left = rend - wrow0;
+  const int64_t nrow = left <= 0 ? 0 : (left < CoreT::WM ? left : CoreT::WM);
+  const uint32_t ldc2 = (uint32_t)a.ldc * 2u;
+  auto rows_of = [&](const uint16_t* p, int64_t ld) {
+    return __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(const_cast<uint16_t*>(p) + (nrow ? wrow0 * ld : 0)), (short)0,
+                                             __builtin_amdgcn_readfirstlane((int)(nrow * ld * 2)), 0x00020000);
+  };
+  const __amdgpu_buffer_rsrc_t cs = rows_of(a.C, a.ldc);
+  constexpr uint32_t kOutside = 0x80000000u;
 #pragma unroll
   for (int i = 0; i < CoreT::MB; ++i) {
-    const int64_t prow0 = wrow0 + i * 32;
-    if (prow0 >= rend) break;
     if constexpr (EPI == kEpiSwigluFwd) {
       using SR = StagedRows<CoreT::GW * 2>;
       constexpr int H = CoreT::NB / 2;
@@ -726,31 +828,31 @@ __device__ __forceinline__ void rows_epilogue(const RowsArgs& a, const CoreT& co
           for (int e = 0; e < 4; ++e) {
             av[e] = core.acc[i][jj][g * 4 + e];
             uv[e] = core.acc[i][jj + H][g * 4 + e];
-            hv[e] = silu_f(av[e]) * uv[e];
+            hv[e] = av[e] * sigmoid_f(av[e]) * uv[e];
           }
           SR::put4(sh, l32, col, hv[0], hv[1], hv[2], hv[3]);
           SR::put4(sa, l32, col, av[0], av[1], av[2], av[3]);
           SR::put4(su, l32, col, uv[0], uv[1], uv[2], uv[3]);
         }
-      const int fc = f0 + wn * CoreT::GW + SR::col_of() * 8;
+      const int fc = f0 + wn * CoreT::GW + SR::col_of(lane) * 8;
+      const __amdgpu_buffer_rsrc_t cs2 = rows_of(a.C2, a.C2 ? a.ldc2 : 0);  // ldc2 = 2 ldc
 #pragma unroll
       for (int it = 0; it < SR::NI; ++it) {
-        const int r = SR::row_of(it);
-        const int64_t row = prow0 + r;
-        const uint4 vh = SR::get(sh, r, SR::col_of());
-        const uint4 va = SR::get(sa, r, SR::col_of());
-        const uint4 vu = SR::get(su, r, SR::col_of());
-        if (row < rend) {
-          *reinterpret_cast<uint4*>(a.C + row * a.ldc + fc) = vh;
-          if (a.C2) {
-            *reinterpret_cast<uint4*>(a.C2 + row * a.ldc2 + fc) = va;
-            *reinterpret_cast<uint4*>(a.C2 + row * a.ldc2 + a.F + fc) = vu;
-          }
-        }
+        const int r = SR::row_of(lane, it);
+        const uint4 vh = SR::get(sh, r, SR::col_of(lane));
+        const uint4 va = SR::get(sa, r, SR::col_of(lane));
+        const uint4 vu = SR::get(su, r, SR::col_of(lane));
+        buffer_store16<kCoherentDevice>(cs, (uint32_t)(i * 32 + r) * ldc2 + (uint32_t)fc * 2u, vh);
+        // (a NULL save_au: an empty resource)
+        const uint32_t o2 = (uint32_t)(i * 32 + r) * (2u * ldc2) + (uint32_t)fc * 2u;
+        buffer_store16<0>(cs2, o2, va);
+        buffer_store16<0>(cs2, o2 + ldc2, vu);
       }
     } else if constexpr (EPI == kEpiSwigluBwd) {
       using SR = StagedRowsF32<CoreT::WN * 4>;
-      const int nc = n0 + wn * CoreT::WN + SR::col_of() * 8;
+      const __amdgpu_buffer_rsrc_t aus = rows_of(a.AU, a.ldau);  // ldau = ldc
+      const int nc = n0 + wn * CoreT::WN + SR::col_of(lane) * 8;
+      const uint32_t outside = nc < a.N ? 0u : kOutside;
 #pragma unroll
       for (int jj = 0; jj < CoreT::NB; ++jj)
 #pragma unroll
@@ -766,35 +868,32 @@ __device__ __forceinline__ void rows_epilogue(const RowsArgs& a, const CoreT& co
       uint4 xa[SR::NI], xu[SR::NI];
 #pragma unroll
       for (int it = 0; it < SR::NI; ++it) {
-        const int64_t row = prow0 + SR::row_of(it);
-        xa[it] = xu[it] = make_uint4(0, 0, 0, 0);
-        if (row < rend) {
-          xa[it] = *reinterpret_cast<const uint4*>(a.AU + row * a.ldau + nc);
-          xu[it] = *reinterpret_cast<const uint4*>(a.AU + row * a.ldau + a.F + nc);
-        }
+        const uint32_t o = outside | ((uint32_t)(i * 32 + SR::row_of(lane, it)) * ldc2 + (uint32_t)nc * 2u);
+        xa[it] = buffer_load16(aus, o);
+        xu[it] = buffer_load16(aus, o + 2u * (uint32_t)a.F);
       }
 #pragma unroll
       for (int it = 0; it < SR::NI; ++it) {
-        const int r = SR::row_of(it);
-        const int64_t row = prow0 + r;
+        const int r = SR::row_of(lane, it);
         // dH at columns nc .. nc + 7; saved A in [0, F), U in [F, 2F)
         float dh[8], A8[8], U8[8], da[8], du[8];
-        SR::get8(ep, r, SR::col_of(), dh);
-        if (row >= rend) continue;
+        SR::get8(ep, r, SR::col_of(lane), dh);
         unpack8(xa[it], A8);
         unpack8(xu[it], U8);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float sg = 1.0f / (1.0f + __expf(-A8[e]));
+          const float sg = sigmoid_f(A8[e]);
           da[e] = dh[e] * U8[e] * (sg + A8[e] * sg * (1.0f - sg));
           du[e] = dh[e] * A8[e] * sg;
         }
-        *reinterpret_cast<uint4*>(a.C + row * a.ldc + nc) = pack8(da);
-        *reinterpret_cast<uint4*>(a.C + row * a.ldc + a.F + nc) = pack8(du);
+        const uint32_t o = outside | ((uint32_t)(i * 32 + r) * ldc2 + (uint32_t)nc * 2u);
+        buffer_store16<kCoherentDevice>(cs, o, pack8(da));
+        buffer_store16<kCoherentDevice>(cs, o + 2u * (uint32_t)a.F, pack8(du));
       }
     } else {
       using SR = StagedRows<CoreT::WN * 2>;
-      const int nc = n0 + wn * CoreT::WN + SR::col_of() * 8;
+      const int nc = n0 + wn * CoreT::WN + SR::col_of(lane) * 8;
+      const uint32_t outside = nc < a.N ? 0u : kOutside;
 #pragma unroll
       for (int jj = 0; jj < CoreT::NB; ++jj)
 #pragma unroll
@@ -805,19 +904,17 @@ __device__ __forceinline__ void rows_epilogue(const RowsArgs& a, const CoreT& co
         }
 #pragma unroll
       for (int it = 0; it < SR::NI; ++it) {
-        const int r = SR::row_of(it);
-        const int64_t row = prow0 + r;
-        const uint4 v = SR::get(ep, r, SR::col_of());
-        if (row < rend) *reinterpret_cast<uint4*>(a.C + row * a.ldc + nc) = v;
+        const int r = SR::row_of(lane, it);
+        const uint4 v = SR::get(ep, r, SR::col_of(lane));
+        buffer_store16<0>(cs, outside | ((uint32_t)(i * 32 + r) * ldc2 + (uint32_t)nc * 2u), v);
       }
     }
   }
 }
 
-// Tail split of the row GEMM (the last, partial round of tiles cut along
-// K): the partial sums of a piece stay in the MFMA register layout, one
-// workspace slot per workgroup, then per wave, then per float4 index with
-// the 64 lanes consecutive, so every store and load moves a whole 1 KiB.
+// Tiles cut along K: the partial sums of a piece stay in the MFMA register
+// layout, one workspace slot per piece, then per wave, then per float4 index
+// with the 64 lanes consecutive, so every store and load moves a whole 1 KiB.
 //
 // The pieces of a tile may run on different XCDs, whose L2 caches are not
 // coherent with each other. The partial sums are therefore stored and loaded
@@ -827,31 +924,21 @@ __device__ __forceinline__ void rows_epilogue(const RowsArgs& a, const CoreT& co
 // fence is needed: such a fence would write back and invalidate the whole
 // L2 of the XCD, evicting the operand tiles that every other workgroup there
 // is using.
-#ifndef FM_TAIL_SPREAD
-#define FM_TAIL_SPREAD 1
-#endif
 #ifndef FM_SPLIT_MAX
 #define FM_SPLIT_MAX 4
 #endif
-#ifndef FM_SPLIT_MIN_K
-#define FM_SPLIT_MIN_K 32
-#endif
-// Cut a small partial last round of 256-wide tiles along N (0: never).
-#ifndef FM_NSPLIT
-#define FM_NSPLIT 1
-#endif
 constexpr int kSplitMax = FM_SPLIT_MAX;    // pieces per tile at most (2..4)
-constexpr int kSplitMinK = FM_SPLIT_MIN_K;  // k-steps a tile needs before it is split
 #ifndef FM_SPLIT_REGION_KIB
 #define FM_SPLIT_REGION_KIB 16
 #endif
 constexpr int kSplitRegionKiB = FM_SPLIT_REGION_KIB;  // LDS per wave for the pieces in flight
-constexpr int kCoherentDevice = 16;  // cache policy of buffer accesses: SC1
 
+// Byte offset of float4 group e of this wavefront in piece pc's slot.
 template <class CoreT, int NW>
-__device__ __forceinline__ uint32_t split_offset(int slot, int wave, int e) {
+__device__ __forceinline__ uint32_t split_offset(int lane, int pc, int wave, int e) {
   constexpr int PER_WAVE = CoreT::MB * CoreT::NB * 4 * 64;  // float4 per wave
-  return (uint32_t)((((uint32_t)slot * NW + wave) * PER_WAVE + (uint32_t)e * 64 + lane64()) * 16u);
+  static_assert(NW * PER_WAVE * 16 <= kPieceBytes, "a piece fits its slot");
+  return (uint32_t)(pc * kPieceBytes + (wave * PER_WAVE + e * 64 + lane) * 16);
 }
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t split_rsrc(float* part, uint32_t bytes) {
@@ -866,7 +953,8 @@ __device__ __forceinline__ void split_dma16(__amdgpu_buffer_rsrc_t rs, uint32_t 
 }
 
 template <class CoreT, int NW>
-__device__ __forceinline__ void split_store(__amdgpu_buffer_rsrc_t rs, int slot, int wave, const CoreT& core) {
+__device__ __forceinline__ void split_store(__amdgpu_buffer_rsrc_t rs, int pc, int wave, const CoreT& core) {
+  const int lane = lane64_here();
 #pragma unroll
   for (int i = 0; i < CoreT::MB; ++i)
 #pragma unroll
@@ -878,7 +966,7 @@ __device__ __forceinline__ void split_store(__amdgpu_buffer_rsrc_t rs, int slot,
         v.y = __float_as_int(core.acc[i][j][4 * c + 1]);
         v.z = __float_as_int(core.acc[i][j][4 * c + 2]);
         v.w = __float_as_int(core.acc[i][j][4 * c + 3]);
-        __builtin_amdgcn_raw_buffer_store_b128(v, rs, split_offset<CoreT, NW>(slot, wave, (i * CoreT::NB + j) * 4 + c),
+        __builtin_amdgcn_raw_buffer_store_b128(v, rs, split_offset<CoreT, NW>(lane, pc, wave, (i * CoreT::NB + j) * 4 + c),
                                                0, kCoherentDevice);
       }
 }
@@ -897,6 +985,7 @@ __device__ __forceinline__ void split_sum(__amdgpu_buffer_rsrc_t rs, int wave, c
   constexpr int NE = CoreT::MB * CoreT::NB * 4;  // float4 groups per lane
   constexpr int GR = kSplitRegionKiB / SPLIT;    // groups per round
   const uint32_t wbase = lds_addr(wl);
+  const int lane = lane64_here();
   static_for<0, (NE + GR - 1) / GR>([&](auto rc) {
     constexpr int e0 = decltype(rc)::value * GR;
     constexpr int ne = NE - e0 < GR ? NE - e0 : GR;
@@ -904,15 +993,15 @@ __device__ __forceinline__ void split_sum(__amdgpu_buffer_rsrc_t rs, int wave, c
     for (int g = 0; g < ne; ++g)
 #pragma unroll
       for (int pc = 0; pc < SPLIT; ++pc)
-        split_dma16(rs, wbase + (pc * GR + g) * 1024, split_offset<CoreT, NW>(pc, wave, e0 + g));
+        split_dma16(rs, wbase + (pc * GR + g) * 1024, split_offset<CoreT, NW>(lane, pc, wave, e0 + g));
     wait_vm<0>();  // this wave's loads have landed in its LDS region
 #pragma unroll
     for (int g = 0; g < ne; ++g) {
       const int e = e0 + g, c = e % 4, j = (e / 4) % CoreT::NB, i = e / 4 / CoreT::NB;
-      float4 t = *reinterpret_cast<const float4*>(wl + g * 1024 + lane64() * 16);
+      float4 t = *reinterpret_cast<const float4*>(wl + g * 1024 + lane * 16);
 #pragma unroll
       for (int pc = 1; pc < SPLIT; ++pc) {
-        const float4 x = *reinterpret_cast<const float4*>(wl + (pc * GR + g) * 1024 + lane64() * 16);
+        const float4 x = *reinterpret_cast<const float4*>(wl + (pc * GR + g) * 1024 + lane * 16);
         t.x += x.x;
         t.y += x.y;
         t.z += x.z;
@@ -927,207 +1016,538 @@ __device__ __forceinline__ void split_sum(__amdgpu_buffer_rsrc_t rs, int wave, c
   });
 }
 
-template <int BM, int BN, int BK, int NS, int WGM, int WGN, bool B_KMAJ, int EPI>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_rows_kernel(RowsArgs a) {
+// Work of one GEMM of a launch: tiles (row tile x 256 columns) in a fixed
+// order, the 256-row ones first. The last `r` tiles may be cut: those of 256
+// rows into `h` halves of 128 columns, and then every (half) tile into `s`
+// pieces along K, each a unit of its own.
+struct PhaseUnits {
+  int nt;     // column tiles
+  int kt;     // k-steps
+  int small;  // tiles of 128 or 64 rows
+  int plain;  // tiles that are not cut
+  int full_cut;  // 256-row tiles among the cut ones
+  int h, s;
+  int total;  // units
+};
+
+// nfull, nsmall: row tiles of 256 rows and of fewer. r: the tiles of a last,
+// partial round (all tiles, if they make less than one round of the G
+// workgroups).
+__device__ __forceinline__ PhaseUnits phase_units(int nfull, int nsmall, int N, int K, int G, int r, bool ws) {
+  PhaseUnits u;
+  u.nt = (N + 255) / 256;
+  u.kt = K / FM_ROWS_BK;
+  u.small = nsmall * u.nt;
+  const int tiles = nfull * u.nt + u.small;
+  r = r < tiles ? r : tiles;
+  u.full_cut = r > u.small ? r - u.small : 0;
+  const int rs = r - u.full_cut;
+  // A partial last round that leaves the chip less than half busy is cut
+  // along N first: two half-width tiles on two workgroups, with no partial
+  // sums (measured faster than cutting the same round along K).
+  u.h = (u.full_cut > 0 && 8 * (2 * u.full_cut + rs) <= 7 * G) ? 2 : 1;
+  // Then, with the workspace, along K: as many pieces as keep at most 7/8 of
+  // the workgroups busy (a cut that fills the chip measured slower than the
+  // round uncut and spread out), none shorter than 16 k-steps (8 for the
+  // small tiles, whose partial sums are a quarter).
+  u.s = 1;
+  const int n = u.full_cut * u.h + rs;
+  if (ws && n > 0 && (u.full_cut == 0 || (u.h == 2 && u.kt >= 32))) {
+    int s = (7 * G / 8) / n;
+    s = s < kSplitMax ? s : kSplitMax;
+    const int most = u.kt / (u.full_cut ? 16 : 8);
+    s = s < most ? s : most;
+    u.s = s < 1 ? 1 : s;
+  }
+  u.plain = tiles - r;
+  u.total = u.plain + n * u.s;
+  return u;
+}
+
+// Queue of XCD x: the units it takes, in order. Whole rounds of G units are
+// dealt in blocks of G / nq consecutive units (which share operand tiles in
+// that XCD's L2), a last partial round in nq nearly equal blocks, so that it
+// is spread over all XCDs.
+struct Queues {
+  int G, nq, c;  // c = G / nq
+  __device__ __forceinline__ int rounds(int total) const { return G == 256 ? total >> 8 : total / G; }
+  __device__ __forceinline__ int part(int rest, int x) const { return nq == kQueues ? x * rest / kQueues : x * rest; }
+  __device__ __forceinline__ int length(int total, int x) const {
+    const int r = rounds(total), rest = total - r * G;
+    return r * c + part(rest, x + 1) - part(rest, x);
+  }
+  __device__ __forceinline__ int unit(int total, int x, int k) const {
+    const int r = rounds(total), rest = total - r * G, q = c == 32 ? k >> 5 : k / c;
+    return q < r ? q * G + x * c + k - q * c : r * G + part(rest, x) + k - r * c;
+  }
+};
+
+// Order of a slot's 256-row tiles: column tiles first, or on wide outputs in
+// groups of 8 row tiles (which share every weight tile), row tile by row tile
+// within each column tile of the group. An XCD's 32 units in flight share its
+// L2: column tiles first, they span 32 / nt row tiles x nt column tiles, few
+// operand tiles while nt is small, but 1 x 32 on a wide output (33 operand
+// tiles for 32 products, against 8 x 4 with groups: 12). Measured, column
+// tiles first -> groups (us): nt = 112 (Mixtral-8x7B gate/up) 2055 -> 1848,
+// nt = 28 (DeepSeek-V3 gate/up input gradient) 563 -> 524, nt = 16 923 -> 907;
+// nt = 6 (Qwen3 gate/up) 113 -> 120, nt = 3 71 -> 75, nt = 8 68.5 -> 69.3.
+#ifndef FM_ROW_GROUP_MIN_NT
+#define FM_ROW_GROUP_MIN_NT 12
+#endif
+
+// Tile shapes: rows x columns, wavefronts along each, LDS stages. The ring
+// of every shape fits kRingBytes.
+template <int BM_, int BN_, int WGM_, int WGN_, int NS_>
+struct TileShape {
+  static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, NS = NS_;
+};
+using FullTile = TileShape<256, 256, FM_ROWS_WGM, FM_ROWS_WGN, FM_ROWS_NS>;
+using HalfTile = TileShape<256, 128, FM_ROWS_WGM, FM_ROWS_WGN, 3>;
+using ShortTile = TileShape<128, 256, 4, 2, 3>;
+using ThinTile = TileShape<64, 256, 2, 4, 3>;
+constexpr int kRingBytes = 147456;
+
+// One unit: tile (slot j, rows from mrel, row tile number mt, column tile
+// nt), half h of it, piece q.
+constexpr int kNone = -1;       // no unit left
+constexpr int kElsewhere = -2;  // the queue is empty, others may not be
+struct RowUnit {
+  int ph;   // which GEMM, kNone or kElsewhere
+  int cls;  // 0: 256 rows, 1: 128, 2: 64
+  int rbeg, rend, w;  // the slot's rows and weight index
+  int mrel, mt, nt;
+  int halved;
+  int h, q, cut;  // cut: index of this unit among the cut ones
+};
+
+__device__ __forceinline__ RowUnit decode_unit(const PhaseUnits& u, const RowTiles& R, int S, int nfull, int idx) {
+  RowUnit r;
+  r.halved = 0;
+  r.h = r.q = 0;
+  int t = idx, j;
+  r.cut = idx - u.plain;
+  if (r.cut >= 0) {
+    int c = r.cut;
+    const int per = u.h * u.s;
+    if (c < u.full_cut * per) {
+      t = u.plain + c / per;
+      r.halved = u.h == 2;
+      r.h = c % per / u.s;
+      r.q = c % u.s;
+    } else {
+      c -= u.full_cut * per;
+      t = u.plain + u.full_cut + c / u.s;
+      r.q = c % u.s;
+    }
+  }
+  if (t < nfull * u.nt) {
+    int lo = 0, hi = S - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (R.full[mid] * u.nt <= t) lo = mid;
+      else hi = mid - 1;
+    }
+    j = __builtin_amdgcn_readfirstlane(lo);
+    const int first = __builtin_amdgcn_readfirstlane(R.full[j]);
+    const int mf = __builtin_amdgcn_readfirstlane(R.full[j + 1]) - first;
+    const int local = t - first * u.nt;
+    int m = local / u.nt;
+    r.nt = local - m * u.nt;
+    if (u.nt >= FM_ROW_GROUP_MIN_NT) {
+      const int g = m >> 3, rem = local - 8 * g * u.nt, left = mf - 8 * g;
+      if (left >= 8) {
+        r.nt = rem >> 3;
+        m = 8 * g + (rem & 7);
+      } else {
+        r.nt = rem / left;
+        m = 8 * g + rem - r.nt * left;
+      }
+    }
+    r.cls = 0;
+    r.mrel = m * 256;
+    r.mt = first + m;
+  } else {
+    t -= nfull * u.nt;
+    const int i = t / u.nt;
+    r.nt = t % u.nt;
+    const int n_short = __builtin_amdgcn_readfirstlane(R.n_short);
+    r.cls = i < n_short ? 1 : 2;
+    j = __builtin_amdgcn_readfirstlane(R.tail[i < n_short ? i : FOREMOE_MAX_SLOTS - 1 - (i - n_short)]);
+    r.mrel = (__builtin_amdgcn_readfirstlane(R.full[j + 1]) - __builtin_amdgcn_readfirstlane(R.full[j])) * 256;
+    r.mt = nfull + i;
+  }
+  r.rbeg = __builtin_amdgcn_readfirstlane(R.off[j]);
+  r.rend = __builtin_amdgcn_readfirstlane(R.off[j + 1]);
+  r.w = __builtin_amdgcn_readfirstlane(R.widx[j]);
+  return r;
+}
+
+__device__ __forceinline__ unsigned load_agent(const unsigned* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void store_agent(unsigned* p, unsigned v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The hand-over of rows between two GEMMs of one launch. A row tile counts
+// its column tiles in halves (2 for a whole one, 1 for each half of a halved
+// one) in fa.row_done, and the queue word kDoneTotal counts all of them.
+//
+// A workgroup may count a tile once all its wavefronts' stores of it have
+// reached memory. Waiting for that right after the epilogue would leave the
+// CU idle while the stores drain, so the count is kept pending: the next
+// unit's first stage loads are issued, and its first wait covers the stores
+// too.
+constexpr int kFinished = 2 * kQueues;       // queue word: workgroups finished
+constexpr int kDoneTotal = 2 * kQueues + 1;  // queue word: halves done
+constexpr int kQueueWords = 2 * kQueues + 2;
+
+struct HandOver {
+  int tile;       // row tile of the unit whose count is pending, or -1
+  unsigned count;
+  bool all_done;  // every tile of the first GEMM is known to be done (thread 0)
+};
+
+__device__ __forceinline__ void count_done(const FfnArgs& fa, HandOver& ho) {
+  // (clamped: slots that overlap, which is not valid, could make more row
+  // tiles than there are counters)
+  if (threadIdx.x == 0) {
+    const int t = ho.tile < kMaxRowTiles ? ho.tile : kMaxRowTiles - 1;
+    __hip_atomic_fetch_add(&fa.row_done[t], ho.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_add(&fa.queue[kDoneTotal * kQueueStride], ho.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  ho.tile = -1;
+}
+// Counts a pending tile now.
+__device__ __forceinline__ void flush_done(const FfnArgs& fa, HandOver& ho) {
+  if (ho.tile < 0) return;
+  wait_vm<0>();
+  __syncthreads();
+  count_done(fa, ho);
+}
+
+// Computes unit r of GEMM fa.p[PH]. take() starts taking the next unit once
+// the k-loop's loads are done; taken() publishes it after the epilogue's
+// stores have been issued, so that its latency hides under the epilogue.
+// done_all: halves of the whole first GEMM.
+template <class TS, bool B_KMAJ, int EPI, int PH, class Take, class Taken>
+__device__ __forceinline__ void run_unit(const FfnArgs& fa, const PhaseUnits& u, const RowUnit& r, char* lds,
+                                         int* s_flag, HandOver& ho, unsigned done_tile, unsigned done_all,
+                                         Take&& take, Taken&& taken) {
+  constexpr int BM = TS::BM, BN = TS::BN, BK = FM_ROWS_BK, NS = TS::NS, WGM = TS::WGM, WGN = TS::WGN;
   constexpr bool SW = (EPI == kEpiSwigluFwd);
   constexpr int NW = WGM * WGN;
   using CoreT = Core<BM, BN, WGM, WGN, SW>;
   using AT = KTile<BM, BK, NW>;
   using BT = typename std::conditional<B_KMAJ, KTile<BN, BK, NW>, MTile<BN, BK, NW>>::type;
   constexpr int STAGE = AT::BYTES + BT::BYTES;
-  __shared__ __attribute__((aligned(1024))) char lds[NS * STAGE];
-  __shared__ int s_mt[FOREMOE_MAX_SLOTS + 1];
-  __shared__ int s_tmp[16];
-  __shared__ int s_last;
-
-  build_slot_tiles<BM>(a.slot_offset, a.S, a.n_cap, s_mt, s_tmp);
-  const int n_tiles = a.N / BN;
-  const int total = s_mt[a.S] * n_tiles;
-  const int wave = wave_id();
+  static_assert(NS * STAGE <= kRingBytes, "the ring fits");
+  static_assert(NW == 8, "eight wavefronts");
+  const RowsArgs& a = fa.p[PH];
+  const int lane = lane64_here(), wave = wave_id();
   const int wm = wave / WGN, wn = wave % WGN;
-  const int KT = a.K / BK;
   const uint32_t lds0 = lds_addr(lds);
-
-  CoreT core;
-  const typename CoreT::template Offsets<AT, BT, BK> offs(wm, wn);
-
-  // Whole rounds of G tiles, one tile per workgroup per round. When the last
-  // round is partial (r < G tiles), its tiles may be cut into `halves`
-  // along N and, with a workspace, each (half) tile into `split` pieces
-  // along K, so that r * halves * split workgroups share it instead of r.
-  // The halves and pieces of one tile run on workgroups of one XCD.
-  const int G = gridDim.x;
-  const int v = xcd_virtual_id();
-  const int r = total % G;
-  int split = 1;
-  // With 256-wide tiles, a partial last round of at most 7/16 G tiles is
-  // first cut along N: each tile becomes two half-width tiles on two
-  // workgroups, with no partial sums (measured faster than cutting the same
-  // round along K). The K split then applies to the (half) tiles.
-  int halves = 1;
-  if constexpr (BN == 256 && FM_NSPLIT) halves = (r > 0 && 16 * r <= 7 * G) ? 2 : 1;
-  if (a.sk_part && r > 0 && KT >= kSplitMinK) {
-    // as many pieces as keep at most 7/8 of the workgroups busy, so that
-    // the round is also spread over the XCDs (below); a split that fills
-    // the GPU measured slower than the unsplit round spread out
-    split = (7 * G / 8) / (r * halves);
-    split = split < kSplitMax ? split : kSplitMax;
-    if (split < 2) split = 1;
-  }
-  const int full = total - r;  // tiles of the whole rounds
-  // One output tile, k-steps [kb, kb + nk). With pieces > 1 this is piece q
-  // of a (half) tile cut along K: the partial sums go to the workspace and
-  // the last piece to arrive adds all pieces in piece order and writes the
-  // (half) tile. half_c = std::true_type: only columns
-  // [h BN / 2, (h + 1) BN / 2) of tile t, each wave owning WM x WN / 2 (a
-  // tile of the last round cut along N, below).
-  auto run_tile = [&](auto half_c, int t, int h, int kb, int nk, int q, int pieces, int slot) {
-    constexpr bool HALF = decltype(half_c)::value;
-    constexpr int BNX = HALF ? BN / 2 : BN;
-    using CoreX = typename std::conditional<HALF, Core<BM, BNX, WGM, WGN, SW>, CoreT>::type;
-    using BTX = typename std::conditional<B_KMAJ, KTile<BNX, BK, NW>, MTile<BNX, BK, NW>>::type;
-    constexpr int STAGEX = AT::BYTES + BTX::BYTES;
-    const int mtg = t / n_tiles, nt = t % n_tiles;
-    int lo = 0, hi = a.S - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (s_mt[mid] <= mtg) lo = mid;
-      else hi = mid - 1;
+  const bool pair = fa.phases == 3;
+  if (PH == 1 && pair) {
+    // Every unit of the first GEMM has been taken by a running workgroup
+    // (units of the second are only handed out after that), those never
+    // wait, and this one's pending count is done first: the wait ends.
+    flush_done(fa, ho);
+    if (threadIdx.x == 0 && !ho.all_done) {
+      const unsigned* done = fa.row_done + (r.mt < kMaxRowTiles ? r.mt : kMaxRowTiles - 1);
+      for (;;) {
+        const unsigned here = load_agent(done), all = load_agent(&fa.queue[kDoneTotal * kQueueStride]);
+        ho.all_done = all >= done_all;
+        if (ho.all_done || here >= done_tile) break;
+        __builtin_amdgcn_s_sleep(16);  // about half a microsecond
+      }
     }
-    const int j = __builtin_amdgcn_readfirstlane(lo);
-    int64_t rbeg = a.slot_offset[j], rend = a.slot_offset[j + 1];
-    rbeg = rbeg < 0 ? 0 : (rbeg > a.n_cap ? a.n_cap : rbeg);
-    rend = rend < 0 ? 0 : (rend > a.n_cap ? a.n_cap : rend);
-    const int mrel = (mtg - s_mt[j]) * BM;  // first tile row relative to the slot
-    const int64_t m0 = rbeg + mrel;
-    const int w = a.slot_widx[j];
-    if (w < 0 || w >= a.W) return;  // invalid weight index: rows left unwritten (every piece skips)
-    const int n0 = nt * BN + h * BNX;          // first output column of the tile grid
-    const int f0 = nt * (BN / 2) + h * (BNX / 2);  // SwiGLU: first H column
+    __syncthreads();
+  }
+  // rows of this unit are done (stores issued)
+  auto unit_done = [&]() {
+    if (PH == 0 && pair) {
+      flush_done(fa, ho);  // (a pending count is normally done by now)
+      ho.tile = r.mt;
+      ho.count = r.halved ? 1u : 2u;
+    }
+  };
+  const int64_t rbeg = r.rbeg, rend = r.rend;
+  const int64_t m0 = rbeg + r.mrel;
+  const int w = r.w;
+  const int n0 = r.nt * 256 + r.h * 128;         // first output column of the tile grid
+  const int f0 = r.nt * 128 + r.h * 64;          // SwiGLU: first H column
+  // an invalid weight index leaves the rows unwritten (every piece skips);
+  // the second half of a column tile that is only 128 wide has no columns
+  if (w < 0 || w >= fa.W || n0 >= a.N) {
+    if (r.q == 0) unit_done();
+    take();
+    __syncthreads();  // every wave has read the current unit
+    taken();
+    return;
+  }
+  const int kb = r.q * u.kt / u.s, nk = (r.q + 1) * u.kt / u.s - kb;
+  const int pieces = r.cut >= 0 ? u.s : 1;
+  const int kb_ = pieces > 1 ? kb : 0, nk_ = pieces > 1 ? nk : u.kt;
 
-    // operand A: the slot's rows only (rows past the slot read as zero);
-    // operand B: weight matrix w. Lane offsets are fixed for the tile; each
-    // stage moves the start of the buffer resource to its first k, so the
-    // range check still ends at the slot's last row.
-    const uint32_t lda2 = (uint32_t)(a.lda * 2), ldb2 = (uint32_t)(a.ldb * 2);
-    const uint16_t* abase = a.A + rbeg * a.lda;
-    const uint32_t abytes = (uint32_t)((rend - rbeg) * a.lda * 2);
-    const uint16_t* bbase = a.B + (int64_t)w * a.wstride;
-    const uint32_t bbytes = (uint32_t)(a.wstride * 2);
-    auto arow = [&](int r) -> uint32_t { return (uint32_t)(mrel + r) * lda2; };
-    auto brow = [&](int r) -> uint32_t {
-      if constexpr (B_KMAJ) {
-        int wr;
-        if constexpr (SW) wr = r < BNX / 2 ? f0 + r : a.F + f0 + (r - BNX / 2);
-        else wr = n0 + r;
-        return (uint32_t)wr * ldb2;
-      } else {
-        // K-major weights: element (n, k) at (k * ldb + n) * 2
-        return (uint32_t)r * ldb2 + (uint32_t)n0 * 2u;
-      }
-    };
-    const uint32_t va0 = AT::voff(arow, 0), vb0 = BTX::voff(brow, 0);
-    uint32_t sa_[AT::PER_WAVE], sb_[BTX::PER_WAVE];
-#pragma unroll
-    for (int i = 0; i < AT::PER_WAVE; ++i) sa_[i] = __builtin_amdgcn_readfirstlane(AT::voff(arow, i) - va0);
-#pragma unroll
-    for (int i = 0; i < BTX::PER_WAVE; ++i) sb_[i] = __builtin_amdgcn_readfirstlane(BTX::voff(brow, i) - vb0);
-    auto issue = [&](int kt, int p) {
-      // stages past the last load nothing (zero-size resources)
-      const bool live = kt < nk;
-      const uint32_t sa = lds0 + (uint32_t)((kt % NS) * STAGEX);
-      const uint32_t k0 = live ? (uint32_t)((kb + kt) * BK) : 0u;
-      if (p < AT::PER_WAVE) {
-        AT::issue_s(buf_rsrc(abase + k0, live ? abytes - 2u * k0 : 0u), sa, va0, sa_[p], p);
-      } else if constexpr (B_KMAJ) {
-        BTX::issue_s(buf_rsrc(bbase + k0, live ? bbytes - 2u * k0 : 0u), sa + AT::BYTES, vb0, sb_[p - AT::PER_WAVE],
-                     p - AT::PER_WAVE);
-      } else {
-        BTX::issue_s(buf_rsrc(bbase + (int64_t)k0 * a.ldb, live ? bbytes - k0 * ldb2 : 0u), sa + AT::BYTES, vb0,
-                     sb_[p - AT::PER_WAVE], p - AT::PER_WAVE);
-      }
-    };
-
-    // After the k-loop: a K piece stores its partial sums and the last piece
-    // of its tile to arrive adds all pieces in piece order; then the
-    // epilogue. cr is the full or the half-width core.
-    auto finish_tile = [&](auto& cr) {
-      using C = typename std::remove_reference<decltype(cr)>::type;
-      constexpr int BNC = C::WN * WGN;  // output columns this core covers
-      if (pieces > 1) {
-        // piece q' of this (half) tile is computed by the workgroup with
-        // slot slot - q + q'; each keeps its partial sums in its own
-        // workspace slot
-        const __amdgpu_buffer_rsrc_t rs = split_rsrc(a.sk_part, (uint32_t)G * (BM * BN * 4));
-        split_store<C, NW>(rs, slot, wave, cr);
-        wait_vm<0>();  // this wave's partial sums have reached memory
-        __syncthreads();
-        const int cidx = (t - full) * (BN / BNC) + h;  // arrival counter of this (half) tile
-        if (threadIdx.x == 0) s_last = atomicAdd(&a.sk_count[cidx], 1u) == (unsigned)(pieces - 1);
-        __syncthreads();
-        if (!s_last) return;
-        // the tile's pieces: slots slot - q .. slot - q + pieces - 1
-        {
-          static_assert(NW * kSplitRegionKiB * 1024 <= NS * STAGE, "split pieces must fit in the ring");
-          const __amdgpu_buffer_rsrc_t ts =
-              split_rsrc(a.sk_part + (size_t)(slot - q) * (BM * BNC), (uint32_t)pieces * (BM * BNC * 4));
-          char* wl = lds + wave * (kSplitRegionKiB * 1024);
-          if (pieces == 2) split_sum<NW, 2>(ts, wave, wl, cr);
-          else if (pieces == 3) split_sum<NW, 3>(ts, wave, wl, cr);
-          else split_sum<NW, 4>(ts, wave, wl, cr);
-        }
-        if (threadIdx.x == 0) atomicExch(&a.sk_count[cidx], 0u);  // ready for the next call
-      }
-      static_assert(NW * EpiBytes<C, EPI>::PER_WAVE <= NS * STAGE, "epilogue staging must fit in the ring");
-      __syncthreads();  // every wave is done reading the ring: it now stages the epilogue
-      rows_epilogue<C, EPI>(a, cr, lds + wave * EpiBytes<C, EPI>::PER_WAVE, m0 + wm * C::WM, rend, n0, f0, wn);
-      __syncthreads();  // staging reads done before the next tile's loads overwrite the ring
-    };
-
-    if constexpr (HALF) {
-      static_assert(STAGEX <= STAGE, "the half-width ring fits in the ring");
-      CoreX hc;
-      const typename CoreX::template Offsets<AT, BTX, BK> ox(wm, wn);
-      hc.zero();
-      pipelined_k_loop<CoreX, AT, BTX, BK, NS, SW ? FM_FRAG_DIST_FWD : FM_FRAG_DIST>(hc, lds, nk, ox, issue);
-      finish_tile(hc);
+  // operand A: the slot's rows only (rows past the slot read as zero);
+  // operand B: weight matrix w. Lane offsets are fixed for the tile; each
+  // stage moves the start of the buffer resource to its first k, so the
+  // range check still ends at the slot's last row.
+  const uint32_t lda2 = (uint32_t)(a.lda * 2), ldb2 = (uint32_t)(a.ldb * 2);
+  const uint16_t* abase = a.A + rbeg * a.lda;
+  const uint32_t abytes = (uint32_t)((rend - rbeg) * a.lda * 2);
+  const uint16_t* bbase = a.B + (int64_t)w * a.wstride;
+  const uint32_t bbytes = (uint32_t)(a.wstride * 2);
+  auto arow = [&](int i) -> uint32_t { return (uint32_t)(r.mrel + i) * lda2; };
+  auto brow = [&](int i) -> uint32_t {
+    if constexpr (B_KMAJ) {
+      int wr;
+      if constexpr (SW) wr = i < BN / 2 ? f0 + i : a.F + f0 + (i - BN / 2);
+      else wr = n0 + i;
+      return (uint32_t)wr * ldb2;
     } else {
-      core.zero();
-      pipelined_k_loop<CoreT, AT, BT, BK, NS, SW ? FM_FRAG_DIST_FWD : FM_FRAG_DIST>(core, lds, nk, offs, issue);
-      finish_tile(core);
+      // K-major weights: element (n, k) at (k * ldb + n) * 2
+      return (uint32_t)i * ldb2 + (uint32_t)n0 * 2u;
+    }
+  };
+  const uint32_t va0 = AT::voff(lane, arow, 0), vb0 = BT::voff(lane, brow, 0);
+  uint32_t sa_[AT::PER_WAVE], sb_[BT::PER_WAVE];
+#pragma unroll
+  for (int i = 0; i < AT::PER_WAVE; ++i) sa_[i] = __builtin_amdgcn_readfirstlane(AT::voff(lane, arow, i) - va0);
+#pragma unroll
+  for (int i = 0; i < BT::PER_WAVE; ++i) sb_[i] = __builtin_amdgcn_readfirstlane(BT::voff(lane, brow, i) - vb0);
+  auto issue = [&](int kt, int p) {
+    // stages past the last load nothing (zero-size resources)
+    const bool live = kt < nk_;
+    const uint32_t sa = lds0 + (uint32_t)((kt % NS) * STAGE);
+    const uint32_t k0 = live ? (uint32_t)((kb_ + kt) * BK) : 0u;
+    if (p < AT::PER_WAVE) {
+      AT::issue_s(buf_rsrc(abase + k0, live ? abytes - 2u * k0 : 0u), sa, va0, sa_[p], p);
+    } else if constexpr (B_KMAJ) {
+      BT::issue_s(buf_rsrc(bbase + k0, live ? bbytes - 2u * k0 : 0u), sa + AT::BYTES, vb0, sb_[p - AT::PER_WAVE],
+                  p - AT::PER_WAVE);
+    } else {
+      BT::issue_s(buf_rsrc(bbase + (int64_t)k0 * a.ldb, live ? bbytes - k0 * ldb2 : 0u), sa + AT::BYTES, vb0,
+                  sb_[p - AT::PER_WAVE], p - AT::PER_WAVE);
     }
   };
 
-  // Whole rounds take the XCD-grouped ids. A partial last round that keeps
-  // at most 7/8 of the workgroups busy is spread over all eight XCDs
-  // instead, in blocks: XCD x takes tiles [x * tpx, (x + 1) * tpx), so that
-  // neighbouring tiles (which share operand rows or weights) still share an
-  // L2, with the halves and pieces of a tile on consecutive workgroups of
-  // that XCD. The XCDs share only memory, so such a round runs faster on eight
-  // partly busy XCDs than on fewer full ones.
-  for (int t = v; t < full; t += G) run_tile(std::false_type{}, t, 0, 0, KT, 0, 1, v);
-  const int per = halves * split;  // workgroups per tile of the last round
-  const int busy = r * per;
-  int u = v;
-  if (FM_TAIL_SPREAD && G % 8 == 0 && 8 * busy <= 7 * G) {
-    const int b = blockIdx.x, tpx = (r + 7) / 8;  // tiles per XCD
-    if (tpx * per <= G / 8) {
-      const int x = b % 8, c = b / 8, j = c / per, i = x * tpx + j;
-      u = (j < tpx && i < r) ? i * per + c % per : busy;  // busy: idle workgroup
+  CoreT core;
+  const typename CoreT::template Offsets<AT, BT, BK> offs(lane, wm, wn);
+  core.zero();
+  constexpr int D = BM == 256 ? FM_FRAG_DIST_ROWS : FM_FRAG_DIST;
+  const bool drain = PH == 0 && ho.tile >= 0;
+  pipelined_k_loop<CoreT, AT, BT, BK, NS, D>(core, lds, nk_, offs, issue, drain, [&] {
+    if (drain) count_done(fa, ho);
+  });
+  take();
+
+  if constexpr (BM * BN * 4 <= kPieceBytes) {
+    if (pieces > 1) {
+      // the partial sums go to the workspace; the last piece of the (half)
+      // tile to arrive adds all of them in piece order
+      const int first = PH * kCutUnits + r.cut - r.q;  // slot of piece 0
+      const __amdgpu_buffer_rsrc_t rs =
+          split_rsrc(fa.part + (size_t)first * (kPieceBytes / 4), (uint32_t)pieces * kPieceBytes);
+      split_store<CoreT, NW>(rs, r.q, wave, core);
+      wait_vm<0>();  // this wave's partial sums have reached memory
+      __syncthreads();
+      unsigned* count = fa.arrived + PH * kCutUnits + r.cut / pieces;
+      if (threadIdx.x == 0) *s_flag = atomicAdd(count, 1u) == (unsigned)(pieces - 1);
+      __syncthreads();
+      if (!*s_flag) {
+        taken();
+        return;
+      }
+      static_assert(NW * kSplitRegionKiB * 1024 <= kRingBytes, "split pieces must fit in the ring");
+      char* wl = lds + wave * (kSplitRegionKiB * 1024);
+      if (pieces == 2) split_sum<NW, 2>(rs, wave, wl, core);
+      else if (pieces == 3) split_sum<NW, 3>(rs, wave, wl, core);
+      else split_sum<NW, 4>(rs, wave, wl, core);
+      if (threadIdx.x == 0) atomicExch(count, 0u);  // ready for the next call
     }
   }
-  if (u < busy) {
-    // unit u: tile full + u / per, half (u % per) / split, K piece u % split
-    const int q = u % split;
-    const int kb = q * KT / split, ke = (q + 1) * KT / split;
-    if constexpr (BN == 256 && FM_NSPLIT) {
-      if (halves == 2) {
-        run_tile(std::true_type{}, full + u / per, (u % per) / split, kb, ke - kb, q, split, u);
+  static_assert(NW * EpiBytes<CoreT, EPI>::PER_WAVE <= kRingBytes, "epilogue staging must fit in the ring");
+  __syncthreads();  // every wave is done reading the ring: it now stages the epilogue
+  rows_epilogue<CoreT, EPI>(a, core, lds + wave * EpiBytes<CoreT, EPI>::PER_WAVE, m0 + wm * CoreT::WM, rend, n0, f0,
+                            wn);
+  unit_done();
+  taken();
+}
+
+// The row GEMMs of one direction (FWD: gate/up with SwiGLU, then down; else
+// the down input gradient with SwiGLU', then gate/up's): persistent
+// workgroups, one per CU, compute units until none is left. One GEMM alone:
+// every workgroup has a fixed share of its XCD's queue. Both in one launch
+// (fa.phases == 3, which needs the workspace): the queues have counters; a
+// workgroup takes from its own XCD's queue, then from the others', and takes
+// units of the second GEMM only when the first has none left, so that the
+// second fills the CUs that the first's last round leaves idle. A unit of
+// the second starts once its row tile is done (fa.row_done). The next unit is
+// taken and looked up while the current one's rows are being stored.
+//
+// What bounds it. A 256 x 256 tile's k-step of 64 takes 2700 cycles against
+// 2048 of matrix work; around the k-loop a tile pays about 5000 cycles for
+// its first stage and 10000 (plain) to 15000 (SwiGLU) for its epilogue, when
+// all CUs store at once. On the Qwen3 EP=8 share (16278 rows in 10 slots, 5
+// to 5586 each; K = 2048, 768) the launches are 1.6 and 2.1 rounds of tiles
+// long, so idle CUs in the last round cost most. Measured on one box, before
+// -> now (us):
+//   Qwen3 forward, both GEMMs       197 -> 165   (116 + 66 -> 110 + 63 apart)
+//   Qwen3 input gradients           199 -> 187   (73 + 113 -> 67 + 110 apart)
+//   Mixtral-8x7B forward           3040 -> 2830  (row groups, tile heights)
+//   DeepSeek-V3 input gradients     924 -> 860
+//   12 slots of 26 rows, d = 2048, F = 768: gate/up 30.4 -> 22.5 (64-row
+//   tiles with three stages in flight, 64 weight rows per CU and k-step at
+//   5 TB/s), down 15.3 -> 14.3
+// before: 256-row tiles only, a GEMM per launch, a fixed share of tiles, and
+// bf16 rounding in integer arithmetic in the epilogues (15000-23000 cycles).
+// One GEMM alone from the counters instead of the fixed share: 2-3 us slower
+// per launch, and the policy update no faster.
+template <bool FWD>
+__global__ __launch_bounds__(512) void gemm_rows_kernel(FfnArgs fa) {
+  __shared__ __attribute__((aligned(1024))) char lds[kRingBytes];
+  __shared__ RowTiles R;
+  __shared__ int s_tmp[16];
+  __shared__ int s_flag;
+  __shared__ int s_claim;
+  __shared__ __attribute__((aligned(16))) RowUnit s_unit;
+
+  const int tid = threadIdx.x;
+  const int G = gridDim.x, nq = G % kQueues == 0 ? kQueues : 1;
+  const Queues Q{G, nq, G / nq};
+  const int x0 = nq == kQueues ? blockIdx.x % kQueues : 0;  // workgroups go to the XCDs in turn
+  const bool pair = fa.phases == 3;
+  // Of two GEMMs even the first unit is taken from the queue, since a
+  // workgroup waiting for rows relies on every unit of the first GEMM being
+  // held by a running workgroup (and not by one that still waits for its CU).
+  int first = nq == kQueues ? blockIdx.x / kQueues : blockIdx.x;
+  if (pair && tid == 0) first = (int)atomicAdd(&fa.queue[x0 * kQueueStride], 1u);
+  build_row_tiles(fa.slot_offset, fa.slot_widx, fa.S, fa.n_cap, R, s_tmp);
+  if (tid == 0) s_claim = first;
+  PhaseUnits u0, u1;
+  const int nfull = __builtin_amdgcn_readfirstlane(R.full[fa.S]);
+  const int nsmall = __builtin_amdgcn_readfirstlane(R.n_short + R.n_thin);
+  {
+    const int rows = nfull + nsmall;
+    const int t0 = rows * ((fa.p[0].N + 255) / 256), t1 = rows * ((fa.p[1].N + 255) / 256);
+    const bool ws = fa.part != nullptr;
+    // the first of two GEMMs is cut only if it makes less than a round (its
+    // partial round is filled by the second); the last round of the second
+    // follows from the work of both
+    const int r0 = t0 < G ? t0 : (pair ? 0 : t0 % G);
+    int r1 = t1 < G ? t1 : t1 % G;
+    if (pair && t0 >= G && t1 >= G) {
+      // both in tiles of the second GEMM, by their k-steps
+      const float rounds = ((float)t0 * (float)fa.p[0].K / (float)fa.p[1].K + (float)t1) / (float)G;
+      r1 = (int)((rounds - floorf(rounds)) * (float)G);
+      if (16 * r1 > 7 * G) r1 = 0;
+    }
+    u0 = phase_units(nfull, nsmall, fa.p[0].N, fa.p[0].K, G, r0, ws);
+    u1 = phase_units(nfull, nsmall, fa.p[1].N, fa.p[1].K, G, r1, ws);
+    if (!(fa.phases & 1)) u0.total = 0;
+    if (!(fa.phases & 2)) u1.total = 0;
+  }
+  HandOver ho{-1, 0u, false};
+  const unsigned done_tile = 2u * (unsigned)u0.nt, done_all = done_tile * (unsigned)(nfull + nsmall);
+
+  // Wavefront 0 keeps the place in the queues: GEMM ph, queue x, position
+  // s_claim. publish() looks the unit up and leaves it in s_unit; it runs
+  // while the other wavefronts still store their rows. Where the queue is
+  // empty, take_elsewhere() follows, after a pending tile has been counted
+  // (a workgroup of the second GEMM may be waiting for it).
+  int ph = (fa.phases & 1) ? 0 : 1, x = x0, step = 0;
+  auto publish = [&]() __attribute__((always_inline)) {
+    const int k = __builtin_amdgcn_readfirstlane(s_claim);
+    const int total = ph == 0 ? u0.total : u1.total;
+    if (k >= Q.length(total, x)) {
+      if (tid == 0) s_unit.ph = pair ? kElsewhere : kNone;
+      return;
+    }
+    step = k;
+    RowUnit r = decode_unit(ph == 0 ? u0 : u1, R, fa.S, nfull, Q.unit(total, x, k));
+    r.ph = ph;
+    if (tid == 0) s_unit = r;
+  };
+  // Looks at all counters at once and takes from the first queue with units
+  // left (own XCD first, first GEMM first).
+  auto take_elsewhere = [&]() __attribute__((always_inline)) {
+    const int lane = lane64();
+    const int qp = (lane >> 3) & 1, qx = ((lane & 7) + x0) % kQueues;
+    const int len = lane < 2 * kQueues && qx < nq ? Q.length(qp == 0 ? u0.total : u1.total, qx) : 0;
+    unsigned* c = &fa.queue[(qp * kQueues + qx) * kQueueStride];
+    bool open = lane < 2 * kQueues && (int)load_agent(c) < len;
+    int got = 0;
+    uint64_t found;
+    while ((found = __ballot(open)) != 0) {
+      const int from = __builtin_ctzll(found);
+      if (lane == from) {
+        got = (int)atomicAdd(c, 1u);
+        open = got < len;
+      }
+      if ((__ballot(open) >> from) & 1) {
+        ph = from >> 3;
+        x = ((from & 7) + x0) % kQueues;
+        const int k = __builtin_amdgcn_readlane(got, from);
+        if (tid == 0) s_claim = k;
+        publish();
         return;
       }
     }
-    run_tile(std::false_type{}, full + u / split, 0, kb, ke - kb, q, split, u);
+    if (tid == 0) s_unit.ph = kNone;
+  };
+
+  if (wave_id() == 0) publish();
+  for (;;) {
+    __syncthreads();  // the unit is known; staging reads done before its loads overwrite the ring
+    if (__builtin_amdgcn_readfirstlane(s_unit.ph) == kElsewhere) {
+      flush_done(fa, ho);
+      __syncthreads();  // every wave has read s_unit
+      if (wave_id() == 0) take_elsewhere();
+      __syncthreads();
+    }
+    RowUnit r;
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(RowUnit) / 4); ++i)
+      reinterpret_cast<int*>(&r)[i] = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(&s_unit)[i]);
+    if (r.ph == kNone) break;
+    auto go = [&](auto phc) __attribute__((always_inline)) {
+      constexpr int PH = decltype(phc)::value;
+      constexpr int EPI = PH == 1 ? kEpiStore : (FWD ? kEpiSwigluFwd : kEpiSwigluBwd);
+      const PhaseUnits& up = PH == 0 ? u0 : u1;
+      int next = 0;
+      auto take = [&]() __attribute__((always_inline)) {
+        next = pair ? INT_MAX : step + Q.c;
+        if (pair && x == x0 && tid == 0)
+          next = (int)atomicAdd(&fa.queue[(PH * kQueues + x0) * kQueueStride], 1u);
+      };
+      auto taken = [&]() __attribute__((always_inline)) {
+        if (tid == 0) s_claim = next;
+      };
+      // a last column tile of 128 columns is a half tile too
+      if (r.cls == 0 && (r.halved || r.nt * 256 + 128 >= fa.p[PH].N))
+        run_unit<HalfTile, FWD, EPI, PH>(fa, up, r, lds, &s_flag, ho, done_tile, done_all, take, taken);
+      else if (r.cls == 0)
+        run_unit<FullTile, FWD, EPI, PH>(fa, up, r, lds, &s_flag, ho, done_tile, done_all, take, taken);
+      else if (r.cls == 1)
+        run_unit<ShortTile, FWD, EPI, PH>(fa, up, r, lds, &s_flag, ho, done_tile, done_all, take, taken);
+      else
+        run_unit<ThinTile, FWD, EPI, PH>(fa, up, r, lds, &s_flag, ho, done_tile, done_all, take, taken);
+    };
+    if (r.ph == 0) go(std::integral_constant<int, 0>{});
+    else go(std::integral_constant<int, 1>{});
+    if (wave_id() == 0) publish();
   }
+  if (!pair) return;
+  flush_done(fa, ho);
+
+  // the last workgroup to finish leaves every counter at zero
+  if (tid == 0) s_flag = atomicAdd(&fa.queue[kFinished * kQueueStride], 1u) == (unsigned)(G - 1);
+  __syncthreads();
+  if (!s_flag) return;
+  if (tid < kQueueWords) store_agent(&fa.queue[tid * kQueueStride], 0u);
+  for (int i = tid; i < nfull + nsmall && i < kMaxRowTiles; i += blockDim.x) store_agent(&fa.row_done[i], 0u);
 }
 
 // ---------------------------------------------------------------------------
@@ -1297,13 +1717,6 @@ struct KCursor {
   const uint16_t* pb;
 };
 
-__device__ __forceinline__ const uint16_t* uniform_ptr(const uint16_t* p) {
-  const uint64_t v = (uint64_t)p;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return (const uint16_t*)(((uint64_t)hi << 32) | lo);
-}
-
 __device__ __forceinline__ void cursor_next_slot(const WgradPlan& P, int V, int g, int s1, KCursor& c) {
   int j = c.j, pos = c.pos;
   for (;;) {
@@ -1386,7 +1799,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_wgrad_kernel(WgradArgs a)
   const uint32_t lds0 = lds_addr(lds);
   const uint32_t lda2 = (uint32_t)(a.lda * 2), ldb2 = (uint32_t)(a.ldb * 2);
   CoreT core;
-  const typename CoreT::template Offsets<AT, BT, BK> offs(wm, wn);
+  const typename CoreT::template Offsets<AT, BT, BK> offs(lane, wm, wn);
 
   // Items (output tile x row chunk) come in descending group size. With
   // work counters each workgroup takes the next item when it is free, which
@@ -1421,12 +1834,12 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_wgrad_kernel(WgradArgs a)
     KCursor ic = cursor_begin(P, V, g, s0, s1);
     auto koa = [&](int k) -> uint32_t { return (uint32_t)k * lda2 + (uint32_t)m0 * 2u; };
     auto kob = [&](int k) -> uint32_t { return (uint32_t)k * ldb2 + (uint32_t)n0 * 2u; };
-    const uint32_t va0 = AT::voff(koa, 0), vb0 = BT::voff(kob, 0);
+    const uint32_t va0 = AT::voff(lane, koa, 0), vb0 = BT::voff(lane, kob, 0);
     uint32_t sa_[AT::PER_WAVE], sb_[BT::PER_WAVE];
 #pragma unroll
-    for (int i = 0; i < AT::PER_WAVE; ++i) sa_[i] = __builtin_amdgcn_readfirstlane(AT::voff(koa, i) - va0);
+    for (int i = 0; i < AT::PER_WAVE; ++i) sa_[i] = __builtin_amdgcn_readfirstlane(AT::voff(lane, koa, i) - va0);
 #pragma unroll
-    for (int i = 0; i < BT::PER_WAVE; ++i) sb_[i] = __builtin_amdgcn_readfirstlane(BT::voff(kob, i) - vb0);
+    for (int i = 0; i < BT::PER_WAVE; ++i) sb_[i] = __builtin_amdgcn_readfirstlane(BT::voff(lane, kob, i) - vb0);
     auto issue = [&](int kt, int p) {
       // the loads of one k-tile are issued in order p = 0 .. PER-1, k-tiles
       // in order: load the cursor's k-tile, advance after its last load. The
@@ -1447,7 +1860,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_wgrad_kernel(WgradArgs a)
     };
 
     core.zero();
-    pipelined_k_loop<CoreT, AT, BT, BK, NS>(core, lds, KT, offs, issue);
+    pipelined_k_loop<CoreT, AT, BT, BK, NS, FM_FRAG_DIST>(core, lds, KT, offs, issue, false, [] {});
     __syncthreads();
 
     const int l32 = lane & 31, c4 = (lane >> 5) * 4;
@@ -1618,31 +2031,35 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradArgs a) {
 // ---------------------------------------------------------------------------
 int persistent_grid() { return num_cus(); }
 
-// Row-GEMM workspace (optional): arrival counters of the split round, then
-// one fp32 partial tile of up to 256 x 256 per workgroup of the grid.
-constexpr size_t kRowsCountBytes = 4096;  // counters for up to 1024 tiles
-constexpr size_t kRowsSlotBytes = (size_t)256 * 256 * 4;
+// Row-GEMM workspace (optional): counters, then the pieces' partial tiles.
+size_t rows_workspace_bytes() { return 4096 + (size_t)persistent_grid() * 256 * 256 * 4; }
 
-size_t rows_workspace_bytes() { return kRowsCountBytes + (size_t)persistent_grid() * kRowsSlotBytes; }
-
-// Row-grouped launches: 256-row tiles; 256-wide output tiles with 2 LDS
-// stages of 64-deep K slices (128 KiB), or 128-wide with 3 stages (144 KiB).
-// e0, e1: optional timing events set when the kernel starts and ends (they
-// ride on the dispatch itself, so no event command sits in the stream).
-template <int BN, bool KMAJ, int EPI>
-void launch_rows(RowsArgs a, void* ws, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
-  if (ws && persistent_grid() <= (int)(kRowsCountBytes / 4)) {
-    a.sk_count = (unsigned*)ws;
-    a.sk_part = (float*)((char*)ws + kRowsCountBytes);
+// Launches the row GEMMs set in a.phases. e0, e1: optional timing events set
+// when the kernel starts and ends (they ride on the dispatch itself, so no
+// event command sits in the stream).
+template <bool FWD>
+void launch_rows(FfnArgs a, void* ws, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  const int G = persistent_grid();
+  const size_t parts = kRowsPartOff + (size_t)2 * kCutUnits * kPieceBytes;
+  if (ws && G <= 256 && rows_workspace_bytes() >= parts) {
+    a.arrived = (unsigned*)((char*)ws + kRowsArrivedOff);
+    a.queue = (unsigned*)((char*)ws + kRowsQueueOff);
+    a.row_done = (unsigned*)((char*)ws + kRowsDoneOff);
+    a.part = (float*)((char*)ws + kRowsPartOff);
   }
-  if constexpr (BN == 256) {
-    constexpr int WGM = FM_ROWS_WGM, WGN = FM_ROWS_WGN;
-    hipExtLaunchKernelGGL(gemm_rows_kernel<256, 256, FM_ROWS_BK, FM_ROWS_NS, WGM, WGN, KMAJ, EPI>,
-                          dim3(persistent_grid()), dim3(64 * WGM * WGN), 0, st, e0, e1, 0, a);
-  } else {
-    hipExtLaunchKernelGGL(gemm_rows_kernel<256, 128, 64, 3, 2, 2, KMAJ, EPI>, dim3(persistent_grid()), dim3(256), 0,
-                          st, e0, e1, 0, a);
+  // both GEMMs in one launch: the counters must hold every row tile, and two
+  // row tiles must not share a 128-byte line of the rows handed over (a
+  // workgroup that read one row tile would keep a stale copy of the next
+  // one's first bytes)
+  const bool pair = a.queue && a.n_cap / 256 + a.S <= kMaxRowTiles && ((uintptr_t)a.p[0].C & 127) == 0;
+  if (a.phases == 3 && !pair) {
+    FfnArgs b = a;
+    b.phases = 1;
+    hipExtLaunchKernelGGL(gemm_rows_kernel<FWD>, dim3(G), dim3(512), 0, st, e0, nullptr, 0, b);
+    a.phases = 2;
+    e0 = nullptr;
   }
+  hipExtLaunchKernelGGL(gemm_rows_kernel<FWD>, dim3(G), dim3(512), 0, st, e0, e1, 0, a);
 }
 
 // Weight-gradient workspace: a 256-byte header of work counters, then the
@@ -1699,167 +2116,210 @@ static int no_launch(hipEvent_t e0, hipEvent_t e1, void* stream) {
 
 extern "C" {
 
+// The checks and the arguments of each row GEMM. `who` names the call;
+// returns OK with *run = false when there is nothing to do.
+struct RowsCall {
+  foremoe_dtype dtype;
+  int32_t d, F, S;
+  const int32_t* slot_offset;
+  const int32_t* slot_widx;
+  int32_t W;
+  int64_t n_cap;
+  void* workspace;
+  size_t ws_bytes;
+};
+
+static int check_rows(const char* who, const RowsCall& c, bool* run) {
+  int rc = check_ffn(who, c.dtype, c.d, c.F, c.S, c.n_cap, c.slot_offset);
+  if (rc) return rc;
+  rc = check_rows_ws(who, c.workspace, c.ws_bytes);
+  if (rc) return rc;
+  *run = c.S != 0 && c.n_cap != 0;
+  return FOREMOE_OK;
+}
+
+static FfnArgs ffn_args(const RowsCall& c, int phases) {
+  FfnArgs a{};
+  a.phases = phases;
+  a.W = c.W;
+  a.slot_offset = c.slot_offset;
+  a.slot_widx = c.slot_widx;
+  a.S = c.S;
+  a.n_cap = c.n_cap;
+  return a;
+}
+
+static F32RowsArgs f32_args(const RowsCall& c, const void* A, const void* W, const void* AU, void* C, void* C2) {
+  return {(const float*)A, (const float*)W, (const float*)AU, c.d, c.F, c.W, c.slot_offset, c.slot_widx, c.S, c.n_cap,
+          (float*)C, (float*)C2};
+}
+
+static RowsArgs gate_up_fwd_args(const RowsCall& c, const void* x_perm, const void* w_gate_up, void* h,
+                                 void* save_au) {
+  RowsArgs a{};
+  a.A = (const uint16_t*)x_perm;
+  a.lda = c.d;
+  a.B = (const uint16_t*)w_gate_up;
+  a.ldb = c.d;
+  a.wstride = (int64_t)2 * c.F * c.d;
+  a.K = c.d;
+  a.N = 2 * c.F;
+  a.F = c.F;
+  a.C = (uint16_t*)h;
+  a.ldc = c.F;
+  a.C2 = (uint16_t*)save_au;
+  a.ldc2 = 2 * (int64_t)c.F;
+  return a;
+}
+
+static RowsArgs down_fwd_args(const RowsCall& c, const void* h, const void* w_down, void* y_perm) {
+  RowsArgs a{};
+  a.A = (const uint16_t*)h;
+  a.lda = c.F;
+  a.B = (const uint16_t*)w_down;
+  a.ldb = c.F;
+  a.wstride = (int64_t)c.d * c.F;
+  a.K = c.F;
+  a.N = c.d;
+  a.F = c.F;
+  a.C = (uint16_t*)y_perm;
+  a.ldc = c.d;
+  return a;
+}
+
+static RowsArgs down_dgrad_args(const RowsCall& c, const void* dy_perm, const void* save_au, const void* w_down,
+                                void* d_au) {
+  RowsArgs a{};
+  a.A = (const uint16_t*)dy_perm;
+  a.lda = c.d;
+  a.B = (const uint16_t*)w_down;  // [d, F]: K-major for this product
+  a.ldb = c.F;
+  a.wstride = (int64_t)c.d * c.F;
+  a.K = c.d;
+  a.N = c.F;
+  a.F = c.F;
+  a.C = (uint16_t*)d_au;
+  a.ldc = 2 * (int64_t)c.F;
+  a.AU = (const uint16_t*)save_au;
+  a.ldau = 2 * (int64_t)c.F;
+  return a;
+}
+
+static RowsArgs gate_up_dgrad_args(const RowsCall& c, const void* d_au, const void* w_gate_up, void* dx_perm) {
+  RowsArgs a{};
+  a.A = (const uint16_t*)d_au;
+  a.lda = 2 * (int64_t)c.F;
+  a.B = (const uint16_t*)w_gate_up;  // [2F, d]: K-major for this product
+  a.ldb = c.d;
+  a.wstride = (int64_t)2 * c.F * c.d;
+  a.K = 2 * c.F;
+  a.N = c.d;
+  a.F = c.F;
+  a.C = (uint16_t*)dx_perm;
+  a.ldc = c.d;
+  return a;
+}
+
 static int ffn_gate_up_fwd_impl(const void* x_perm, foremoe_dtype dtype, int32_t d, int32_t F, int32_t S,
-                            const int32_t* slot_offset, const int32_t* slot_widx, int32_t W, const void* w_gate_up,
-                            int64_t n_cap, void* h, void* save_au, void* workspace, size_t ws_bytes, void* stream, hipEvent_t e0, hipEvent_t e1) {
-  int rc = check_ffn("gate_up_fwd", dtype, d, F, S, n_cap, slot_offset);
+                                const int32_t* slot_offset, const int32_t* slot_widx, int32_t W,
+                                const void* w_gate_up, int64_t n_cap, void* h, void* save_au, void* workspace,
+                                size_t ws_bytes, void* stream, hipEvent_t e0, hipEvent_t e1) {
+  const RowsCall c{dtype, d, F, S, slot_offset, slot_widx, W, n_cap, workspace, ws_bytes};
+  bool run = false;
+  const int rc = check_rows("gate_up_fwd", c, &run);
   if (rc) return rc;
-  rc = check_rows_ws("gate_up_fwd", workspace, ws_bytes);
-  if (rc) return rc;
-  if (S == 0 || n_cap == 0) return no_launch(e0, e1, stream);
+  if (!run) return no_launch(e0, e1, stream);
   REQUIRE(x_perm && slot_widx && w_gate_up && h && W >= 1, "gate_up_fwd: NULL buffer or W < 1");
-  hipStream_t st = (hipStream_t)stream;
   if (dtype == FOREMOE_BF16) {
-    RowsArgs a{};
-    a.A = (const uint16_t*)x_perm;
-    a.lda = d;
-    a.B = (const uint16_t*)w_gate_up;
-    a.ldb = d;
-    a.wstride = (int64_t)2 * F * d;
-    a.W = W;
-    a.K = d;
-    a.N = 2 * F;
-    a.F = F;
-    a.slot_offset = slot_offset;
-    a.slot_widx = slot_widx;
-    a.S = S;
-    a.n_cap = n_cap;
-    a.C = (uint16_t*)h;
-    a.ldc = F;
-    a.C2 = (uint16_t*)save_au;
-    a.ldc2 = 2 * (int64_t)F;
-    launch_rows<256, true, kEpiSwigluFwd>(a, workspace, st, e0, e1);
+    FfnArgs a = ffn_args(c, 1);
+    a.p[0] = gate_up_fwd_args(c, x_perm, w_gate_up, h, save_au);
+    launch_rows<true>(a, workspace, (hipStream_t)stream, e0, e1);
   } else {
-    launch_f32_rows(kF32GateUpFwd,
-                    {(const float*)x_perm, (const float*)w_gate_up, nullptr, d, F, W, slot_offset, slot_widx, S, n_cap,
-                     (float*)h, (float*)save_au},
-                    st, e0, e1);
+    launch_f32_rows(kF32GateUpFwd, f32_args(c, x_perm, w_gate_up, nullptr, h, save_au), (hipStream_t)stream, e0, e1);
   }
   return check_launch("foremoe_ffn_gate_up_fwd");
 }
 
 static int ffn_down_fwd_impl(const void* h, foremoe_dtype dtype, int32_t d, int32_t F, int32_t S,
-                         const int32_t* slot_offset, const int32_t* slot_widx, int32_t W, const void* w_down,
-                         int64_t n_cap, void* y_perm, void* workspace, size_t ws_bytes, void* stream, hipEvent_t e0, hipEvent_t e1) {
-  int rc = check_ffn("down_fwd", dtype, d, F, S, n_cap, slot_offset);
+                             const int32_t* slot_offset, const int32_t* slot_widx, int32_t W, const void* w_down,
+                             int64_t n_cap, void* y_perm, void* workspace, size_t ws_bytes, void* stream,
+                             hipEvent_t e0, hipEvent_t e1) {
+  const RowsCall c{dtype, d, F, S, slot_offset, slot_widx, W, n_cap, workspace, ws_bytes};
+  bool run = false;
+  const int rc = check_rows("down_fwd", c, &run);
   if (rc) return rc;
-  rc = check_rows_ws("down_fwd", workspace, ws_bytes);
-  if (rc) return rc;
-  if (S == 0 || n_cap == 0) return no_launch(e0, e1, stream);
+  if (!run) return no_launch(e0, e1, stream);
   REQUIRE(h && slot_widx && w_down && y_perm && W >= 1, "down_fwd: NULL buffer or W < 1");
-  hipStream_t st = (hipStream_t)stream;
   if (dtype == FOREMOE_BF16) {
-    RowsArgs a{};
-    a.A = (const uint16_t*)h;
-    a.lda = F;
-    a.B = (const uint16_t*)w_down;
-    a.ldb = F;
-    a.wstride = (int64_t)d * F;
-    a.W = W;
-    a.K = F;
-    a.N = d;
-    a.F = F;
-    a.slot_offset = slot_offset;
-    a.slot_widx = slot_widx;
-    a.S = S;
-    a.n_cap = n_cap;
-    a.C = (uint16_t*)y_perm;
-    a.ldc = d;
-    if (d % 256 == 0) launch_rows<256, true, kEpiStore>(a, workspace, st, e0, e1);
-    else launch_rows<128, true, kEpiStore>(a, workspace, st, e0, e1);
+    FfnArgs a = ffn_args(c, 2);
+    a.p[1] = down_fwd_args(c, h, w_down, y_perm);
+    launch_rows<true>(a, workspace, (hipStream_t)stream, e0, e1);
   } else {
-    launch_f32_rows(kF32DownFwd,
-                    {(const float*)h, (const float*)w_down, nullptr, d, F, W, slot_offset, slot_widx, S, n_cap,
-                     (float*)y_perm, nullptr},
-                    st, e0, e1);
+    launch_f32_rows(kF32DownFwd, f32_args(c, h, w_down, nullptr, y_perm, nullptr), (hipStream_t)stream, e0, e1);
   }
   return check_launch("foremoe_ffn_down_fwd");
 }
 
 int foremoe_grouped_ffn_fwd(const void* x_perm, foremoe_dtype dtype, int32_t d, int32_t F, int32_t S,
                             const int32_t* slot_offset, const int32_t* slot_widx, int32_t W, const void* w_gate_up,
-                            const void* w_down, int64_t n_cap, void* h, void* y_perm, void* save_au, void* workspace, size_t ws_bytes, void* stream) {
-  int rc = foremoe_ffn_gate_up_fwd(x_perm, dtype, d, F, S, slot_offset, slot_widx, W, w_gate_up, n_cap, h, save_au,
-                                   workspace, ws_bytes, stream);
-  if (rc) return rc;
-  return foremoe_ffn_down_fwd(h, dtype, d, F, S, slot_offset, slot_widx, W, w_down, n_cap, y_perm, workspace, ws_bytes,
-                              stream);
+                            const void* w_down, int64_t n_cap, void* h, void* y_perm, void* save_au, void* workspace,
+                            size_t ws_bytes, void* stream) {
+  const RowsCall c{dtype, d, F, S, slot_offset, slot_widx, W, n_cap, workspace, ws_bytes};
+  bool run = false;
+  const int rc = check_rows("grouped_ffn_fwd", c, &run);
+  if (rc || !run) return rc;
+  REQUIRE(x_perm && slot_widx && w_gate_up && w_down && h && y_perm && W >= 1,
+          "grouped_ffn_fwd: NULL buffer or W < 1");
+  if (dtype == FOREMOE_BF16) {
+    FfnArgs a = ffn_args(c, 3);
+    a.p[0] = gate_up_fwd_args(c, x_perm, w_gate_up, h, save_au);
+    a.p[1] = down_fwd_args(c, h, w_down, y_perm);
+    launch_rows<true>(a, workspace, (hipStream_t)stream, nullptr, nullptr);
+  } else {
+    const hipStream_t st = (hipStream_t)stream;
+    launch_f32_rows(kF32GateUpFwd, f32_args(c, x_perm, w_gate_up, nullptr, h, save_au), st, nullptr, nullptr);
+    launch_f32_rows(kF32DownFwd, f32_args(c, h, w_down, nullptr, y_perm, nullptr), st, nullptr, nullptr);
+  }
+  return check_launch("foremoe_grouped_ffn_fwd");
 }
 
 static int ffn_down_dgrad_impl(const void* dy_perm, const void* save_au, foremoe_dtype dtype, int32_t d, int32_t F,
-                           int32_t S, const int32_t* slot_offset, const int32_t* slot_widx, int32_t W,
-                           const void* w_down, int64_t n_cap, void* d_au, void* workspace, size_t ws_bytes, void* stream, hipEvent_t e0, hipEvent_t e1) {
-  int rc = check_ffn("down_dgrad", dtype, d, F, S, n_cap, slot_offset);
+                               int32_t S, const int32_t* slot_offset, const int32_t* slot_widx, int32_t W,
+                               const void* w_down, int64_t n_cap, void* d_au, void* workspace, size_t ws_bytes,
+                               void* stream, hipEvent_t e0, hipEvent_t e1) {
+  const RowsCall c{dtype, d, F, S, slot_offset, slot_widx, W, n_cap, workspace, ws_bytes};
+  bool run = false;
+  const int rc = check_rows("down_dgrad", c, &run);
   if (rc) return rc;
-  rc = check_rows_ws("down_dgrad", workspace, ws_bytes);
-  if (rc) return rc;
-  if (S == 0 || n_cap == 0) return no_launch(e0, e1, stream);
+  if (!run) return no_launch(e0, e1, stream);
   REQUIRE(dy_perm && save_au && slot_widx && w_down && d_au && W >= 1, "down_dgrad: NULL buffer or W < 1");
-  hipStream_t st = (hipStream_t)stream;
   if (dtype == FOREMOE_BF16) {
-    RowsArgs a{};
-    a.A = (const uint16_t*)dy_perm;
-    a.lda = d;
-    a.B = (const uint16_t*)w_down;  // [d, F]: K-major for this product
-    a.ldb = F;
-    a.wstride = (int64_t)d * F;
-    a.W = W;
-    a.K = d;
-    a.N = F;
-    a.F = F;
-    a.slot_offset = slot_offset;
-    a.slot_widx = slot_widx;
-    a.S = S;
-    a.n_cap = n_cap;
-    a.C = (uint16_t*)d_au;
-    a.ldc = 2 * (int64_t)F;
-    a.AU = (const uint16_t*)save_au;
-    a.ldau = 2 * (int64_t)F;
-    if (F % 256 == 0) launch_rows<256, false, kEpiSwigluBwd>(a, workspace, st, e0, e1);
-    else launch_rows<128, false, kEpiSwigluBwd>(a, workspace, st, e0, e1);
+    FfnArgs a = ffn_args(c, 1);
+    a.p[0] = down_dgrad_args(c, dy_perm, save_au, w_down, d_au);
+    launch_rows<false>(a, workspace, (hipStream_t)stream, e0, e1);
   } else {
-    launch_f32_rows(kF32DownDgrad,
-                    {(const float*)dy_perm, (const float*)w_down, (const float*)save_au, d, F, W, slot_offset,
-                     slot_widx, S, n_cap, (float*)d_au, nullptr},
-                    st, e0, e1);
+    launch_f32_rows(kF32DownDgrad, f32_args(c, dy_perm, w_down, save_au, d_au, nullptr), (hipStream_t)stream, e0, e1);
   }
   return check_launch("foremoe_ffn_down_dgrad");
 }
 
 static int ffn_gate_up_dgrad_impl(const void* d_au, foremoe_dtype dtype, int32_t d, int32_t F, int32_t S,
-                              const int32_t* slot_offset, const int32_t* slot_widx, int32_t W, const void* w_gate_up,
-                              int64_t n_cap, void* dx_perm, void* workspace, size_t ws_bytes, void* stream, hipEvent_t e0, hipEvent_t e1) {
-  int rc = check_ffn("gate_up_dgrad", dtype, d, F, S, n_cap, slot_offset);
+                                  const int32_t* slot_offset, const int32_t* slot_widx, int32_t W,
+                                  const void* w_gate_up, int64_t n_cap, void* dx_perm, void* workspace,
+                                  size_t ws_bytes, void* stream, hipEvent_t e0, hipEvent_t e1) {
+  const RowsCall c{dtype, d, F, S, slot_offset, slot_widx, W, n_cap, workspace, ws_bytes};
+  bool run = false;
+  const int rc = check_rows("gate_up_dgrad", c, &run);
   if (rc) return rc;
-  rc = check_rows_ws("gate_up_dgrad", workspace, ws_bytes);
-  if (rc) return rc;
-  if (S == 0 || n_cap == 0) return no_launch(e0, e1, stream);
+  if (!run) return no_launch(e0, e1, stream);
   REQUIRE(d_au && slot_widx && w_gate_up && dx_perm && W >= 1, "gate_up_dgrad: NULL buffer or W < 1");
-  hipStream_t st = (hipStream_t)stream;
   if (dtype == FOREMOE_BF16) {
-    RowsArgs a{};
-    a.A = (const uint16_t*)d_au;
-    a.lda = 2 * (int64_t)F;
-    a.B = (const uint16_t*)w_gate_up;  // [2F, d]: K-major for this product
-    a.ldb = d;
-    a.wstride = (int64_t)2 * F * d;
-    a.W = W;
-    a.K = 2 * F;
-    a.N = d;
-    a.F = F;
-    a.slot_offset = slot_offset;
-    a.slot_widx = slot_widx;
-    a.S = S;
-    a.n_cap = n_cap;
-    a.C = (uint16_t*)dx_perm;
-    a.ldc = d;
-    if (d % 256 == 0) launch_rows<256, false, kEpiStore>(a, workspace, st, e0, e1);
-    else launch_rows<128, false, kEpiStore>(a, workspace, st, e0, e1);
+    FfnArgs a = ffn_args(c, 2);
+    a.p[1] = gate_up_dgrad_args(c, d_au, w_gate_up, dx_perm);
+    launch_rows<false>(a, workspace, (hipStream_t)stream, e0, e1);
   } else {
-    launch_f32_rows(kF32GateUpDgrad,
-                    {(const float*)d_au, (const float*)w_gate_up, nullptr, d, F, W, slot_offset, slot_widx, S, n_cap,
-                     (float*)dx_perm, nullptr},
-                    st, e0, e1);
+    launch_f32_rows(kF32GateUpDgrad, f32_args(c, d_au, w_gate_up, nullptr, dx_perm, nullptr), (hipStream_t)stream, e0,
+                    e1);
   }
   return check_launch("foremoe_ffn_gate_up_dgrad");
 }
@@ -1929,11 +2389,23 @@ int foremoe_grouped_ffn_dgrad(const void* dy_perm, const void* save_au, foremoe_
                               int32_t S, const int32_t* slot_offset, const int32_t* slot_widx, int32_t W,
                               const void* w_gate_up, const void* w_down, int64_t n_cap, void* d_au, void* dx_perm,
                               void* workspace, size_t ws_bytes, void* stream) {
-  int rc = foremoe_ffn_down_dgrad(dy_perm, save_au, dtype, d, F, S, slot_offset, slot_widx, W, w_down, n_cap, d_au,
-                                  workspace, ws_bytes, stream);
-  if (rc) return rc;
-  return foremoe_ffn_gate_up_dgrad(d_au, dtype, d, F, S, slot_offset, slot_widx, W, w_gate_up, n_cap, dx_perm,
-                                   workspace, ws_bytes, stream);
+  const RowsCall c{dtype, d, F, S, slot_offset, slot_widx, W, n_cap, workspace, ws_bytes};
+  bool run = false;
+  const int rc = check_rows("grouped_ffn_dgrad", c, &run);
+  if (rc || !run) return rc;
+  REQUIRE(dy_perm && save_au && slot_widx && w_down && w_gate_up && d_au && dx_perm && W >= 1,
+          "grouped_ffn_dgrad: NULL buffer or W < 1");
+  if (dtype == FOREMOE_BF16) {
+    FfnArgs a = ffn_args(c, 3);
+    a.p[0] = down_dgrad_args(c, dy_perm, save_au, w_down, d_au);
+    a.p[1] = gate_up_dgrad_args(c, d_au, w_gate_up, dx_perm);
+    launch_rows<false>(a, workspace, (hipStream_t)stream, nullptr, nullptr);
+  } else {
+    const hipStream_t st = (hipStream_t)stream;
+    launch_f32_rows(kF32DownDgrad, f32_args(c, dy_perm, w_down, save_au, d_au, nullptr), st, nullptr, nullptr);
+    launch_f32_rows(kF32GateUpDgrad, f32_args(c, d_au, w_gate_up, nullptr, dx_perm, nullptr), st, nullptr, nullptr);
+  }
+  return check_launch("foremoe_grouped_ffn_dgrad");
 }
 
 // One weight-gradient GEMM over n steps' rows (every step: A [n_cap, M],

@@ -1,0 +1,138 @@
+"""The row GEMMs over every tile shape (256, 128 and 64 rows; whole and half
+column tiles), as two launches and as one launch per direction, with and
+without the workspace, against fp64 products of the same bf16 operands.
+
+Tolerance: a bf16 output is within half an ulp (2^-9 relative) of its fp32
+sum, which is within gamma = K 2^-24 of the magnitudes' sum (any order); the
+second GEMM of a pair multiplies the first one's rounded rows as the GPU
+wrote them."""
+import numpy as np
+import pytest
+import torch
+
+
+def _dev(a, gpu, dtype=torch.bfloat16):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(gpu).to(dtype)
+
+
+def _f64(t):
+    return t.double().cpu().numpy()
+
+
+def _close(name, got, ref, mag, K):
+    err = np.abs(got - ref)
+    bound = 2.0 ** -8 * np.abs(ref) + K * 2.0 ** -23 * mag + 1e-6
+    assert np.all(np.isfinite(got)), f"{name}: not finite"
+    assert np.all(err <= bound), f"{name}: {np.max(err - bound):.3g} over its bound"
+
+
+def _check(gpu, rows, d, F, W, use_ws, widx=None, misalign=0):
+    from paper_2606_11867_amd import _lib, api
+    lib = _lib.load()
+    rng = np.random.default_rng(len(rows) * 7 + d + F)
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    widx = (np.arange(len(rows)) % W if widx is None else np.asarray(widx)).astype(np.int32)
+    N, S = int(off[-1]), len(rows)
+    x, dy = (_dev(rng.standard_normal((N, d), dtype=np.float32), gpu) for _ in range(2))
+    gu = _dev(rng.standard_normal((W, 2 * F, d), dtype=np.float32) * d ** -0.5, gpu)
+    dn = _dev(rng.standard_normal((W, d, F), dtype=np.float32) * F ** -0.5, gpu)
+    od, wd = _dev(off, gpu, torch.int32), _dev(widx, gpu, torch.int32)
+    ws = api.ffn_workspace(gpu) if use_ws else None
+    p = lambda t: t.data_ptr()  # noqa: E731
+    wp, wn = (p(ws), ws.numel()) if use_ws else (None, 0)
+    st = torch.cuda.current_stream().cuda_stream
+
+    def rows_buf(cols, fill):  # guarded rows, optionally off the 128-byte line
+        raw = torch.full((N * cols + 256,), fill, dtype=torch.bfloat16, device=gpu)
+        return raw[misalign:misalign + N * cols].view(N, cols), raw
+
+    outs = []
+    for pair in (False, True):
+        (h, hr), (y, yr), (au, ar) = rows_buf(F, 3.0), rows_buf(d, 3.0), rows_buf(2 * F, 3.0)
+        (dau, dr), (dx, xr) = rows_buf(2 * F, 3.0), rows_buf(d, 3.0)
+        for _ in range(2):  # twice: the counters must be back at zero
+            if pair:
+                rc = [lib.foremoe_grouped_ffn_fwd(p(x), 1, d, F, S, p(od), p(wd), W, p(gu), p(dn), N, p(h), p(y),
+                                                  p(au), wp, wn, st),
+                      lib.foremoe_grouped_ffn_dgrad(p(dy), p(au), 1, d, F, S, p(od), p(wd), W, p(gu), p(dn), N,
+                                                    p(dau), p(dx), wp, wn, st)]
+            else:
+                rc = [lib.foremoe_ffn_gate_up_fwd(p(x), 1, d, F, S, p(od), p(wd), W, p(gu), N, p(h), p(au), wp, wn,
+                                                  st),
+                      lib.foremoe_ffn_down_fwd(p(h), 1, d, F, S, p(od), p(wd), W, p(dn), N, p(y), wp, wn, st),
+                      lib.foremoe_ffn_down_dgrad(p(dy), p(au), 1, d, F, S, p(od), p(wd), W, p(dn), N, p(dau), wp, wn,
+                                                 st),
+                      lib.foremoe_ffn_gate_up_dgrad(p(dau), 1, d, F, S, p(od), p(wd), W, p(gu), N, p(dx), wp, wn,
+                                                    st)]
+            assert rc == [0] * len(rc)
+        torch.cuda.synchronize()
+        if use_ws:
+            assert not bool(ws[:65536].any()), "counters not back at zero"
+        for raw, t in ((hr, h), (yr, y), (ar, au), (dr, dau), (xr, dx)):  # nothing outside the rows
+            assert bool((raw[:misalign] == 3.0).all()) and bool((raw[misalign + t.numel():] == 3.0).all())
+        outs.append((h, y, au, dau, dx))
+    gu64, dn64 = _f64(gu), _f64(dn)
+    for pair, (h, y, au, dau, dx) in enumerate(outs):
+        for j, w in enumerate(widx):
+            r = slice(off[j], off[j + 1])
+            if rows[j] == 0:
+                continue
+            if not 0 <= w < W:
+                assert all(bool((t[r] == 3.0).all()) for t in (h, y, au, dau, dx))
+                continue
+            tag = f"pair={bool(pair)} slot {j} ({rows[j]} rows)"
+            X, G, D = _f64(x[r]), gu64[w], dn64[w]
+            AU = _f64(au[r])
+            _close(tag + " A|U", AU, X @ G.T, np.abs(X) @ np.abs(G).T, d)
+            A, U = np.split(X @ G.T, 2, axis=1)  # H comes from the unrounded sums
+            mA, mU = np.split(np.abs(X) @ np.abs(G).T, 2, axis=1)
+            s = 1 / (1 + np.exp(-A))
+            H = _f64(h[r])
+            _close(tag + " H", H, A * s * U, 1.2 * (mA * np.abs(U) + np.abs(A) * mU), d + 16)
+            _close(tag + " Y", _f64(y[r]), H @ D.T, np.abs(H) @ np.abs(D).T, F)
+            A, U = np.split(AU, 2, axis=1)
+            s = 1 / (1 + np.exp(-A))
+            DY, DAU = _f64(dy[r]), _f64(dau[r])
+            dH, mH = DY @ D, np.abs(DY) @ np.abs(D)
+            ds = s + A * s * (1 - s)
+            _close(tag + " dA", DAU[:, :F], dH * U * ds, mH * np.abs(U) * (s + np.abs(A) * s * (1 - s)), d + 16)
+            _close(tag + " dU", DAU[:, F:], dH * A * s, mH * np.abs(A) * s, d + 16)
+            _close(tag + " dX", _f64(dx[r]), DAU @ G, np.abs(DAU) @ np.abs(G), 2 * F)
+
+
+# rows at the edges of the three tile heights; widths that end in a column
+# tile of 128, fewer and more than 12 column tiles (row groups of 8)
+LAYOUTS = {
+    "edges": ([1, 63, 64, 65, 0, 127, 128, 129, 255, 256, 257, 0, 320, 321, 384, 385], 256, 128),
+    "odd-width": ([5, 200, 700, 40, 0, 90], 384, 640),
+    "thin-only": ([3, 0, 17, 64], 1024, 256),
+    "row-groups": ([2304, 40, 300], 3328, 1664),
+    "rounds": ([3000, 1500, 100, 60, 900], 1152, 896),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("use_ws", [True, False])
+@pytest.mark.parametrize("name", list(LAYOUTS))
+def test_row_tiles(gpu, name, use_ws):
+    rows, d, F = LAYOUTS[name]
+    print(f"\n[case] row tiles {name}: rows {rows}, d={d}, F={F}, workspace {use_ws}", flush=True)
+    _check(gpu, rows, d, F, 3, use_ws)
+
+
+@pytest.mark.gpu
+def test_row_tiles_many_slots(gpu):
+    """More slots than one wavefront's table pass, with bad weight indices."""
+    rows = [int(v) for v in np.random.default_rng(3).integers(0, 90, 300)]
+    rows[7], rows[299] = 500, 300
+    widx = np.arange(300) % 3
+    widx[5], widx[7] = -1, 3
+    print(f"\n[case] row tiles, 300 slots, {sum(rows)} rows", flush=True)
+    _check(gpu, rows, 256, 128, 3, True, widx=widx)
+
+
+@pytest.mark.gpu
+def test_row_tiles_rows_off_the_line(gpu):
+    """Handed-over rows that do not start on a 128-byte line: two launches."""
+    print("\n[case] row tiles, rows 16 bytes off the line", flush=True)
+    _check(gpu, [300, 70, 30], 256, 128, 2, True, misalign=8)
