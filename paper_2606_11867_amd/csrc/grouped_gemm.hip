@@ -1599,8 +1599,10 @@ struct WgradArgs {
 };
 
 // Tiles of one group's dW that a call computes, and the index of the i-th.
+// M and N are multiples of 128: a last row or column of 256-wide tiles may be
+// half empty.
 __device__ __forceinline__ int wgrad_call_tiles(const WgradArgs& a, int BM, int BN) {
-  return ((a.M / BM) * (a.N / BN) - a.tpart + a.tparts - 1) / a.tparts;
+  return (((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN) - a.tpart + a.tparts - 1) / a.tparts;
 }
 __device__ __forceinline__ int wgrad_tile(const WgradArgs& a, int i) { return a.tpart + i * a.tparts; }
 
@@ -1610,26 +1612,40 @@ __device__ __forceinline__ int wgrad_tile(const WgradArgs& a, int i) { return a.
 struct WgradPlan {
   int beg[FOREMOE_MAX_SLOTS];        // clamped row range [beg, end) of virtual slot v in its step's rows
   int end[FOREMOE_MAX_SLOTS];
-  int gs[FOREMOE_MAX_SLOTS];         // step << 16 | gradient index, -1 for empty/invalid slots
+  uint16_t gs[FOREMOE_MAX_SLOTS];    // step << 10 | gradient index, kNoSlot for empty/invalid slots
+  uint16_t next[FOREMOE_MAX_SLOTS];  // next virtual slot of the same group, kNoSlot after the last
+  uint16_t first[FOREMOE_MAX_SLOTS];  // first virtual slot of each group
   int rows[FOREMOE_MAX_SLOTS];       // rows per group
-  int order[FOREMOE_MAX_SLOTS];      // groups by descending rows
-  int ibase[FOREMOE_MAX_SLOTS + 1];  // work-item prefix over ordered groups
+  uint16_t order[FOREMOE_MAX_SLOTS];  // groups by descending rows
+  uint16_t rem[FOREMOE_MAX_SLOTS];   // ordered groups with a last, partial chunk, by its descending size
+  int ibase[FOREMOE_MAX_SLOTS + 1];  // prefix over ordered groups of their whole chunks
   int pbase[FOREMOE_MAX_SLOTS + 1];  // partial-tile prefix over ordered groups
   const uint16_t* A[FOREMOE_MAX_WGRAD_STEPS];  // operands of each step
   const uint16_t* B[FOREMOE_MAX_WGRAD_STEPS];
+  unsigned long long total;          // rows of all groups
   int nne;                           // non-empty groups
+  int nrem;                          // groups with a partial chunk
   int ch;                            // chunk rows (INT_MAX: no split)
-  __device__ __forceinline__ int gidx(int v) const { return gs[v] < 0 ? -1 : (gs[v] & 0xFFFF); }
-  __device__ __forceinline__ int step(int v) const { return gs[v] >> 16; }
+  static constexpr int kNoSlot = 0xFFFF;
+  __device__ __forceinline__ int gidx(int v) const { return gs[v] & 1023; }
+  __device__ __forceinline__ int step(int v) const { return gs[v] >> 10; }
 };
+static_assert(FOREMOE_MAX_SLOTS <= 1024 && FOREMOE_MAX_WGRAD_STEPS <= 32, "gs fields");
 
+// Every workgroup builds the plan, so it has to be quick: a slot finds its
+// group's next one once here (walked through at every item and every slot
+// change, 80 to 160 virtual slots cost each item thousands of cycles), and
+// one wavefront does the prefix sums and the ranking of the partial chunks.
 template <int BM, int BN, int BK>
 __device__ void build_wgrad_plan(const WgradArgs& a, WgradPlan& P) {
   const int tid = threadIdx.x;
   const int G = a.G, V = a.V;
   const int tpg = wgrad_call_tiles(a, BM, BN);
   const int nt = blockDim.x;
-  if (tid == 0) P.nne = 0;
+  if (tid == 0) {
+    P.nne = P.nrem = 0;
+    P.total = 0;
+  }
   // the step table into LDS with compile-time indices (a kernel argument
   // indexed at run time would be copied to scratch)
 #pragma unroll
@@ -1639,7 +1655,11 @@ __device__ void build_wgrad_plan(const WgradArgs& a, WgradPlan& P) {
       P.B[m] = a.step[m].B;
     }
   }
-  for (int g = tid; g < G; g += nt) P.rows[g] = 0;
+  int* first = P.ibase;  // (free until the prefix sums)
+  for (int g = tid; g < G; g += nt) {
+    P.rows[g] = 0;
+    first[g] = INT_MAX;
+  }
   for (int v = tid; v < V; v += nt) {
     int m = 0;
 #pragma unroll
@@ -1657,53 +1677,84 @@ __device__ void build_wgrad_plan(const WgradArgs& a, WgradPlan& P) {
         n_cap = a.step[q].n_cap;
         j = v - a.step[q].vbase;
       }
-    int64_t lo = off[j], hi = off[j + 1];
-    lo = lo < 0 ? 0 : (lo > n_cap ? n_cap : lo);
-    hi = hi < 0 ? 0 : (hi > n_cap ? n_cap : hi);
+    const int lo = (int)clamp_row(off[j], n_cap), hi = (int)clamp_row(off[j + 1], n_cap);
     const int g = gi[j];
     const bool ok = g >= 0 && g < G && hi > lo;
-    P.beg[v] = (int)lo;
-    P.end[v] = ok ? (int)hi : (int)lo;
-    P.gs[v] = ok ? (m << 16 | g) : -1;
+    P.beg[v] = lo;
+    P.end[v] = ok ? hi : lo;
+    P.gs[v] = (uint16_t)(ok ? (m << 10 | g) : WgradPlan::kNoSlot);
   }
   __syncthreads();
-  for (int v = tid; v < V; v += nt)
-    if (P.gs[v] >= 0) atomicAdd(&P.rows[P.gidx(v)], P.end[v] - P.beg[v]);
+  for (int v = tid; v < V; v += nt) {
+    const int gs = P.gs[v];
+    if (gs == WgradPlan::kNoSlot) continue;
+    const int g = gs & 1023, n = P.end[v] - P.beg[v];
+    atomicAdd(&P.rows[g], n);
+    atomicMin(&first[g], v);
+    atomicAdd(&P.total, (unsigned long long)n);
+    int w = v + 1;
+    while (w < V && (P.gs[w] == WgradPlan::kNoSlot || (P.gs[w] & 1023) != g)) ++w;
+    P.next[v] = (uint16_t)(w < V ? w : WgradPlan::kNoSlot);
+  }
   __syncthreads();
   for (int g = tid; g < G; g += nt) {
     const int rg = P.rows[g];
     if (rg <= 0) continue;
+    P.first[g] = (uint16_t)first[g];
     int rank = 0;
     for (int h = 0; h < G; ++h) {
       const int rh = P.rows[h];
       rank += (rh > rg) || (rh == rg && h < g);
     }
-    P.order[rank] = g;
+    P.order[rank] = (uint16_t)g;
     atomicAdd(&P.nne, 1);
   }
   __syncthreads();
-  if (tid == 0) {
-    long long total = 0;
-    for (int i = 0; i < P.nne; ++i) total += P.rows[P.order[i]];
+  if (tid < 64) {
+    const int nne = __builtin_amdgcn_readfirstlane(P.nne), lane = lane64();
     int ch = INT_MAX;
-    if (a.p_max > 0 && total > 0) {
-      long long c = (total * tpg + a.p_max - 1) / a.p_max;
+    if (a.p_max > 0 && nne > 0) {
+      unsigned long long c = (P.total * (unsigned)tpg + (unsigned)a.p_max - 1) / (unsigned)a.p_max;
       c = (c + BK - 1) / BK * BK;
-      if (c < BK) c = BK;
       ch = c > INT_MAX ? INT_MAX : (int)c;
     }
-    P.ch = ch;
-    int ib = 0, pb = 0;
-    for (int i = 0; i < P.nne; ++i) {
-      const int rg = P.rows[P.order[i]];
-      const int cg = ch == INT_MAX ? 1 : (rg + ch - 1) / ch;
-      P.ibase[i] = ib;
-      P.pbase[i] = pb;
-      ib += cg * tpg;
-      pb += (cg - 1) * tpg;
+    int ib = 0, pb = 0, nrem = 0;
+    for (int i0 = 0; i0 < nne; i0 += 64) {
+      const int i = i0 + lane;
+      const int rg = i < nne ? P.rows[P.order[i]] : 0;
+      const int whole = ch == INT_MAX ? 0 : rg / ch, ri = rg - whole * (ch == INT_MAX ? 0 : ch);
+      const int wt = whole * tpg, pt = rg > 0 ? (whole + (ri > 0) - 1) * tpg : 0;
+      int wi = wt, pi = pt;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int w = __shfl_up(wi, o, 64), p = __shfl_up(pi, o, 64);
+        if (lane >= o) {
+          wi += w;
+          pi += p;
+        }
+      }
+      if (i < nne) {
+        P.ibase[i] = ib + wi - wt;
+        P.pbase[i] = pb + pi - pt;
+      }
+      ib += __shfl(wi, 63, 64);
+      pb += __shfl(pi, 63, 64);
+      // ranked within these 64 groups (all there are, but for huge tables)
+      int rank = nrem;
+      const int n = nne - i0 < 64 ? nne - i0 : 64;
+      for (int h = 0; h < n; ++h) {
+        const int rh = __builtin_amdgcn_readlane(ri, h);
+        rank += (rh > ri) || (rh == ri && h < lane);
+      }
+      if (ri > 0) P.rem[rank] = (uint16_t)i;
+      nrem += __popcll(__ballot(ri > 0));
     }
-    P.ibase[P.nne] = ib;
-    P.pbase[P.nne] = pb;
+    if (lane == 0) {
+      P.ibase[nne] = ib;
+      P.pbase[nne] = pb;
+      P.nrem = nrem;
+      P.ch = ch;
+    }
   }
   __syncthreads();
 }
@@ -1717,56 +1768,49 @@ struct KCursor {
   const uint16_t* pb;
 };
 
-__device__ __forceinline__ void cursor_next_slot(const WgradPlan& P, int V, int g, int s1, KCursor& c) {
-  int j = c.j, pos = c.pos;
-  for (;;) {
-    if (j >= 0 && P.gidx(j) == g) pos += P.end[j] - P.beg[j];
-    ++j;
-    if (j >= V || pos >= s1) {
-      c.done = true;
-      return;
-    }
-    if (P.gidx(j) == g) break;
-  }
-  c.j = j;
-  c.pos = pos;
-  c.lo = P.beg[j];
-  const int n = P.end[j] - P.beg[j];
-  c.hi = P.beg[j] + (n < s1 - pos ? n : s1 - pos);
+__device__ __forceinline__ void cursor_slot(const WgradPlan& P, int s0, int s1, KCursor& c) {
+  const int beg = __builtin_amdgcn_readfirstlane(P.beg[c.j]), end = __builtin_amdgcn_readfirstlane(P.end[c.j]);
+  const int n = end - beg, skip = s0 > c.pos ? s0 - c.pos : 0;
+  c.lo = beg + skip;
+  c.hi = beg + (n < s1 - c.pos ? n : s1 - c.pos);
   c.k = c.lo;
-  c.pa = uniform_ptr(P.A[P.step(j)]);
-  c.pb = uniform_ptr(P.B[P.step(j)]);
+  const int m = __builtin_amdgcn_readfirstlane(P.step(c.j));
+  c.pa = uniform_ptr(P.A[m]);
+  c.pb = uniform_ptr(P.B[m]);
 }
 
-__device__ __forceinline__ KCursor cursor_begin(const WgradPlan& P, int V, int g, int s0, int s1) {
+__device__ __forceinline__ void cursor_next_slot(const WgradPlan& P, int s1, KCursor& c) {
+  const int next = __builtin_amdgcn_readfirstlane(P.next[c.j]);
+  c.pos += __builtin_amdgcn_readfirstlane(P.end[c.j]) - __builtin_amdgcn_readfirstlane(P.beg[c.j]);
+  if (next == WgradPlan::kNoSlot || c.pos >= s1) {
+    c.done = true;
+    return;
+  }
+  c.j = next;
+  cursor_slot(P, 0, s1, c);
+}
+
+// [s0, s1) is not empty and lies inside the group's rows.
+__device__ __forceinline__ KCursor cursor_begin(const WgradPlan& P, int g, int s0, int s1) {
   KCursor c;
   c.done = false;
-  int pos = 0;
-  for (int j = 0; j < V; ++j) {
-    if (P.gidx(j) != g) continue;
-    const int n = P.end[j] - P.beg[j];
-    if (pos + n > s0) {
-      c.j = j;
-      c.pos = pos;
-      c.lo = P.beg[j] + (s0 - pos);
-      c.hi = P.beg[j] + (n < s1 - pos ? n : s1 - pos);
-      c.k = c.lo;
-      c.pa = uniform_ptr(P.A[P.step(j)]);
-      c.pb = uniform_ptr(P.B[P.step(j)]);
-      return c;
-    }
-    pos += n;
+  c.pos = 0;
+  c.j = __builtin_amdgcn_readfirstlane(P.first[g]);
+  for (;;) {
+    const int n = __builtin_amdgcn_readfirstlane(P.end[c.j]) - __builtin_amdgcn_readfirstlane(P.beg[c.j]);
+    const int next = __builtin_amdgcn_readfirstlane(P.next[c.j]);
+    if (c.pos + n > s0 || next == WgradPlan::kNoSlot) break;
+    c.pos += n;
+    c.j = next;
   }
-  c.done = true;
-  c.pa = uniform_ptr(P.A[0]);
-  c.pb = uniform_ptr(P.B[0]);
+  cursor_slot(P, s0, s1, c);
   return c;
 }
 
 template <int BK>
-__device__ __forceinline__ void cursor_advance(const WgradPlan& P, int V, int g, int s1, KCursor& c) {
+__device__ __forceinline__ void cursor_advance(const WgradPlan& P, int s1, KCursor& c) {
   c.k += BK;
-  if (c.k >= c.hi) cursor_next_slot(P, V, g, s1, c);
+  if (c.k >= c.hi) cursor_next_slot(P, s1, c);
 }
 
 template <int BM, int BN, int BK, int NS, int WGM, int WGN>
@@ -1791,9 +1835,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_wgrad_kernel(WgradArgs a)
       a.plan_out[4 + 3 * i] = P.pbase[i];
     }
   }
-  const int V = a.V;
-  const int nt_n = a.N / BN, tpg = wgrad_call_tiles(a, BM, BN);
-  const int total = P.ibase[P.nne];
+  const int nt_n = (a.N + BN - 1) / BN, tpg = wgrad_call_tiles(a, BM, BN);
+  const int whole = __builtin_amdgcn_readfirstlane(P.ibase[P.nne]);
+  const int total = whole + __builtin_amdgcn_readfirstlane(P.nrem) * tpg;
   const int lane = lane64(), wave = wave_id();
   const int wm = wave / WGN, wn = wave % WGN;
   const uint32_t lds0 = lds_addr(lds);
@@ -1801,9 +1845,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_wgrad_kernel(WgradArgs a)
   CoreT core;
   const typename CoreT::template Offsets<AT, BT, BK> offs(lane, wm, wn);
 
-  // Items (output tile x row chunk) come in descending group size. With
-  // work counters each workgroup takes the next item when it is free, which
-  // balances the very uneven item sizes; without, a fixed stride (XCD-aware).
+  // Items (output tile x row chunk) come in descending size: the whole chunks
+  // of all groups, then the groups' last, partial ones. (Group by group, a
+  // large group's small rest ran before the next group's whole chunks, which
+  // then ended late: 4 micro-steps of the Qwen3 share, down 0.84 of that time
+  // in a simulation of the item sizes.) With work counters each workgroup
+  // takes the next item when it is free, which balances the very uneven
+  // sizes; without, a fixed stride (XCD-aware).
   __shared__ int s_item;
   auto next_item = [&](int prev) -> int {
     if (!a.sched) return prev < 0 ? xcd_virtual_id() : prev + (int)gridDim.x;
@@ -1812,16 +1860,25 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_wgrad_kernel(WgradArgs a)
     return s_item;
   };
   for (int t = next_item(-1); t < total; t = next_item(t)) {
-    int lo = 0, hi = P.nne - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (P.ibase[mid] <= t) lo = mid;
-      else hi = mid - 1;
+    int lo, local, c;  // ordered group, item within its whole (partial) chunks, chunk
+    if (t < whole) {
+      lo = 0;
+      int hi = P.nne - 1;
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (P.ibase[mid] <= t) lo = mid;
+        else hi = mid - 1;
+      }
+      lo = __builtin_amdgcn_readfirstlane(lo);
+      local = t - P.ibase[lo];
+      c = local / tpg;
+    } else {
+      local = t - whole;
+      lo = __builtin_amdgcn_readfirstlane(P.rem[local / tpg]);
+      c = P.ch == INT_MAX ? 0 : P.rows[P.order[lo]] / P.ch;
     }
-    const int gi = __builtin_amdgcn_readfirstlane(lo);
-    const int g = P.order[gi];
-    const int local = t - P.ibase[gi];
-    const int c = local / tpg, tile_l = local % tpg, tile = wgrad_tile(a, tile_l);
+    const int gi = lo, g = __builtin_amdgcn_readfirstlane(P.order[gi]);
+    const int tile_l = local % tpg, tile = wgrad_tile(a, tile_l);
     const int m0 = (tile / nt_n) * BM, n0 = (tile % nt_n) * BN;
     const int rg = P.rows[g];
     const int s0 = P.ch == INT_MAX ? 0 : c * P.ch;
@@ -1829,9 +1886,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_wgrad_kernel(WgradArgs a)
 
     // number of k-tiles of this chunk (each k-tile stays inside one slot)
     int KT = 0;
-    for (KCursor cc = cursor_begin(P, V, g, s0, s1); !cc.done; cursor_next_slot(P, V, g, s1, cc))
+    for (KCursor cc = cursor_begin(P, g, s0, s1); !cc.done; cursor_next_slot(P, s1, cc))
       KT += (cc.hi - cc.lo + BK - 1) / BK;
-    KCursor ic = cursor_begin(P, V, g, s0, s1);
+    KCursor ic = cursor_begin(P, g, s0, s1);
     auto koa = [&](int k) -> uint32_t { return (uint32_t)k * lda2 + (uint32_t)m0 * 2u; };
     auto kob = [&](int k) -> uint32_t { return (uint32_t)k * ldb2 + (uint32_t)n0 * 2u; };
     const uint32_t va0 = AT::voff(lane, koa, 0), vb0 = BT::voff(lane, kob, 0);
@@ -1856,7 +1913,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_wgrad_kernel(WgradArgs a)
         BT::issue_s(buf_rsrc(ic.pb + (int64_t)k * a.ldb, nrow * ldb2), sa + AT::BYTES, vb0, sb_[p - AT::PER_WAVE],
                     p - AT::PER_WAVE);
       }
-      if (p == AT::PER_WAVE + BT::PER_WAVE - 1 && live) cursor_advance<BK>(P, V, g, s1, ic);
+      if (p == AT::PER_WAVE + BT::PER_WAVE - 1 && live) cursor_advance<BK>(P, s1, ic);
     };
 
     core.zero();
@@ -1864,7 +1921,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_wgrad_kernel(WgradArgs a)
     __syncthreads();
 
     const int l32 = lane & 31, c4 = (lane >> 5) * 4;
-    if (c == 0) {
+    // a wave past the last row or column of dW (both multiples of 128) has
+    // nothing to add
+    static_assert(128 % CoreT::WM == 0 && 128 % CoreT::WN == 0, "waves are wholly inside or outside");
+    const bool inside = m0 + wm * CoreT::WM < a.M && n0 + wn * CoreT::WN < a.N;
+    if (!inside) {
+      // (falls through to the barrier below)
+    } else if (c == 0) {
       // dW += acc. The current dW values of this wave's output are brought
       // into LDS with asynchronous buffer loads (two 32-row blocks at a time,
       // all loads in flight together; each wave uses its own LDS region, so
@@ -1975,7 +2038,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradArgs a) {
   const int* pl = a.plan_out;
   const int nne = pl[0], ch = pl[1];
   if (ch == INT_MAX) return;
-  const int nt_n = a.N / BN, tpg = wgrad_call_tiles(a, BM, BN);
+  const int nt_n = (a.N + BN - 1) / BN, tpg = wgrad_call_tiles(a, BM, BN);
   int nsplit = 0;
   while (nsplit < nne && (pl[3 + 3 * nsplit] + ch - 1) / ch > 1) ++nsplit;
   const int total = nsplit * tpg * kReduceParts;
@@ -2008,14 +2071,17 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradArgs a) {
         }
       }
       float4 o[V];
+      // (rows and columns of the tile past dW's are left alone)
+      auto in_dw = [&](int e) { return m0 + e / BN < a.M && n0 + e % BN < a.N; };
 #pragma unroll
       for (int v = 0; v < V; ++v) {
         const int e = e0 + v * 1024;
-        o[v] = *reinterpret_cast<const float4*>(Cg + (int64_t)(m0 + e / BN) * a.ldc + n0 + e % BN);
+        if (in_dw(e)) o[v] = *reinterpret_cast<const float4*>(Cg + (int64_t)(m0 + e / BN) * a.ldc + n0 + e % BN);
       }
 #pragma unroll
       for (int v = 0; v < V; ++v) {
         const int e = e0 + v * 1024;
+        if (!in_dw(e)) continue;
         o[v].x += s[v].x;
         o[v].y += s[v].y;
         o[v].z += s[v].z;
@@ -2439,6 +2505,7 @@ static int wgrad_common(const char* who, const foremoe_wgrad_step* steps, int32_
   if (dtype == FOREMOE_BF16) {
     WgradArgs a{};
     int v = 0;
+    int64_t rows = 0;  // at most
     for (int m = 0; m < n; ++m) {
       const foremoe_wgrad_step& t = steps[m];
       if (t.S == 0 || t.n_cap == 0) continue;  // contributes nothing
@@ -2450,6 +2517,7 @@ static int wgrad_common(const char* who, const foremoe_wgrad_step* steps, int32_
       q.S = t.S;
       q.vbase = v;
       q.n_cap = t.n_cap;
+      rows += t.n_cap;
       v += t.S;
     }
     a.V = v;
@@ -2471,7 +2539,18 @@ static int wgrad_common(const char* who, const foremoe_wgrad_step* steps, int32_
     a.part = has_part ? (float*)((char*)ws + kWgradHeaderBytes + kWgradPlanBytes) : nullptr;
     const size_t part_bytes = has_part ? ws_bytes - kWgradHeaderBytes - kWgradPlanBytes : 0;
     const dim3 grid(persistent_grid()), block(256);
-    if (M % 256 == 0 && N % 256 == 0) {
+    // 256 x 256 tiles. Where a dimension is an odd multiple of 128, too, with
+    // half-empty last ones, if these make the work at most 1.6 times as much
+    // and there is enough of it: 128 -> 256 tiles, both products, 12 groups of
+    // 200 / 2000 / 16000 rows in all (us): d = 1152, F = 896 110 -> 94 /
+    // 151 -> 122 / 291 -> 227; d = 640, F = 384 56 -> 62 / 94 -> 76 /
+    // 135 -> 112; d = 384, F = 128 45 -> 47 / 58 -> 63 / 127 -> 130; d = F =
+    // 128 (twice and four times the work) 41 -> 51 / 51 -> 64 / 126 -> 151. A
+    // call for one part of several keeps the tile numbering of the interface,
+    // which has 128 x 128 tiles there.
+    const int64_t area = (int64_t)M * N, padded = (int64_t)((M + 255) / 256) * ((N + 255) / 256) * 65536;
+    const bool odd_ok = parts == 1 && 5 * padded <= 8 * area && area >= 131072 && (area >= 1048576 || rows >= 1024);
+    if ((M % 256 == 0 && N % 256 == 0) || odd_ok) {
       constexpr int WGM = FM_WG_WGM, WGN = FM_WG_WGN;
       a.p_max = (int)(part_bytes / (256 * 256 * 4));
       hipLaunchKernelGGL((gemm_wgrad_kernel<256, 256, FM_WG_BK, FM_WG_NS, WGM, WGN>), grid, dim3(64 * WGM * WGN), 0,
