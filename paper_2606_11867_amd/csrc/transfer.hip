@@ -11,7 +11,13 @@
 // name one gradient applied in record order in fp32, so the result is
 // deterministic. Both kernels are HBM-bound copies moving 16-byte vectors
 // with the nontemporal hint (the data streams through once); every record
-// boundary and part boundary is a multiple of 16 bytes.
+// boundary and part boundary is a multiple of 16 bytes. One vector per
+// thread and one pass per workgroup: the hardware's dispatch then keeps the
+// accesses in flight close together in memory, while about 4 workgroups per
+// CU striding through a record each spread them over all of it. Copy-out and
+// copy-in of 20 experts (2.2 GB moved, two gradients added): 466 us striding,
+// 356 with one vector per thread (6.3 TB/s), 361 with 2, 367 with 4, 449 with
+// 8; at 4, 395 without the hint, 378 with it on loads only, 383 on stores.
 //
 // The prefetch is a host-to-device DMA (hipMemcpyAsync on the caller's
 // stream) straight into the weight slots: no kernel and no GPU buffer.
@@ -27,7 +33,14 @@ namespace {
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kXferThreads = 256;
-constexpr int kXferVecPerThread = 4;  // 16-byte vectors per thread per pass, all loads before the stores
+constexpr uint32_t kXferChunk = kXferThreads * 16;  // bytes a workgroup moves: one 16-byte vector per thread
+
+__device__ __forceinline__ u32x4 xfer_load(const char* p) {
+  return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+}
+__device__ __forceinline__ void xfer_store(char* p, u32x4 v) {
+  __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p));
+}
 
 struct XferRecords {
   int32_t widx[FOREMOE_MAX_XFER_RECORDS];
@@ -66,30 +79,15 @@ __device__ __forceinline__ char* part_addr(const RecordParts& rp, uint64_t off, 
   return gdn + (uint64_t)rec.gidx[r] * rp.dn_g + off;
 }
 
-// Copy-out: record r = blockIdx.y. Each thread moves kXferVecPerThread
-// vectors per pass, issuing every load before the first store.
+// Copy-out: record r = blockIdx.y, one vector per thread.
 __global__ __launch_bounds__(kXferThreads) void copy_out_kernel(RecordParts rp, XferRecords rec, const char* wgu,
                                                                 const char* wdn, const char* ggu, const char* gdn,
                                                                 char* buf) {
   const int r = blockIdx.y;
-  const uint64_t nvec = rp.total() / 16;
-  char* dst = buf + (uint64_t)r * rp.total();
-  const uint64_t step = (uint64_t)gridDim.x * kXferThreads * kXferVecPerThread;
-  for (uint64_t v0 = (uint64_t)blockIdx.x * kXferThreads * kXferVecPerThread + threadIdx.x; v0 < nvec; v0 += step) {
-    u32x4 a[kXferVecPerThread];
-#pragma unroll
-    for (int u = 0; u < kXferVecPerThread; ++u) {
-      const uint64_t v = v0 + (uint64_t)u * kXferThreads;
-      if (v < nvec)
-        a[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(
-            part_addr(rp, v * 16, r, rec, (char*)wgu, (char*)wdn, (char*)ggu, (char*)gdn)));
-    }
-#pragma unroll
-    for (int u = 0; u < kXferVecPerThread; ++u) {
-      const uint64_t v = v0 + (uint64_t)u * kXferThreads;
-      if (v < nvec) __builtin_nontemporal_store(a[u], reinterpret_cast<u32x4*>(dst + v * 16));
-    }
-  }
+  const uint64_t total = rp.total(), off = (uint64_t)blockIdx.x * kXferChunk + threadIdx.x * 16u;
+  if (off < total)
+    xfer_store(buf + (uint64_t)r * total + off,
+               xfer_load(part_addr(rp, off, r, rec, (char*)wgu, (char*)wdn, (char*)ggu, (char*)gdn)));
 }
 
 // Copy-in work: rows [0, n_par) copy record par[i]'s parameters into weight
@@ -106,68 +104,41 @@ struct CopyInPlan {
   int32_t ord[FOREMOE_MAX_XFER_RECORDS];
 };
 
-__device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
+__device__ __forceinline__ u32x4 add4(u32x4 a, u32x4 b) {
+  u32x4 r;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r[i] = __float_as_uint(__uint_as_float(a[i]) + __uint_as_float(b[i]));
+  return r;
+}
 
 __global__ __launch_bounds__(kXferThreads) void copy_in_kernel(RecordParts rp, XferRecords rec, CopyInPlan pl,
                                                                const char* buf, char* wgu, char* wdn, float* ggu,
                                                                float* gdn) {
   const int row = blockIdx.y;
   const uint64_t rbytes = rp.total();
-  const uint64_t step = (uint64_t)gridDim.x * kXferThreads * kXferVecPerThread;
-  const uint64_t first = (uint64_t)blockIdx.x * kXferThreads * kXferVecPerThread + threadIdx.x;
+  const uint64_t off = (uint64_t)blockIdx.x * kXferChunk + threadIdx.x * 16u;
   if (row < pl.n_par) {
+    if (off >= rp.gu_p + rp.dn_p) return;
     const int r = pl.par[row];
-    const uint64_t nvec = (rp.gu_p + rp.dn_p) / 16;
-    const char* src = buf + (uint64_t)r * rbytes;
-    for (uint64_t v0 = first; v0 < nvec; v0 += step) {
-      u32x4 a[kXferVecPerThread];
-#pragma unroll
-      for (int u = 0; u < kXferVecPerThread; ++u) {
-        const uint64_t v = v0 + (uint64_t)u * kXferThreads;
-        if (v < nvec) a[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + v * 16));
-      }
-#pragma unroll
-      for (int u = 0; u < kXferVecPerThread; ++u) {
-        const uint64_t v = v0 + (uint64_t)u * kXferThreads;
-        if (v >= nvec) continue;
-        const uint64_t off = v * 16;
-        char* dst = off < rp.gu_p ? wgu + (uint64_t)rec.widx[r] * rp.gu_p + off
-                                  : wdn + (uint64_t)rec.widx[r] * rp.dn_p + (off - rp.gu_p);
-        __builtin_nontemporal_store(a[u], reinterpret_cast<u32x4*>(dst));
-      }
-    }
+    char* dst = off < rp.gu_p ? wgu + (uint64_t)rec.widx[r] * rp.gu_p + off
+                              : wdn + (uint64_t)rec.widx[r] * rp.dn_p + (off - rp.gu_p);
+    xfer_store(dst, xfer_load(buf + (uint64_t)r * rbytes + off));
     return;
   }
+  if (off >= rp.gu_g + rp.dn_g) return;
   const int g = row - pl.n_par;
   const int tgt = pl.grp_tgt[g], start = pl.grp_start[g];
   const int a0 = pl.grp_off[g], a1 = pl.grp_off[g + 1];
-  const uint64_t par_bytes = rp.gu_p + rp.dn_p;
-  const uint64_t nvec = (rp.gu_g + rp.dn_g) / 16;
-  const uint64_t gu_vec = rp.gu_g / 16;
-  for (uint64_t v0 = first; v0 < nvec; v0 += step) {
-#pragma unroll
-    for (int u = 0; u < kXferVecPerThread; ++u) {
-      const uint64_t v = v0 + (uint64_t)u * kXferThreads;
-      if (v >= nvec) continue;
-      float4* dst = v < gu_vec ? reinterpret_cast<float4*>(ggu) + (uint64_t)tgt * gu_vec + v
-                               : reinterpret_cast<float4*>(gdn) + (uint64_t)tgt * (rp.dn_g / 16) + (v - gu_vec);
-      float4 acc = start >= 0 ? *reinterpret_cast<const float4*>(buf + (uint64_t)start * rbytes + par_bytes + v * 16)
-                              : *dst;
-      for (int k = a0; k < a1; ++k)
-        acc = add4(acc, *reinterpret_cast<const float4*>(buf + (uint64_t)pl.ord[k] * rbytes + par_bytes + v * 16));
-      *dst = acc;
-    }
-  }
+  const char* rec0 = buf + rp.gu_p + rp.dn_p + off;  // this vector in record 0
+  char* dst = off < rp.gu_g ? (char*)ggu + (uint64_t)tgt * rp.gu_g + off
+                            : (char*)gdn + (uint64_t)tgt * rp.dn_g + (off - rp.gu_g);
+  u32x4 acc = xfer_load(start >= 0 ? rec0 + (uint64_t)start * rbytes : dst);
+  for (int k = a0; k < a1; ++k) acc = add4(acc, xfer_load(rec0 + (uint64_t)pl.ord[k] * rbytes));
+  xfer_store(dst, acc);
 }
 
-unsigned xfer_blocks_x(uint64_t nvec, int rows) {
-  // about 4 workgroups per CU over all rows together
-  const uint64_t per_block = (uint64_t)kXferThreads * kXferVecPerThread;
-  uint64_t want = (uint64_t)num_cus() * 4 / (uint64_t)(rows > 0 ? rows : 1);
-  if (want < 1) want = 1;
-  const uint64_t need = (nvec + per_block - 1) / per_block;
-  return (unsigned)std::max<uint64_t>(1, std::min(want, need));
-}
+// workgroups per record: chunks of its longest part list
+unsigned xfer_blocks_x(uint64_t bytes) { return (unsigned)((bytes + kXferChunk - 1) / kXferChunk); }
 
 }  // namespace
 }  // namespace foremoe
@@ -224,8 +195,7 @@ int foremoe_copy_out(const void* w_gate_up, const void* w_down, foremoe_dtype dt
   REQUIRE(!(what & FOREMOE_XFER_GRADS) || (dw_gate_up && dw_down), "copy_out: gradient arrays NULL");
   REQUIRE((((uintptr_t)w_gate_up | (uintptr_t)w_down | (uintptr_t)dw_gate_up | (uintptr_t)dw_down) & 15) == 0,
           "copy_out: expert arrays must be 16-byte aligned");
-  const uint64_t nvec = rp.total() / 16;
-  hipLaunchKernelGGL(copy_out_kernel, dim3(xfer_blocks_x(nvec, n), n), dim3(kXferThreads), 0, (hipStream_t)stream,
+  hipLaunchKernelGGL(copy_out_kernel, dim3(xfer_blocks_x(rp.total()), n), dim3(kXferThreads), 0, (hipStream_t)stream,
                      rp, rec, (const char*)w_gate_up, (const char*)w_down, (const char*)dw_gate_up,
                      (const char*)dw_down, (char*)buf);
   return check_launch("foremoe_copy_out");
@@ -286,8 +256,8 @@ int foremoe_copy_in(const void* buf, size_t buf_bytes, int32_t n, const int32_t*
           "copy_in: expert arrays must be 16-byte aligned");
   const int rows = pl.n_par + pl.n_grp;
   if (rows == 0) return FOREMOE_OK;
-  const uint64_t nvec = std::max(rp.gu_p + rp.dn_p, rp.gu_g + rp.dn_g) / 16;
-  hipLaunchKernelGGL(copy_in_kernel, dim3(xfer_blocks_x(nvec, rows), rows), dim3(kXferThreads), 0,
+  const uint64_t most = std::max(rp.gu_p + rp.dn_p, rp.gu_g + rp.dn_g);
+  hipLaunchKernelGGL(copy_in_kernel, dim3(xfer_blocks_x(most), rows), dim3(kXferThreads), 0,
                      (hipStream_t)stream, rp, rec, pl, (const char*)buf, (char*)w_gate_up, (char*)w_down, dw_gate_up,
                      dw_down);
   return check_launch("foremoe_copy_in");
