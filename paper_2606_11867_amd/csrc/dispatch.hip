@@ -429,6 +429,15 @@ struct RowReader {
   }
 };
 
+// STREAM: with the nontemporal hint.
+template <bool STREAM>
+__device__ __forceinline__ void store16(void* p, uint4 v) {
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  const u32x4 t = {v.x, v.y, v.z, v.w};
+  if constexpr (STREAM) __builtin_nontemporal_store(t, reinterpret_cast<u32x4*>(p));
+  else *reinterpret_cast<u32x4*>(p) = t;
+}
+
 __global__ __launch_bounds__(256) void permute_gather_kernel(
     const uint4* __restrict__ x, int64_t vec_per_row, const int32_t* __restrict__ ids, int64_t npairs, KeyMap km,
     int nkeys, int R_max, const int32_t* __restrict__ block_base, const uint16_t* __restrict__ rank,
@@ -514,7 +523,7 @@ __global__ __launch_bounds__(256) void permute_gather_kernel(
 #pragma unroll
           for (int u = 0; u < kVecPerLane; ++u) {
             const int64_t vi = v0 + u * 64 + lane;
-            if (vi < vec_per_row) x_perm[(int64_t)rows[r] * vec_per_row + vi] = a[r][u];
+            if (vi < vec_per_row) store16<false>(x_perm + (int64_t)rows[r] * vec_per_row + vi, a[r][u]);
           }
         }
       }
@@ -551,7 +560,7 @@ struct Vec<uint16_t> {
 #pragma unroll
     for (int i = 0; i < M / 2; ++i) w[i] = pack_bf2(f[2 * i], f[2 * i + 1]);
     if constexpr (M == 8) {
-      *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
+      store16<true>(p, make_uint4(w[0], w[1], w[2], w[3]));
     } else {
       *reinterpret_cast<uint2*>(p) = make_uint2(w[0], w[1]);
     }
@@ -570,7 +579,9 @@ struct Vec<float> {
   template <int M>
   __device__ static void store(float* p, const float* f) {
 #pragma unroll
-    for (int i = 0; i < M; i += 4) *reinterpret_cast<float4*>(p + i) = make_float4(f[i], f[i + 1], f[i + 2], f[i + 3]);
+    for (int i = 0; i < M; i += 4)
+      store16<true>(p + i, make_uint4(__float_as_uint(f[i]), __float_as_uint(f[i + 1]), __float_as_uint(f[i + 2]),
+                                __float_as_uint(f[i + 3])));
   }
 };
 
@@ -603,68 +614,77 @@ __device__ __forceinline__ TokenPairs token_pairs(const int32_t* __restrict__ pa
 }
 
 // ---------------------------------------------------------------------------
-// Step 5 (and the backward of step 3 with unit weights): one wavefront per
-// token, y[t] = sum_k g_k * Y[row_k] in ascending k, fp32 accumulation. The
-// rows of up to kPairGroup pairs are loaded together before accumulating.
+// Step 5 (and the backward of step 3 with unit weights): y[t] = sum_k g_k *
+// Y[row_k] in ascending k, fp32 accumulation. One wavefront per token and
+// column chunk (64 * kGatherChunk vectors); the rows of up to kPairGroup
+// pairs are loaded together before accumulating.
+//
+// HBM-bound, and mostly by its stores where few tokens have a local pair (y
+// is dense). One pass per wavefront and no loop over tokens keeps the stores
+// in flight close together in memory, and they carry the nontemporal hint (in
+// a loop of 4096 workgroups without it, us): DeepSeek-V3 EP=32 share (32768
+// tokens of 14 KiB, 7872 local pairs) combine 130 -> 72, permute_bwd
+// 127 -> 80; Qwen3 share 21.8 -> 20.3 and 21.4 -> 20.1. Without the hint 122
+// and 102. combine_bwd's stores carry it too (76 -> 65 and 57.6 -> 54.5; the
+// input-gradient GEMM that reads its rows next is no slower); the permute's
+// do not (dispatch the same, the policy update 0.5% slower with it).
 // ---------------------------------------------------------------------------
 template <typename Tin, typename Tout>
 __global__ __launch_bounds__(256) void combine_kernel(const Tin* __restrict__ y_perm, const int32_t* __restrict__ pair_to_row,
                                                       const float* __restrict__ gates, int64_t T, int K, int d,
-                                                      int64_t n_cap, Tout* __restrict__ y) {
+                                                      int64_t n_cap, int nchunk, Tout* __restrict__ y) {
   constexpr int VE = Vec<Tin>::N;
   const int lane = threadIdx.x & 63;
-  const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int64_t nwaves = (int64_t)gridDim.x * 4;
+  const int64_t item = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t t = item / nchunk;
+  if (t >= T) return;
+  const int v0 = (int)(item - t * nchunk) * 64 * kGatherChunk;
   const int nvec = d / VE;
   const uint32_t row_bytes = (uint32_t)d * (uint32_t)sizeof(Tin);
-  for (int64_t t = wave; t < T; t += nwaves) {
-    const TokenPairs tp = token_pairs(pair_to_row, gates, t, K, n_cap);
-    for (int v0 = 0; v0 < nvec; v0 += 64 * kGatherChunk) {
-      float acc[kGatherChunk][VE];
+  const TokenPairs tp = token_pairs(pair_to_row, gates, t, K, n_cap);
+  float acc[kGatherChunk][VE];
 #pragma unroll
-      for (int u = 0; u < kGatherChunk; ++u)
+  for (int u = 0; u < kGatherChunk; ++u)
 #pragma unroll
-        for (int i = 0; i < VE; ++i) acc[u][i] = 0.f;
-      uint64_t m = tp.valid;
-      while (m) {
-        int ks[kPairGroup];
-        int n = 0;
+    for (int i = 0; i < VE; ++i) acc[u][i] = 0.f;
+  uint64_t m = tp.valid;
+  while (m) {
+    int ks[kPairGroup];
+    int n = 0;
 #pragma unroll
-        for (int q = 0; q < kPairGroup; ++q) {
-          ks[q] = m ? __builtin_ctzll(m) : -1;
-          if (m) {
-            m &= m - 1;
-            ++n;
-          }
-        }
-        uint4 raw[kPairGroup][kGatherChunk];
-#pragma unroll
-        for (int q = 0; q < kPairGroup; ++q) {
-          const int row = __builtin_amdgcn_readfirstlane(q < n ? __shfl(tp.row, ks[q], 64) : 0);
-          const RowReader rd(y_perm + (int64_t)row * d, q < n ? row_bytes : 0u);
-#pragma unroll
-          for (int u = 0; u < kGatherChunk; ++u) raw[q][u] = rd.load((uint32_t)((v0 + u * 64 + lane) * 16));
-        }
-#pragma unroll
-        for (int q = 0; q < kPairGroup; ++q) {
-          if (q >= n) break;
-          const float g = __shfl(tp.gate, ks[q], 64);
-#pragma unroll
-          for (int u = 0; u < kGatherChunk; ++u) {
-            float v[VE];
-            Vec<Tin>::widen(raw[q][u], v);
-#pragma unroll
-            for (int i = 0; i < VE; ++i) acc[u][i] += g * v[i];
-          }
-        }
-      }
-      Tout* dst = y + t * d;
-#pragma unroll
-      for (int u = 0; u < kGatherChunk; ++u) {
-        const int vi = v0 + u * 64 + lane;
-        if (vi < nvec) Vec<Tout>::template store<VE>(dst + (int64_t)vi * VE, acc[u]);
+    for (int q = 0; q < kPairGroup; ++q) {
+      ks[q] = m ? __builtin_ctzll(m) : -1;
+      if (m) {
+        m &= m - 1;
+        ++n;
       }
     }
+    uint4 raw[kPairGroup][kGatherChunk];
+#pragma unroll
+    for (int q = 0; q < kPairGroup; ++q) {
+      const int row = __builtin_amdgcn_readfirstlane(q < n ? __shfl(tp.row, ks[q], 64) : 0);
+      const RowReader rd(y_perm + (int64_t)row * d, q < n ? row_bytes : 0u);
+#pragma unroll
+      for (int u = 0; u < kGatherChunk; ++u) raw[q][u] = rd.load((uint32_t)((v0 + u * 64 + lane) * 16));
+    }
+#pragma unroll
+    for (int q = 0; q < kPairGroup; ++q) {
+      if (q >= n) break;
+      const float g = __shfl(tp.gate, ks[q], 64);
+#pragma unroll
+      for (int u = 0; u < kGatherChunk; ++u) {
+        float v[VE];
+        Vec<Tin>::widen(raw[q][u], v);
+#pragma unroll
+        for (int i = 0; i < VE; ++i) acc[u][i] += g * v[i];
+      }
+    }
+  }
+  Tout* dst = y + t * d;
+#pragma unroll
+  for (int u = 0; u < kGatherChunk; ++u) {
+    const int vi = v0 + u * 64 + lane;
+    if (vi < nvec) Vec<Tout>::template store<VE>(dst + (int64_t)vi * VE, acc[u]);
   }
 }
 
@@ -752,6 +772,12 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(const T* __restrict__ 
       }
     }
   }
+}
+
+// Column chunks of a row, one wavefront each.
+int gather_chunks(int d, foremoe_dtype dtype) {
+  const int nvec = d / (dtype == FOREMOE_BF16 ? 8 : 4);
+  return (nvec + 64 * kGatherChunk - 1) / (64 * kGatherChunk);
 }
 
 int gather_grid(int64_t items) {
@@ -988,16 +1014,17 @@ int foremoe_permute(const void* x, foremoe_dtype dtype, int64_t T, int32_t d, co
 static int launch_combine(const void* y_perm, foremoe_dtype in_dtype, const int32_t* pair_to_row, const float* gates,
                           int64_t T, int32_t K, int32_t d, int64_t n_cap, void* y, foremoe_dtype out_dtype,
                           hipStream_t st) {
-  const dim3 grid(gather_grid(T)), block(256);
+  const int nchunk = gather_chunks(d, in_dtype);
+  const dim3 grid((unsigned)((T * nchunk + 3) / 4)), block(256);
   if (in_dtype == FOREMOE_BF16 && out_dtype == FOREMOE_BF16)
     hipLaunchKernelGGL((combine_kernel<uint16_t, uint16_t>), grid, block, 0, st, (const uint16_t*)y_perm, pair_to_row,
-                       gates, T, K, d, n_cap, (uint16_t*)y);
+                       gates, T, K, d, n_cap, nchunk, (uint16_t*)y);
   else if (in_dtype == FOREMOE_BF16 && out_dtype == FOREMOE_F32)
     hipLaunchKernelGGL((combine_kernel<uint16_t, float>), grid, block, 0, st, (const uint16_t*)y_perm, pair_to_row,
-                       gates, T, K, d, n_cap, (float*)y);
+                       gates, T, K, d, n_cap, nchunk, (float*)y);
   else if (in_dtype == FOREMOE_F32 && out_dtype == FOREMOE_F32)
     hipLaunchKernelGGL((combine_kernel<float, float>), grid, block, 0, st, (const float*)y_perm, pair_to_row, gates,
-                       T, K, d, n_cap, (float*)y);
+                       T, K, d, n_cap, nchunk, (float*)y);
   else
     return set_error(FOREMOE_EUNSUPPORTED, "combine: fp32 input with bf16 output is not supported");
   return FOREMOE_OK;

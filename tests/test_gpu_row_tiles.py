@@ -2,7 +2,7 @@
 column tiles), as two launches and as one launch per direction, with and
 without the workspace, against fp64 products of the same bf16 operands.
 
-Tolerance: a bf16 output is within half an ulp (2^-9 relative) of its fp32
+Tolerance: a bf16 output is within half an ulp (2^-8 relative) of its fp32
 sum, which is within gamma = K 2^-24 of the magnitudes' sum (any order); the
 second GEMM of a pair multiplies the first one's rounded rows as the GPU
 wrote them."""
