@@ -10,6 +10,12 @@ libforemoe.so. A micro-step is
   -> combine -> combine_bwd -> down dgrad (+SwiGLU') -> gate/up dgrad
   -> gate/up wgrad, down wgrad -> permute_bwd
 
+where the two forward GEMMs, and the two data-gradient GEMMs, are one launch
+unless one of them is timed by itself or a weight gradient runs beside each
+(8 pipelined micro-steps of the Qwen3 share: 5.27 ms with one launch per
+direction in both, 5.38 with two for the data gradients, 5.62 with two in
+both).
+
 Schedules:
   * one stream: every call in that order;
   * overlap: the two weight-gradient GEMMs run on a second stream (default
@@ -261,17 +267,22 @@ class PolicyUpdate:
 
         def call(phase, st, rc_fn):
             def run():
-                timed = ev is not None and phase in ev
+                t = ev is not None and phase in ev
                 if phase in ROW_GEMMS:
-                    e = (ev[phase][0].cuda_event, ev[phase][1].cuda_event) if timed else (None, None)
+                    e = (ev[phase][0].cuda_event, ev[phase][1].cuda_event) if t else (None, None)
                     _lib.check(rc_fn(st.cuda_stream, *e), phase)
                     return
-                if timed:
+                if t:
                     ev[phase][0].record(st)
                 _lib.check(rc_fn(st.cuda_stream), phase)
-                if timed:
+                if t:
                     ev[phase][1].record(st)
             ops.append((phase, run))
+
+        # the two row GEMMs of a direction run as one launch, unless one of
+        # them is timed by itself
+        def timed(*phases):
+            return ev is not None and any(p in ev for p in phases)
 
         n_dep = [0]
 
@@ -317,10 +328,14 @@ class PolicyUpdate:
         if pipelined and fwd_after_side:  # the previous micro-step's second-stream work ends first
             prev = self.done[(i - 1) % 2]
             ops.append((None, lambda: prev.wait(main)))
-        call("gate_up_fwd", main, lambda q, e0, e1: lib.foremoe_ffn_gate_up_fwd_timed(
-            P["x_perm"], BF16, d, F, S, so, widx, G, gu, n_cap, P["h"], P["au"], rws, rwsz, q, e0, e1))
-        call("down_fwd", main, lambda q, e0, e1: lib.foremoe_ffn_down_fwd_timed(
-            P["h"], BF16, d, F, S, so, widx, G, dn, n_cap, P["y_perm"], rws, rwsz, q, e0, e1))
+        if timed("gate_up_fwd", "down_fwd"):
+            call("gate_up_fwd", main, lambda q, e0, e1: lib.foremoe_ffn_gate_up_fwd_timed(
+                P["x_perm"], BF16, d, F, S, so, widx, G, gu, n_cap, P["h"], P["au"], rws, rwsz, q, e0, e1))
+            call("down_fwd", main, lambda q, e0, e1: lib.foremoe_ffn_down_fwd_timed(
+                P["h"], BF16, d, F, S, so, widx, G, dn, n_cap, P["y_perm"], rws, rwsz, q, e0, e1))
+        else:
+            call("ffn_fwd", main, lambda q: lib.foremoe_grouped_ffn_fwd(
+                P["x_perm"], BF16, d, F, S, so, widx, G, gu, dn, n_cap, P["h"], P["y_perm"], P["au"], rws, rwsz, q))
         if early and next_ms is not None and not (M > 1 and self.wgrad_launches_at(i)):
             # (not after the last micro-step of a group: the group's weight-
             # gradient kernels, launched at its end, hold every CU for a while,
@@ -353,13 +368,18 @@ class PolicyUpdate:
         if overlap and M == 1:
             dep(side, main)
             down_wgrad(side)
-        call("down_dgrad", main, lambda q, e0, e1: lib.foremoe_ffn_down_dgrad_timed(
-            P["dy_perm"], P["au"], BF16, d, F, S, so, widx, G, dn, n_cap, P["d_au"], rws, rwsz, q, e0, e1))
-        if overlap and M == 1:
-            dep(side, main)
-            gate_up_wgrad(side)
-        call("gate_up_dgrad", main, lambda q, e0, e1: lib.foremoe_ffn_gate_up_dgrad_timed(
-            P["d_au"], BF16, d, F, S, so, widx, G, gu, n_cap, P["dx_perm"], rws, rwsz, q, e0, e1))
+        if timed("down_dgrad", "gate_up_dgrad") or (overlap and M == 1):
+            call("down_dgrad", main, lambda q, e0, e1: lib.foremoe_ffn_down_dgrad_timed(
+                P["dy_perm"], P["au"], BF16, d, F, S, so, widx, G, dn, n_cap, P["d_au"], rws, rwsz, q, e0, e1))
+            if overlap and M == 1:
+                dep(side, main)
+                gate_up_wgrad(side)
+            call("gate_up_dgrad", main, lambda q, e0, e1: lib.foremoe_ffn_gate_up_dgrad_timed(
+                P["d_au"], BF16, d, F, S, so, widx, G, gu, n_cap, P["dx_perm"], rws, rwsz, q, e0, e1))
+        else:
+            call("ffn_dgrad", main, lambda q: lib.foremoe_grouped_ffn_dgrad(
+                P["dy_perm"], P["au"], BF16, d, F, S, so, widx, G, gu, dn, n_cap, P["d_au"], P["dx_perm"], rws,
+                rwsz, q))
         if not overlap and M == 1:  # same order as on the side stream: down, then gate/up
             down_wgrad(main)
             gate_up_wgrad(main)
