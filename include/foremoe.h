@@ -126,10 +126,10 @@ typedef struct foremoe_plan {
 #define FOREMOE_WS_INVALID_IDS 0  /* ids outside [-1, E): skipped, written by histogram */
 #define FOREMOE_WS_DROPPED 1      /* local pairs beyond n_cap, written by permute       */
 #define FOREMOE_WS_PLAN_ERRORS 2  /* device-side plan errors, written by assign         */
-/* Word 63 is the arrival ticket of foremoe_histogram_assign; that call's
- * first kernel zeroes it, so a workspace needs no initialisation and a stale
- * ticket (a workspace not zero-filled, an earlier call that did not
- * complete) cannot misfire. */
+/* Words 62 and 63 are an error count and the arrival ticket of
+ * foremoe_histogram_assign; that call's first kernel zeroes them, so a
+ * workspace needs no initialisation and stale values (a workspace not
+ * zero-filled, an earlier call that did not complete) cannot misfire. */
 size_t foremoe_workspace_size(int64_t T, int32_t K, int32_t E);
 
 /*
@@ -181,11 +181,11 @@ int foremoe_assign_replicas(const int32_t* counts, const foremoe_plan* plan,
  * replica split): the same outputs as foremoe_histogram (plan->n_src < 2)
  * or foremoe_histogram_src (plan->n_src >= 2, sources from
  * plan->src_token_begin) into counts [n_src * E], followed by
- * foremoe_assign_replicas with the same plan, workspace and stream. With up
- * to 256 keys this is two launches instead of three: the per-key column
- * scan and the replica split share one, where the last workgroup to finish
- * the scan does the split (a ticket in workspace status word 63, see
- * above). Larger key sets run the three launches. Same argument rules and
+ * foremoe_assign_replicas with the same plan, workspace and stream, in two
+ * launches instead of three: one wavefront per key scans the key's column and
+ * splits it over its replicas, and the last workgroup to finish turns the
+ * slots' counts into offsets (a ticket in workspace status word 63 and an
+ * error count in word 62, see above). Same argument rules and
  * errors as the two calls it replaces.
  */
 int foremoe_histogram_assign(const int32_t* ids, int64_t T, int32_t K, const foremoe_plan* plan,

@@ -12,7 +12,6 @@ namespace foremoe {
 namespace {
 
 constexpr int kWaves = kHistThreads / 64;
-constexpr int kPairsPerWave = kHistChunk / kWaves;
 
 int key_bits(int E) {
   int b = 1;
@@ -75,9 +74,14 @@ __device__ __forceinline__ int pair_key(int v, int64_t p, const KeyMap& km, cons
 // prefix over the groups in pair order gives each group's base, and a
 // pair's rank is its group's base plus the same-key lanes below it.
 // ---------------------------------------------------------------------------
-// ticket (may be NULL): the arrival ticket of the scan+split kernel that
-// follows on the same stream; workgroup 0 zeroes it, so that kernel always
-// starts from a zero ticket whatever the workspace held before.
+// clear (may be empty): what the scan+split kernel that follows on the same
+// stream starts from: workgroup 0 zeroes its arrival ticket and error count
+// and marks every virtual slot as not taken, whatever the workspace held.
+struct SplitClear {
+  uint32_t* ticket;  // ticket[0], and the error count in ticket[-1]; or NULL
+  int32_t* vslot;
+  int n_vslot;
+};
 constexpr int kHistIters = kHistChunk / kHistThreads;
 constexpr int kHistGroups = kHistChunk / 64;
 static_assert(kHistChunk % kHistThreads == 0 && kHistChunk <= 65536, "ranks are uint16 within a block");
@@ -85,11 +89,14 @@ static_assert(kHistChunk % kHistThreads == 0 && kHistChunk <= 65536, "ranks are 
 __global__ __launch_bounds__(kHistThreads) void hist_count_kernel(const int32_t* __restrict__ ids, int64_t npairs,
                                                                   KeyMap km, int E, int nbits,
                                                                   int32_t* __restrict__ partial,
-                                                                  uint16_t* __restrict__ rank, uint32_t* ticket) {
+                                                                  uint16_t* __restrict__ rank, SplitClear clear) {
   __shared__ int s_g[kHistGroups][FOREMOE_MAX_EXPERTS + 1];
   __shared__ int s_tb[FOREMOE_MAX_SOURCES + 1];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  if (ticket && blockIdx.x == 0 && tid == 0) atomicExch(ticket, 0u);
+  if (clear.ticket && blockIdx.x == 0) {
+    if (tid < 2) atomicExch(clear.ticket - tid, 0u);
+    for (int i = tid; i < clear.n_vslot; i += kHistThreads) clear.vslot[i] = -1;
+  }
   for (int i = tid; i < kHistGroups * (E + 1); i += kHistThreads) s_g[i / (E + 1)][i % (E + 1)] = 0;
   load_sources(km, s_tb);
   __syncthreads();
@@ -204,7 +211,6 @@ __device__ __forceinline__ int clamp_nrep(const PlanDev& P, int e, int& err) {
 // the kernel costs a few memory round trips.
 // Two sizes: up to 256 keys with 256 threads (small LDS, quick to launch)
 // and up to FOREMOE_MAX_EXPERTS keys with 1024 threads.
-// `counts` may point to global memory or to LDS.
 template <int kAssignThreads, int MAXK>
 __device__ __forceinline__ void assign_block(const int32_t* counts, const PlanDev& P, int32_t* __restrict__ rep_begin,
                                              int32_t* __restrict__ slot_count, int32_t* __restrict__ slot_offset,
@@ -323,77 +329,152 @@ __global__ __launch_bounds__(kAssignThreads) void assign_kernel(const int32_t* _
 }
 
 // ---------------------------------------------------------------------------
-// Step 1b and step 2 in one launch (up to 256 keys): one workgroup per key
-// column turns the per-block counts into block bases and the key's total,
-// as hist_scan_kernel does; the last workgroup to finish (a ticket in the
-// workspace header) then splits the keys over the replicas, as
-// assign_kernel does. Workgroups may run on different XCDs, whose L2
-// caches are not coherent with each other: the totals are stored and loaded
-// with device scope (SC1 cache policy: written through, never read from a
-// stale line), and each workgroup's total has reached memory before it
-// takes its ticket (its block bases, read only by later kernels, are stored
-// after). No workgroup waits for another. The ticket is zero on entry: the
-// count kernel before it on the same stream has zeroed it.
+// Step 1b and step 2 in one launch: one wavefront per key adds up the key's
+// per-block counts, splits them over its replicas as assign_kernel does, and
+// leaves the counts of the virtual slots that hold them in vslot_offset; the
+// last workgroup to finish (a ticket in the workspace header) turns those
+// into offsets. Workgroups may run on different XCDs, whose L2 caches are not
+// coherent with each other: slot counts and the error count are stored and
+// loaded with device scope, and have reached memory before their workgroup
+// takes its ticket; the block bases, read only by later kernels, are stored
+// after. No workgroup waits for another.
+//
+// Latency-bound: a launch is about four dependent round trips to memory.
+// With the whole split in the last workgroup, from the counts of all keys, it
+// was slower, and above 256 keys its tables did not fit beside the scan, so
+// that those ran three kernels. Steps 1-3 (us, before -> now): 16384 x 8 ids, 128
+// keys 38.8 -> 37.8; 1024 keys (8 sources) 54.0 -> 48.6.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kHistThreads) void hist_scan_assign_kernel(
+__global__ __launch_bounds__(kHistThreads) void hist_scan_split_kernel(
     int32_t* __restrict__ partial, int64_t nblocks, int nkeys, int32_t* __restrict__ counts, uint32_t* ticket,
     PlanDev P, int32_t* __restrict__ rep_begin, int32_t* __restrict__ slot_count, int32_t* __restrict__ slot_offset,
-    int32_t* __restrict__ vslot_offset, int32_t* __restrict__ rep_slot, int32_t* __restrict__ status) {
+    int32_t* vslot_offset, int32_t* __restrict__ rep_slot, int32_t* __restrict__ status) {
+  constexpr int kHeld = 4;  // chunks of 64 blocks whose counts stay in registers
+  __shared__ int s_rs[kWaves][FOREMOE_MAX_REPLICAS];
   __shared__ int s_tmp[kWaves];
-  __shared__ int s_cnt[257];
+  __shared__ int s_off[FOREMOE_MAX_SLOTS + 1];
   __shared__ int s_last;
-  // the plan's tables (at most 256 keys here), loaded by every workgroup
-  // beside its column so that the last one finds them in LDS
-  __shared__ int s_nrep[256];
-  __shared__ int s_w[256 * FOREMOE_MAX_REPLICAS];
-  __shared__ int s_se[FOREMOE_MAX_SLOTS];
-  __shared__ int s_sr[FOREMOE_MAX_SLOTS];
-  const int e = blockIdx.x, tid = threadIdx.x;
-  const int v_first = tid < nblocks ? partial[(int64_t)tid * (nkeys + 1) + e] : 0;
-  const int32_t* wsrc = P.src_rep_weight ? P.src_rep_weight : P.expert_rep_weight;
-  const int nw = P.src_rep_weight ? nkeys * P.R_max : (P.expert_rep_weight ? P.E * P.R_max : 0);
-  for (int i = tid; i < P.E; i += kHistThreads) s_nrep[i] = P.expert_nrep[i];
-  for (int i = tid; i < nw; i += kHistThreads) s_w[i] = wsrc[i];
-  for (int i = tid; i < P.S; i += kHistThreads) {
-    s_se[i] = P.slot_expert[i];
-    s_sr[i] = P.slot_replica[i];
-  }
-  // one chunk of blocks (the usual case): the block bases are stored after
-  // the ticket, so that taking it waits only for the total's store
-  const bool defer = nblocks <= kHistThreads;
-  int base_first = 0;
-  int carry = 0;
-  for (int64_t b0 = 0; b0 < nblocks; b0 += kHistThreads) {
-    const int64_t b = b0 + tid;
-    const int v = b0 == 0 ? v_first : (b < nblocks ? partial[b * (nkeys + 1) + e] : 0);
-    int total;
-    const int incl = block_inclusive_scan(v, s_tmp, total);
-    if (b < nblocks) {
-      if (defer) base_first = carry + incl - v;
-      else partial[b * (nkeys + 1) + e] = carry + incl - v;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int e = blockIdx.x * kWaves + w, NS = P.n_src * P.S;
+  int32_t* col = partial + e;
+  const int64_t ld = nkeys + 1;
+  int v[kHeld];
+  if (e <= nkeys) {
+#pragma unroll
+    for (int c = 0; c < kHeld; ++c) {
+      const int64_t b = c * 64 + lane;
+      v[c] = b < nblocks ? col[b * ld] : 0;
     }
+  }
+  if (e < nkeys) {
+    const int src = e / P.E, ex = e - src * P.E, RS = P.R_max + 1;
+    int err = 0;
+    int R = P.expert_nrep[ex];
+    if (R < 1 || R > P.R_max) {
+      err = src == 0;  // once per expert
+      R = 1;
+    }
+    const int32_t* wt = P.src_rep_weight ? P.src_rep_weight + (int64_t)e * P.R_max
+                                          : (P.expert_rep_weight ? P.expert_rep_weight + (int64_t)ex * P.R_max : nullptr);
+    const int wv = lane < R ? (wt ? wt[lane] : 1) : 0;
+    // the (virtual) slot of each replica; with duplicates the lowest wins
+    if (lane < FOREMOE_MAX_REPLICAS) s_rs[w][lane] = INT_MAX;
+    for (int j = lane; j < P.S; j += 64) {
+      const int se = P.slot_expert[j], r = P.slot_replica[j];
+      if (se == ex && r >= 0 && r < P.R_max) atomicMin(&s_rs[w][r], j * P.n_src + src);
+    }
+    int n = 0;
+#pragma unroll
+    for (int c = 0; c < kHeld; ++c) n += v[c];
+    for (int64_t b = kHeld * 64 + lane; b < nblocks; b += 64) n += col[b * ld];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o, 64);
+    long long incl = wv;  // weights up to and including this replica
+#pragma unroll
+    for (int o = 1; o < FOREMOE_MAX_REPLICAS; o <<= 1) {
+      const long long t = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += t;
+    }
+    const long long total = __shfl(incl, FOREMOE_MAX_REPLICAS - 1, 64);
+    // all-zero per-source weights are fine for an empty block
+    const bool bad = __ballot(wv < 0) != 0 || (total <= 0 && (n > 0 || !P.src_rep_weight));
+    err += bad;
+    const bool eq = bad || total <= 0;
+    const int hi = lane < R ? (int)(((long long)n * (eq ? lane + 1 : incl)) / (eq ? (long long)R : total)) : n;
+    const int up = __shfl_up(hi, 1, 64), lo = lane == 0 ? 0 : up;
+    const int jj = lane < P.R_max ? s_rs[w][lane] : INT_MAX;
+    const bool held = lane < R && jj != INT_MAX;  // else the replica is remote
+    if (held) __hip_atomic_store(vslot_offset + jj, hi - lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0 && err) atomicAdd(ticket - 1, (uint32_t)err);
+    if (lane == 0) {
+      counts[e] = n;
+      rep_begin[(int64_t)e * RS] = 0;
+    }
+    if (lane < P.R_max) {
+      rep_begin[(int64_t)e * RS + 1 + lane] = hi;
+      rep_slot[e * P.R_max + lane] = held ? jj : -1;
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's slot counts have reached memory
+  __syncthreads();
+  if (tid == 0) s_last = atomicAdd(ticket, 1u) == gridDim.x - 1;
+  // exclusive block bases of the key
+  if (e <= nkeys) {
+    int carry = 0;
+    auto scan = [&](int64_t b, int c) {
+      int incl = c;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += t;
+      }
+      if (b < nblocks) col[b * ld] = carry + incl - c;
+      carry += __shfl(incl, 63, 64);
+    };
+#pragma unroll
+    for (int c = 0; c < kHeld; ++c)
+      if (c * 64 < nblocks) scan(c * 64 + lane, v[c]);
+    for (int64_t b0 = kHeld * 64; b0 < nblocks; b0 += 64) {
+      const int64_t b = b0 + lane;
+      scan(b, b < nblocks ? col[b * ld] : 0);
+    }
+    if (e == nkeys && lane == 0) status[FOREMOE_WS_INVALID_IDS] = carry;
+  }
+  __syncthreads();
+  if (!s_last) return;
+  // the last workgroup: slot counts to offsets
+  int err = 0, carry = 0;
+  for (int j0 = 0; j0 < NS; j0 += kHistThreads) {
+    const int jj = j0 + tid;
+    int c = 0;
+    if (jj < NS) {
+      c = __hip_atomic_load(vslot_offset + jj, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (c < 0) {  // no key took it: a bad slot, counted once
+        err += jj % P.n_src == 0;
+        c = 0;
+      }
+    }
+    int total;
+    const int incl = block_inclusive_scan(c, s_tmp, total);
+    if (jj < NS) s_off[jj] = carry + incl - c;
     carry += total;
   }
-  if (tid == 0) {
-    if (e < nkeys) __hip_atomic_store(counts + e, carry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else status[FOREMOE_WS_INVALID_IDS] = carry;
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the total has reached memory
-    s_last = atomicAdd(ticket, 1u) == gridDim.x - 1;
+  if (tid == 0) s_off[NS] = carry;
+  if (err) atomicAdd(ticket - 1, (uint32_t)err);
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  __syncthreads();
+  for (int jj = tid; jj <= NS; jj += kHistThreads) vslot_offset[jj] = s_off[jj];
+  for (int j = tid; j < P.S; j += kHistThreads) {
+    slot_count[j] = s_off[(j + 1) * P.n_src] - s_off[j * P.n_src];
+    slot_offset[j] = s_off[j * P.n_src];
   }
-  __syncthreads();
-  if (defer && tid < nblocks) partial[(int64_t)tid * (nkeys + 1) + e] = base_first;
-  if (!s_last) return;
-  for (int k = tid; k < nkeys; k += kHistThreads)
-    s_cnt[k] = __hip_atomic_load(counts + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __syncthreads();
-  PlanDev L = P;
-  L.expert_nrep = s_nrep;
-  L.slot_expert = s_se;
-  L.slot_replica = s_sr;
-  if (P.src_rep_weight) L.src_rep_weight = s_w;
-  else if (P.expert_rep_weight) L.expert_rep_weight = s_w;
-  assign_block<kHistThreads, 256>(s_cnt, L, rep_begin, slot_count, slot_offset, vslot_offset, rep_slot, status);
-  if (tid == 0) atomicExch(ticket, 0u);  // ready for the next call
+  if (tid == 0) {
+    slot_offset[P.S] = carry;
+    status[FOREMOE_WS_PLAN_ERRORS] =
+        (int32_t)__hip_atomic_load(ticket - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    atomicExch(ticket, 0u);
+    atomicExch(ticket - 1, 0u);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -826,7 +907,7 @@ static int histogram_common(const char* who, const int32_t* ids, int64_t T, int3
   int32_t* partial = (int32_t*)((char*)ws + kWsPartialOff);
   uint16_t* rank = (uint16_t*)((char*)ws + ws_rank_off(T, K, E));
   hipLaunchKernelGGL(hist_count_kernel, dim3((unsigned)nb), dim3(kHistThreads), 0, st, ids, npairs, km, E,
-                     key_bits(E), partial, rank, (uint32_t*)nullptr);
+                     key_bits(E), partial, rank, SplitClear{nullptr, nullptr, 0});
   hipLaunchKernelGGL(hist_scan_kernel, dim3(E + 1), dim3(kHistThreads), 0, st, partial, nb, E, counts, status);
   return check_launch(who);
 }
@@ -906,11 +987,6 @@ static int histogram_assign_impl(const int32_t* ids, int64_t T, int32_t K, const
   const PlanDev P = plan_dev(plan);
   const int nkeys = P.n_src * P.E;
   const KeyMap km{P.E, P.n_src, K, P.n_src >= 2 ? plan->src_token_begin : nullptr};
-  if (nkeys > 256) {  // large key sets: the three separate launches
-    rc = histogram_common("foremoe_histogram_assign", ids, T, K, nkeys, km, counts, ws, ws_bytes, status, stream);
-    if (rc) return rc;
-    return assign_impl(counts, plan, rep_begin, slot_count, slot_offset, ws, ws_bytes, status, stream);
-  }
   rc = check_hist("foremoe_histogram_assign", ids, T, K, nkeys, counts, ws, ws_bytes);
   if (rc) return rc;
   hipStream_t st = (hipStream_t)stream;
@@ -919,11 +995,12 @@ static int histogram_assign_impl(const int32_t* ids, int64_t T, int32_t K, const
   int32_t* partial = (int32_t*)((char*)ws + kWsPartialOff);
   uint16_t* rank = (uint16_t*)((char*)ws + ws_rank_off(T, K, nkeys));
   uint32_t* ticket = (uint32_t*)ws + kWsTicketWord;
+  int32_t* vslot = (int32_t*)((char*)ws + kWsVSlotOff);
   hipLaunchKernelGGL(hist_count_kernel, dim3((unsigned)nb), dim3(kHistThreads), 0, st, ids, npairs, km, nkeys,
-                     key_bits(nkeys), partial, rank, ticket);
-  hipLaunchKernelGGL(hist_scan_assign_kernel, dim3(nkeys + 1), dim3(kHistThreads), 0, st, partial, nb, nkeys, counts,
-                     ticket, P, rep_begin, slot_count, slot_offset,
-                     (int32_t*)((char*)ws + kWsVSlotOff), (int32_t*)((char*)ws + kWsRepSlotOff), status);
+                     key_bits(nkeys), partial, rank, SplitClear{ticket, vslot, P.n_src * P.S});
+  hipLaunchKernelGGL(hist_scan_split_kernel, dim3(nkeys / kWaves + 1), dim3(kHistThreads), 0, st, partial, nb, nkeys,
+                     counts, ticket, P, rep_begin, slot_count, slot_offset, vslot,
+                     (int32_t*)((char*)ws + kWsRepSlotOff), status);
   return check_launch("foremoe_histogram_assign");
 }
 

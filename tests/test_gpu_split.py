@@ -1,0 +1,66 @@
+"""foremoe_histogram_assign (counts, replica split and offsets in two
+launches) against foremoe_histogram(_src) and foremoe_assign_replicas, bit
+for bit, over key counts around a workgroup's four keys and the 256 and 1024
+limits, more blocks than stay in registers, and faulty plans."""
+import numpy as np
+import pytest
+import torch
+
+
+def _plan(rng, E, S, R_max, n_src, T, gpu, faulty, weights):
+    from paper_2606_11867_amd import api
+    i32 = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.int32)).to(gpu)  # noqa: E731
+    nrep = rng.integers(1, R_max + 1, E)
+    se = rng.integers(0, E, S)
+    sr = np.array([rng.integers(0, nrep[e]) for e in se]) if S else np.zeros(0, int)
+    w = rng.integers(0, 4, (n_src if weights == "src" else 1, E, R_max)) + (0 if faulty else 1)
+    if faulty and S:
+        nrep[rng.integers(0, E)] = R_max + 1
+        nrep[rng.integers(0, E)] = 0
+        se[0], sr[-1] = -1, R_max
+        w[0, rng.integers(0, E)] = -1
+    tb = np.sort(rng.integers(0, T + 1, n_src + 1))
+    tb[0], tb[-1] = 0, T
+    return api.DevicePlan(E=E, S=S, R_max=R_max, W=1, G=1, slot_expert=i32(se), slot_replica=i32(sr),
+                          expert_nrep=i32(nrep), expert_rep_weight=i32(w[0]) if weights == "expert" else None,
+                          slot_widx=i32(np.zeros(S)), slot_gidx=i32(np.zeros(S)), n_src=n_src,
+                          src_token_begin=i32(tb) if n_src > 1 else None,
+                          src_rep_weight=i32(w) if weights == "src" and n_src > 1 else None)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("faulty", [False, True])
+@pytest.mark.parametrize("E,n_src,S,R_max,T,K,weights", [
+    (1, 1, 1, 1, 3, 1, "none"), (3, 1, 5, 2, 100, 2, "expert"), (4, 1, 0, 16, 64, 3, "none"),
+    (5, 1, 300, 16, 700, 5, "expert"), (255, 1, 40, 4, 5000, 8, "expert"), (256, 1, 1024, 2, 1000, 8, "none"),
+    (257, 1, 30, 3, 2000, 8, "expert"), (1024, 1, 64, 16, 40000, 4, "expert"), (128, 8, 24, 8, 20001, 8, "src"),
+    (16, 64, 16, 2, 4000, 8, "src"), (7, 3, 11, 5, 333, 2, "expert")])
+def test_histogram_assign_matches_separate_calls(gpu, E, n_src, S, R_max, T, K, weights, faulty):
+    from paper_2606_11867_amd import api
+    print(f"\n[case] split E={E} n_src={n_src} S={S} R_max={R_max} T={T} K={K} {weights} faulty={faulty}", flush=True)
+    rng = np.random.default_rng(E * 10 + n_src + faulty)
+    plan = _plan(rng, E, S, R_max, n_src, T, gpu, faulty, weights)
+    ids = rng.integers(-1, E + (1 if faulty else 0), (T, K)).astype(np.int32)
+    ids = torch.from_numpy(ids).to(gpu)
+    ws1, ws2 = (api.workspace(T, K, E * n_src, gpu) for _ in range(2))
+    ws2.fill_(0xA5)  # whatever the workspace held before
+    if n_src > 1:
+        counts = api.histogram_src(ids, E, plan.src_token_begin, ws1)
+    else:
+        counts = api.histogram(ids, E, ws1)
+    want = (counts.reshape(-1), *api.assign_replicas(counts, plan, ws1))
+    for _ in range(2):
+        got = api.histogram_assign(ids, plan, ws2)
+        torch.cuda.synchronize()
+        for name, a, b in zip(("counts", "rep_begin", "slot_count", "slot_offset"), got, want):
+            assert torch.equal(a, b), name
+        st = [w[:256].view(torch.int32).cpu().numpy() for w in (ws1, ws2)]
+        assert st[0][0] == st[1][0] and st[0][2] == st[1][2], "invalid ids or plan errors"
+    # what the permute goes on with: replica slots, virtual slot offsets, block bases
+    n_rs, nb = E * n_src * R_max, -(-T * K // 512)
+    i1, i2 = (w.view(torch.int32) for w in (ws1, ws2))
+    assert torch.equal(i1[64:64 + n_rs], i2[64:64 + n_rs])
+    v0 = 64 + 1024 * 16
+    assert torch.equal(i1[v0:v0 + S * n_src + 1], i2[v0:v0 + S * n_src + 1])
+    p0 = v0 + 1088  # 1025 offsets, padded to 256 bytes
+    assert torch.equal(i1[p0:p0 + nb * (E * n_src + 1)], i2[p0:p0 + nb * (E * n_src + 1)])
