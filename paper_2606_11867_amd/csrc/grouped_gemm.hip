@@ -69,9 +69,12 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 enum Epi { kEpiStore = 0, kEpiSwigluFwd = 1, kEpiSwigluBwd = 2 };
 
-// 1 / (1 + exp(-a)), by the hardware reciprocal (within 1 ulp in fp32; the
-// results are rounded to bf16).
-__device__ __forceinline__ float sigmoid_f(float a) { return __builtin_amdgcn_rcpf(1.0f + __expf(-a)); }
+// Correctly rounded fp32 divisions. The hardware reciprocal would be a few
+// instructions cheaper, but it is 1 ulp off and flushes subnormal results:
+// for a below -87.3 SiLU and its gradient, numbers near 1e-37 in bf16, would
+// become 0.
+__device__ __forceinline__ float silu_f(float a) { return a / (1.0f + __expf(-a)); }
+__device__ __forceinline__ float sigmoid_f(float a) { return 1.0f / (1.0f + __expf(-a)); }
 
 __device__ __forceinline__ int lane64() { return threadIdx.x & 63; }
 // The same, recomputed where it stands: a kernel with several tile shapes in
@@ -828,7 +831,7 @@ __device__ __forceinline__ void rows_epilogue(const RowsArgs& a, const CoreT& co
           for (int e = 0; e < 4; ++e) {
             av[e] = core.acc[i][jj][g * 4 + e];
             uv[e] = core.acc[i][jj + H][g * 4 + e];
-            hv[e] = av[e] * sigmoid_f(av[e]) * uv[e];
+            hv[e] = silu_f(av[e]) * uv[e];
           }
           SR::put4(sh, l32, col, hv[0], hv[1], hv[2], hv[3]);
           SR::put4(sa, l32, col, av[0], av[1], av[2], av[3]);
