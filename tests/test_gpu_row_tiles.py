@@ -136,3 +136,29 @@ def test_row_tiles_rows_off_the_line(gpu):
     """Handed-over rows that do not start on a 128-byte line: two launches."""
     print("\n[case] row tiles, rows 16 bytes off the line", flush=True)
     _check(gpu, [300, 70, 30], 256, 128, 2, True, misalign=8)
+
+
+@pytest.mark.gpu
+def test_round_of_halves_and_small_tiles_is_not_cut_along_k(gpu):
+    """One round of 256-row tiles (in halves) and of smaller ones that would
+    be more than 7/8 of the CUs as halves throughout: no K pieces, so the
+    workspace changes no bit."""
+    from paper_2606_11867_amd import api
+    rows, d, F = [300, 40, 26, 17, 200, 64, 1, 90, 5], 2048, 768  # 60 tiles of the gate/up product, 12 of 256 rows
+    if torch.cuda.get_device_properties(gpu).multi_processor_count != 256:
+        pytest.skip("the layout is worked out for 256 CUs")
+    print(f"\n[case] mixed round, rows {rows}, d={d}, F={F}", flush=True)
+    g = torch.Generator(device=gpu).manual_seed(3)
+    bf = lambda *s, scale=1.0: torch.randn(*s, generator=g, device=gpu).mul_(scale).bfloat16()  # noqa: E731
+    W, N = len(rows), sum(rows)
+    x, dy = bf(N, d), bf(N, d)
+    gu, dn = bf(W, 2 * F, d, scale=d ** -0.5), bf(W, d, F, scale=F ** -0.5)
+    off = torch.tensor([0] + list(np.cumsum(rows)), dtype=torch.int32, device=gpu)
+    widx = torch.arange(W, dtype=torch.int32, device=gpu)
+    runs = []
+    for ws in (api.ffn_workspace(gpu), None):
+        h, y, au = api.grouped_ffn_fwd(x, off, widx, gu, dn, ws=ws)
+        runs.append((h, y, au))
+    torch.cuda.synchronize()
+    for name, a, b in zip(("H", "Y", "A|U"), *runs):
+        assert torch.equal(a, b), name
