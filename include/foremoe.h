@@ -282,7 +282,10 @@ int foremoe_dispatch_static(const int32_t* ids, int64_t T, int32_t K, const fore
  * the fp32 summation order.
  * Calls that share a workspace
  * must not overlap in time (same stream, or ordered by events); after a
- * call that did not complete, zero the workspace again. Too small or
+ * call that did not complete, zero the workspace again. A call whose
+ * workspace was not zero, or was shared by an overlapping call, gives wrong
+ * rows; a call of both products may moreover take some seconds, until it
+ * gives up waiting for rows that are not coming. Too small or
  * misaligned: FOREMOE_EINVAL, nothing launched. Ignored for f32.
  */
 size_t foremoe_ffn_workspace_size(void);

@@ -1208,11 +1208,15 @@ __device__ __forceinline__ void store_agent(unsigned* p, unsigned v) {
 constexpr int kFinished = 2 * kQueues;       // queue word: workgroups finished
 constexpr int kDoneTotal = 2 * kQueues + 1;  // queue word: halves done
 constexpr int kQueueWords = 2 * kQueues + 2;
+// Looks at the counters before a wait is given up: seconds, against the
+// milliseconds of the longest unit. Looks are counted, not time, so that a
+// process that is not running does not run out of it.
+constexpr int kMaxPolls = 1 << 23;
 
 struct HandOver {
   int tile;       // row tile of the unit whose count is pending, or -1
   unsigned count;
-  bool all_done;  // every tile of the first GEMM is known to be done (thread 0)
+  bool all_done;  // no wait is needed any more: every tile of the first GEMM is done (thread 0)
 };
 
 __device__ __forceinline__ void count_done(const FfnArgs& fa, HandOver& ho) {
@@ -1258,13 +1262,16 @@ __device__ __forceinline__ void run_unit(const FfnArgs& fa, const PhaseUnits& u,
   if (PH == 1 && pair) {
     // Every unit of the first GEMM has been taken by a running workgroup
     // (units of the second are only handed out after that), those never
-    // wait, and this one's pending count is done first: the wait ends.
+    // wait, and this one's pending count is done first: the rows come, within
+    // the time of one unit. They do not if the counters were not zero when
+    // the call began, or another call changes them meanwhile: after
+    // kMaxPolls looks the workgroup goes on, and waits no more.
     flush_done(fa, ho);
     if (threadIdx.x == 0 && !ho.all_done) {
       const unsigned* done = fa.row_done + (r.mt < kMaxRowTiles ? r.mt : kMaxRowTiles - 1);
-      for (;;) {
+      for (int polls = 0;; ++polls) {
         const unsigned here = load_agent(done), all = load_agent(&fa.queue[kDoneTotal * kQueueStride]);
-        ho.all_done = all >= done_all;
+        ho.all_done = all >= done_all || polls == kMaxPolls;
         if (ho.all_done || here >= done_tile) break;
         __builtin_amdgcn_s_sleep(16);  // about half a microsecond
       }
@@ -1468,7 +1475,7 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(FfnArgs fa) {
   auto publish = [&]() __attribute__((always_inline)) {
     const int k = __builtin_amdgcn_readfirstlane(s_claim);
     const int total = ph == 0 ? u0.total : u1.total;
-    if (k >= Q.length(total, x)) {
+    if ((unsigned)k >= (unsigned)Q.length(total, x)) {  // (unsigned: whatever a counter held)
       if (tid == 0) s_unit.ph = pair ? kElsewhere : kNone;
       return;
     }
@@ -1484,14 +1491,14 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(FfnArgs fa) {
     const int qp = (lane >> 3) & 1, qx = ((lane & 7) + x0) % kQueues;
     const int len = lane < 2 * kQueues && qx < nq ? Q.length(qp == 0 ? u0.total : u1.total, qx) : 0;
     unsigned* c = &fa.queue[(qp * kQueues + qx) * kQueueStride];
-    bool open = lane < 2 * kQueues && (int)load_agent(c) < len;
+    bool open = lane < 2 * kQueues && load_agent(c) < (unsigned)len;
     int got = 0;
     uint64_t found;
     while ((found = __ballot(open)) != 0) {
       const int from = __builtin_ctzll(found);
       if (lane == from) {
         got = (int)atomicAdd(c, 1u);
-        open = got < len;
+        open = (unsigned)got < (unsigned)len;
       }
       if ((__ballot(open) >> from) & 1) {
         ph = from >> 3;

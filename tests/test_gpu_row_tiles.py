@@ -162,3 +162,30 @@ def test_round_of_halves_and_small_tiles_is_not_cut_along_k(gpu):
     torch.cuda.synchronize()
     for name, a, b in zip(("H", "Y", "A|U"), *runs):
         assert torch.equal(a, b), name
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("left_over", [1000, 2 ** 32 - 16])
+def test_counters_that_were_not_zero(gpu, left_over):
+    """A queue counter that another call left behind: the launch of both
+    products ends (its waits are bounded, and no counter value is taken for a
+    unit), leaves every counter at zero, and the next call is right again."""
+    from paper_2606_11867_amd import api
+    d, F, rows = 512, 256, [700, 40, 300]
+    print(f"\n[case] queue counter at {left_over}, rows {rows}", flush=True)
+    g = torch.Generator(device=gpu).manual_seed(5)
+    bf = lambda *s: torch.randn(*s, generator=g, device=gpu).mul_(0.05).bfloat16()  # noqa: E731
+    x, gu, dn = bf(sum(rows), d), bf(3, 2 * F, d), bf(3, d, F)
+    off = torch.tensor([0] + list(np.cumsum(rows)), dtype=torch.int32, device=gpu)
+    widx = torch.arange(3, dtype=torch.int32, device=gpu)
+    ws = api.ffn_workspace(gpu)
+    want = api.grouped_ffn_fwd(x, off, widx, gu, dn, ws=ws)
+    counters = ws[:65536].view(torch.int32)
+    counters[1024] = left_over if left_over < 2 ** 31 else left_over - 2 ** 32  # first product, first queue
+    api.grouped_ffn_fwd(x, off, widx, gu, dn, ws=ws)
+    torch.cuda.synchronize()
+    assert not bool(counters.any()), "counters not back at zero"
+    got = api.grouped_ffn_fwd(x, off, widx, gu, dn, ws=ws)
+    torch.cuda.synchronize()
+    for name, a, b in zip(("H", "Y", "A|U"), got, want):
+        assert torch.equal(a, b), name
