@@ -701,8 +701,8 @@ __device__ __forceinline__ TokenPairs token_pairs(const int32_t* __restrict__ pa
 // pairs are loaded together before accumulating.
 //
 // HBM-bound, and mostly by its stores where few tokens have a local pair (y
-// is dense). One pass per wavefront and no loop over tokens keeps the stores
-// in flight close together in memory, and they carry the nontemporal hint (in
+// is dense). One item per wavefront (combine_grid) keeps the stores in
+// flight close together in memory, and they carry the nontemporal hint (in
 // a loop of 4096 workgroups without it, us): DeepSeek-V3 EP=32 share (32768
 // tokens of 14 KiB, 7872 local pairs) combine 130 -> 72, permute_bwd
 // 127 -> 80; Qwen3 share 21.8 -> 20.3 and 21.4 -> 20.1. Without the hint 122
@@ -716,56 +716,58 @@ __global__ __launch_bounds__(256) void combine_kernel(const Tin* __restrict__ y_
                                                       int64_t n_cap, int nchunk, Tout* __restrict__ y) {
   constexpr int VE = Vec<Tin>::N;
   const int lane = threadIdx.x & 63;
-  const int64_t item = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t t = item / nchunk;
-  if (t >= T) return;
-  const int v0 = (int)(item - t * nchunk) * 64 * kGatherChunk;
   const int nvec = d / VE;
   const uint32_t row_bytes = (uint32_t)d * (uint32_t)sizeof(Tin);
-  const TokenPairs tp = token_pairs(pair_to_row, gates, t, K, n_cap);
-  float acc[kGatherChunk][VE];
+  const int64_t items = T * nchunk, stride = (int64_t)gridDim.x * 4;
+  for (int64_t item = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); item < items;
+       item += stride) {
+    const int64_t t = nchunk == 1 ? item : item / nchunk;
+    const int v0 = (int)(item - t * nchunk) * 64 * kGatherChunk;
+    const TokenPairs tp = token_pairs(pair_to_row, gates, t, K, n_cap);
+    float acc[kGatherChunk][VE];
 #pragma unroll
-  for (int u = 0; u < kGatherChunk; ++u)
+    for (int u = 0; u < kGatherChunk; ++u)
 #pragma unroll
-    for (int i = 0; i < VE; ++i) acc[u][i] = 0.f;
-  uint64_t m = tp.valid;
-  while (m) {
-    int ks[kPairGroup];
-    int n = 0;
+      for (int i = 0; i < VE; ++i) acc[u][i] = 0.f;
+    uint64_t m = tp.valid;
+    while (m) {
+      int ks[kPairGroup];
+      int n = 0;
 #pragma unroll
-    for (int q = 0; q < kPairGroup; ++q) {
-      ks[q] = m ? __builtin_ctzll(m) : -1;
-      if (m) {
-        m &= m - 1;
-        ++n;
+      for (int q = 0; q < kPairGroup; ++q) {
+        ks[q] = m ? __builtin_ctzll(m) : -1;
+        if (m) {
+          m &= m - 1;
+          ++n;
+        }
+      }
+      uint4 raw[kPairGroup][kGatherChunk];
+#pragma unroll
+      for (int q = 0; q < kPairGroup; ++q) {
+        const int row = __builtin_amdgcn_readfirstlane(q < n ? __shfl(tp.row, ks[q], 64) : 0);
+        const RowReader rd(y_perm + (int64_t)row * d, q < n ? row_bytes : 0u);
+#pragma unroll
+        for (int u = 0; u < kGatherChunk; ++u) raw[q][u] = rd.load((uint32_t)((v0 + u * 64 + lane) * 16));
+      }
+#pragma unroll
+      for (int q = 0; q < kPairGroup; ++q) {
+        if (q >= n) break;
+        const float g = __shfl(tp.gate, ks[q], 64);
+#pragma unroll
+        for (int u = 0; u < kGatherChunk; ++u) {
+          float v[VE];
+          Vec<Tin>::widen(raw[q][u], v);
+#pragma unroll
+          for (int i = 0; i < VE; ++i) acc[u][i] += g * v[i];
+        }
       }
     }
-    uint4 raw[kPairGroup][kGatherChunk];
+    Tout* dst = y + t * d;
 #pragma unroll
-    for (int q = 0; q < kPairGroup; ++q) {
-      const int row = __builtin_amdgcn_readfirstlane(q < n ? __shfl(tp.row, ks[q], 64) : 0);
-      const RowReader rd(y_perm + (int64_t)row * d, q < n ? row_bytes : 0u);
-#pragma unroll
-      for (int u = 0; u < kGatherChunk; ++u) raw[q][u] = rd.load((uint32_t)((v0 + u * 64 + lane) * 16));
+    for (int u = 0; u < kGatherChunk; ++u) {
+      const int vi = v0 + u * 64 + lane;
+      if (vi < nvec) Vec<Tout>::template store<VE>(dst + (int64_t)vi * VE, acc[u]);
     }
-#pragma unroll
-    for (int q = 0; q < kPairGroup; ++q) {
-      if (q >= n) break;
-      const float g = __shfl(tp.gate, ks[q], 64);
-#pragma unroll
-      for (int u = 0; u < kGatherChunk; ++u) {
-        float v[VE];
-        Vec<Tin>::widen(raw[q][u], v);
-#pragma unroll
-        for (int i = 0; i < VE; ++i) acc[u][i] += g * v[i];
-      }
-    }
-  }
-  Tout* dst = y + t * d;
-#pragma unroll
-  for (int u = 0; u < kGatherChunk; ++u) {
-    const int vi = v0 + u * 64 + lane;
-    if (vi < nvec) Vec<Tout>::template store<VE>(dst + (int64_t)vi * VE, acc[u]);
   }
 }
 
@@ -868,6 +870,18 @@ int gather_grid(int64_t items) {
   if (blocks > cap) blocks = cap;
   if (blocks < 1) blocks = 1;
   return (int)blocks;
+}
+
+// Workgroups of the combine: one item per wavefront, or 16 workgroups per CU
+// that loop over the items where rows are narrow (half of a wavefront's lanes
+// idle: starting wavefronts then costs more than scattered stores; 2^20
+// tokens, fp32, rows of 1 / 8 / 32 / 64 vectors: 213 / 215 / 356 / 429 us with
+// one item per wavefront, 182 / 183 / 328 / 431 with the loop) or where the
+// launch would reach 2^32 threads, which HIP refuses.
+int64_t combine_grid(int64_t items, int d, foremoe_dtype dtype) {
+  const int nvec = d / (dtype == FOREMOE_BF16 ? 8 : 4);
+  const int64_t blocks = (items + 3) / 4;
+  return nvec <= 32 || blocks >= ((int64_t)1 << 24) ? gather_grid(items) : blocks;
 }
 
 }  // namespace
@@ -1092,7 +1106,7 @@ static int launch_combine(const void* y_perm, foremoe_dtype in_dtype, const int3
                           int64_t T, int32_t K, int32_t d, int64_t n_cap, void* y, foremoe_dtype out_dtype,
                           hipStream_t st) {
   const int nchunk = gather_chunks(d, in_dtype);
-  const dim3 grid((unsigned)((T * nchunk + 3) / 4)), block(256);
+  const dim3 grid((unsigned)combine_grid(T * nchunk, d, in_dtype)), block(256);
   if (in_dtype == FOREMOE_BF16 && out_dtype == FOREMOE_BF16)
     hipLaunchKernelGGL((combine_kernel<uint16_t, uint16_t>), grid, block, 0, st, (const uint16_t*)y_perm, pair_to_row,
                        gates, T, K, d, n_cap, nchunk, (uint16_t*)y);

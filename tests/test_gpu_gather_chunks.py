@@ -47,3 +47,29 @@ def test_gather_chunks(gpu, T, K, d, dtype, out):
     for got, ref, mag in ((y, ry, my), (dx, rx, mx)):
         err = np.abs(got.double().cpu().numpy() - ref)
         assert np.all(err <= eps * np.abs(ref) + (K + 2) * 2.0 ** -23 * mag)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d", [8, 264])
+def test_combine_past_the_launch_limit(gpu, d):
+    """2^26 wavefronts and more, one per token: as many threads as a launch
+    may not have. Narrow rows and wider ones; slices of the result against
+    torch (one pair per token, so the product is rounded once)."""
+    from paper_2606_11867_amd import api
+    T, n = 2 ** 26 + 5, 1000
+    print(f"\n[case] combine T={T} d={d}", flush=True)
+    g = torch.Generator(device=gpu).manual_seed(d)
+    yp = torch.randn(n, d, generator=g, device=gpu).bfloat16()
+    p2r = torch.randint(-1, n + 2, (T,), generator=g, device=gpu, dtype=torch.int32)
+    gates = torch.rand(T, 1, generator=g, device=gpu)
+    for name, y, scale in (("combine", api.combine(yp, p2r, gates, out_dtype=torch.bfloat16), gates),
+                           ("permute_bwd", api.permute_bwd(yp, p2r, T, 1, out_dtype=torch.bfloat16), None)):
+        torch.cuda.synchronize()
+        for t0 in [0, 2 ** 24 - 7, 2 ** 25, T - 2 ** 16]:
+            s = slice(t0, min(t0 + 2 ** 16, T))
+            r = p2r[s].long()
+            ok = (r >= 0) & (r < n)
+            ref = yp[r.clamp(0, n - 1)].float() * (scale[s] if scale is not None else 1.0)
+            ref[~ok] = 0
+            assert torch.equal(y[s], ref.bfloat16()), f"{name}: tokens from {t0}"
+        del y
