@@ -42,6 +42,11 @@ __device__ __forceinline__ void xfer_store(char* p, u32x4 v) {
   __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p));
 }
 
+// This thread's byte of its record.
+__device__ __forceinline__ uint64_t xfer_offset() {
+  return ((uint64_t)blockIdx.z * gridDim.x + blockIdx.x) * kXferChunk + threadIdx.x * 16u;
+}
+
 struct XferRecords {
   int32_t widx[FOREMOE_MAX_XFER_RECORDS];
   int32_t gidx[FOREMOE_MAX_XFER_RECORDS];
@@ -84,7 +89,7 @@ __global__ __launch_bounds__(kXferThreads) void copy_out_kernel(RecordParts rp, 
                                                                 const char* wdn, const char* ggu, const char* gdn,
                                                                 char* buf) {
   const int r = blockIdx.y;
-  const uint64_t total = rp.total(), off = (uint64_t)blockIdx.x * kXferChunk + threadIdx.x * 16u;
+  const uint64_t total = rp.total(), off = xfer_offset();
   if (off < total)
     xfer_store(buf + (uint64_t)r * total + off,
                xfer_load(part_addr(rp, off, r, rec, (char*)wgu, (char*)wdn, (char*)ggu, (char*)gdn)));
@@ -116,7 +121,7 @@ __global__ __launch_bounds__(kXferThreads) void copy_in_kernel(RecordParts rp, X
                                                                float* gdn) {
   const int row = blockIdx.y;
   const uint64_t rbytes = rp.total();
-  const uint64_t off = (uint64_t)blockIdx.x * kXferChunk + threadIdx.x * 16u;
+  const uint64_t off = xfer_offset();
   if (row < pl.n_par) {
     if (off >= rp.gu_p + rp.dn_p) return;
     const int r = pl.par[row];
@@ -137,8 +142,13 @@ __global__ __launch_bounds__(kXferThreads) void copy_in_kernel(RecordParts rp, X
   xfer_store(dst, acc);
 }
 
-// workgroups per record: chunks of its longest part list
-unsigned xfer_blocks_x(uint64_t bytes) { return (unsigned)((bytes + kXferChunk - 1) / kXferChunk); }
+// One workgroup per chunk of the longest part list, for each of `rows` rows.
+// A launch may have fewer than 2^32 threads in a dimension: records of 64 GiB
+// and more take several layers of 2^23 chunks.
+dim3 xfer_grid(uint64_t bytes, int rows) {
+  const uint64_t chunks = (bytes + kXferChunk - 1) / kXferChunk, most = (uint64_t)1 << 23;
+  return dim3((unsigned)std::min(chunks, most), rows, (unsigned)((chunks + most - 1) / most));
+}
 
 }  // namespace
 }  // namespace foremoe
@@ -195,7 +205,7 @@ int foremoe_copy_out(const void* w_gate_up, const void* w_down, foremoe_dtype dt
   REQUIRE(!(what & FOREMOE_XFER_GRADS) || (dw_gate_up && dw_down), "copy_out: gradient arrays NULL");
   REQUIRE((((uintptr_t)w_gate_up | (uintptr_t)w_down | (uintptr_t)dw_gate_up | (uintptr_t)dw_down) & 15) == 0,
           "copy_out: expert arrays must be 16-byte aligned");
-  hipLaunchKernelGGL(copy_out_kernel, dim3(xfer_blocks_x(rp.total()), n), dim3(kXferThreads), 0, (hipStream_t)stream,
+  hipLaunchKernelGGL(copy_out_kernel, xfer_grid(rp.total(), n), dim3(kXferThreads), 0, (hipStream_t)stream,
                      rp, rec, (const char*)w_gate_up, (const char*)w_down, (const char*)dw_gate_up,
                      (const char*)dw_down, (char*)buf);
   return check_launch("foremoe_copy_out");
@@ -257,7 +267,7 @@ int foremoe_copy_in(const void* buf, size_t buf_bytes, int32_t n, const int32_t*
   const int rows = pl.n_par + pl.n_grp;
   if (rows == 0) return FOREMOE_OK;
   const uint64_t most = std::max(rp.gu_p + rp.dn_p, rp.gu_g + rp.dn_g);
-  hipLaunchKernelGGL(copy_in_kernel, dim3(xfer_blocks_x(most), rows), dim3(kXferThreads), 0,
+  hipLaunchKernelGGL(copy_in_kernel, xfer_grid(most, rows), dim3(kXferThreads), 0,
                      (hipStream_t)stream, rp, rec, pl, (const char*)buf, (char*)w_gate_up, (char*)w_down, dw_gate_up,
                      dw_down);
   return check_launch("foremoe_copy_in");

@@ -130,3 +130,39 @@ def test_prefetch_from_pinned_master(gpu):
     torch.cuda.synchronize()
     for e, w in zip(needed, slot_of.tolist()):
         assert torch.equal(wgu[w].cpu(), master_gu[e]) and torch.equal(wdn[w].cpu(), master_dn[e]), (e, w)
+
+
+def test_record_past_the_launch_limit(gpu):
+    """One record of more than 64 GiB (a vector per thread: 2^32 of them)
+    through copy-out and copy-in, compared at the ends of its parts and
+    around the 32 and 64 GiB marks."""
+    from paper_2606_11867_amd import api
+    d = F = 107024
+    n = api.xfer_record_bytes(d, F, torch.bfloat16, 1)
+    assert n > 2 ** 36
+    if torch.cuda.mem_get_info(gpu)[0] < 2 * n + 2 ** 32:
+        pytest.skip(f"needs {2 * n >> 30} GiB of device memory")
+    print(f"\n[case] transfer of one record of {n} bytes", flush=True)
+    gu = torch.empty((1, 2 * F, d), dtype=torch.bfloat16, device=gpu)
+    dn = torch.empty((1, d, F), dtype=torch.bfloat16, device=gpu)
+    grad = torch.empty((1, 2, 1), device=gpu)  # not part of the record
+    gub, dnb = (t.view(torch.uint8).reshape(-1) for t in (gu, dn))
+    # marked windows: (bytes of the arrays, their place in the record)
+    win, g = 4096, torch.Generator(device=gpu).manual_seed(1)
+    marks = [(gub, 0, 0), (gub, 2 ** 35 - 16, 2 ** 35 - 16), (gub, gub.numel() - win, gub.numel() - win),
+             (dnb, 0, gub.numel()), (dnb, 2 ** 36 - win - gub.numel(), 2 ** 36 - win),
+             (dnb, 2 ** 36 - gub.numel(), 2 ** 36), (dnb, dnb.numel() - win, n - win)]
+    want = []
+    for arr, at, _ in marks:
+        arr[at:at + win] = torch.randint(0, 256, (win,), generator=g, device=gpu, dtype=torch.uint8)
+        want.append(arr[at:at + win].clone())
+    buf = torch.empty(n, dtype=torch.uint8, device=gpu)
+    api.copy_out(gu, dn, grad, grad, [0], [0], 1, buf=buf)
+    torch.cuda.synchronize()
+    for (arr, at, off), w in zip(marks, want):
+        assert torch.equal(buf[off:off + win], w), f"copy-out, byte {off}"
+        arr[at:at + win] = 0
+    api.copy_in(buf, [0], [0], [0], 1, gu, dn, grad, grad)
+    torch.cuda.synchronize()
+    for (arr, at, off), w in zip(marks, want):
+        assert torch.equal(arr[at:at + win], w), f"copy-in, byte {off}"
