@@ -20,6 +20,7 @@
 
 #include "common.h"
 #include "ffn_f32.h"
+#include "row_units.h"
 
 namespace foremoe {
 namespace {
@@ -32,9 +33,6 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 // Tile configurations (overridable at build time for tuning sweeps).
-#ifndef FM_ROWS_BK
-#define FM_ROWS_BK 64
-#endif
 #ifndef FM_ROWS_NS
 #define FM_ROWS_NS 2
 #endif
@@ -587,25 +585,14 @@ struct FfnArgs {
   unsigned* row_done;  // workspace: halves of column tiles done per row tile of the first GEMM
 };
 
-// Workspace of the row GEMMs: counters (zero between calls), then the fp32
-// partial tiles of the pieces (at most 128 KiB each).
-constexpr size_t kRowsArrivedOff = 0;            // arrival counters of both GEMMs
-constexpr size_t kRowsQueueOff = 4096;           // queue counters
-constexpr size_t kRowsDoneOff = 12288;           // per row tile
-constexpr size_t kRowsPartOff = 65536;
-constexpr int kMaxRowTiles = (int)((kRowsPartOff - kRowsDoneOff) / 4);
-constexpr int kPieceBytes = 128 * 1024;
-constexpr int kCutUnits = 224;  // units of a GEMM's tiles cut along K, at most (7/8 of 256 workgroups)
 constexpr int kQueues = 8;       // one per XCD
 // Queue counters are 256 bytes apart: in one line, the atomics of all
 // workgroups (they end their tiles together) would queue up behind each other.
 constexpr int kQueueStride = 64;
 
-// Row tiles of a launch, built by every workgroup from the slot offsets. A
-// slot's rows are cut into tiles of 256; what is left over is a tile of its
-// own: of 256 rows if more than 128 are left, of 128 ("short") if more than
-// 64, else of 64 ("thin"). Row tiles are numbered: the 256-row ones slot by
-// slot, then the short ones, then the thin ones.
+// Row tiles of a launch (slot_tiles), built by every workgroup from the slot
+// offsets. They are numbered: the 256-row ones slot by slot, then the short
+// ones, then the thin ones.
 struct RowTiles {
   int full[FOREMOE_MAX_SLOTS + 1];  // 256-row tiles of the slots before
   uint16_t tail[FOREMOE_MAX_SLOTS];  // slots of the short tiles from the front, of the thin ones from the back
@@ -635,9 +622,9 @@ __device__ void build_row_tiles(const int32_t* __restrict__ off, const int32_t* 
         if (j == S - 1) R.off[S] = end;
         R.widx[j] = widx[j];
         if (rows > 0) {
-          const int left = rows % 256;
-          full = rows / 256 + (left > 128);
-          tail = left > 128 || left == 0 ? 0 : (left > 64 ? 1 : 1 << 16);
+          const SlotTiles t = slot_tiles(rows);
+          full = t.full;
+          tail = t.is_short | t.is_thin << 16;
         }
       }
       int fi = full, ti = tail;
@@ -927,10 +914,6 @@ __device__ __forceinline__ void rows_epilogue(const RowsArgs& a, const CoreT& co
 // fence is needed: such a fence would write back and invalidate the whole
 // L2 of the XCD, evicting the operand tiles that every other workgroup there
 // is using.
-#ifndef FM_SPLIT_MAX
-#define FM_SPLIT_MAX 4
-#endif
-constexpr int kSplitMax = FM_SPLIT_MAX;    // pieces per tile at most (2..4)
 #ifndef FM_SPLIT_REGION_KIB
 #define FM_SPLIT_REGION_KIB 16
 #endif
@@ -1017,58 +1000,6 @@ __device__ __forceinline__ void split_sum(__amdgpu_buffer_rsrc_t rs, int wave, c
     }
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): LDS reads done before the region is refilled
   });
-}
-
-// Work of one GEMM of a launch: tiles (row tile x 256 columns) in a fixed
-// order, the 256-row ones first. The last `r` tiles may be cut: those of 256
-// rows into `h` halves of 128 columns, and then every (half) tile into `s`
-// pieces along K, each a unit of its own.
-struct PhaseUnits {
-  int nt;     // column tiles
-  int kt;     // k-steps
-  int small;  // tiles of 128 or 64 rows
-  int plain;  // tiles that are not cut
-  int full_cut;  // 256-row tiles among the cut ones
-  int h, s;
-  int total;  // units
-};
-
-// nfull, nsmall: row tiles of 256 rows and of fewer. r: the tiles of a last,
-// partial round (all tiles, if they make less than one round of the G
-// workgroups).
-__device__ __forceinline__ PhaseUnits phase_units(int nfull, int nsmall, int N, int K, int G, int r, bool ws) {
-  PhaseUnits u;
-  u.nt = (N + 255) / 256;
-  u.kt = K / FM_ROWS_BK;
-  u.small = nsmall * u.nt;
-  const int tiles = nfull * u.nt + u.small;
-  r = r < tiles ? r : tiles;
-  u.full_cut = r > u.small ? r - u.small : 0;
-  const int rs = r - u.full_cut;
-  // A partial last round that leaves the chip less than half busy is cut
-  // along N first: two half-width tiles on two workgroups, with no partial
-  // sums (measured faster than cutting the same round along K).
-  u.h = (u.full_cut > 0 && 8 * (2 * u.full_cut + rs) <= 7 * G) ? 2 : 1;
-  // Then, with the workspace, along K: as many pieces as keep at most 7/8 of
-  // the workgroups busy (a cut that fills the chip measured slower than the
-  // round uncut and spread out), none shorter than 16 k-steps (8 for the
-  // small tiles, whose partial sums are a quarter). Beside halves a small
-  // tile counts as two: the halves bound such a round, and pieces gain little
-  // on it (layer of 512 tokens, 12 tiles of 256 rows and 48 small ones,
-  // K = 2048, in 2 pieces 59.8 us, uncut 61.4) for sums in another fp32
-  // order than the tiles alone give.
-  u.s = 1;
-  const int n = u.full_cut * u.h + rs;
-  if (ws && n > 0 && (u.full_cut == 0 || (u.h == 2 && u.kt >= 32))) {
-    int s = (7 * G / 8) / (u.h * r);
-    s = s < kSplitMax ? s : kSplitMax;
-    const int most = u.kt / (u.full_cut ? 16 : 8);
-    s = s < most ? s : most;
-    u.s = s < 1 ? 1 : s;
-  }
-  u.plain = tiles - r;
-  u.total = u.plain + n * u.s;
-  return u;
 }
 
 // Queue of XCD x: the units it takes, in order. Whole rounds of G units are
@@ -1361,13 +1292,13 @@ __device__ __forceinline__ void run_unit(const FfnArgs& fa, const PhaseUnits& u,
     if (pieces > 1) {
       // the partial sums go to the workspace; the last piece of the (half)
       // tile to arrive adds all of them in piece order
-      const int first = PH * kCutUnits + r.cut - r.q;  // slot of piece 0
+      const int base = PH * cut_units((int)gridDim.x), first = base + r.cut - r.q;  // slot of piece 0
       const __amdgpu_buffer_rsrc_t rs =
           split_rsrc(fa.part + (size_t)first * (kPieceBytes / 4), (uint32_t)pieces * kPieceBytes);
       split_store<CoreT, NW>(rs, r.q, wave, core);
       wait_vm<0>();  // this wave's partial sums have reached memory
       __syncthreads();
-      unsigned* count = fa.arrived + PH * kCutUnits + r.cut / pieces;
+      unsigned* count = fa.arrived + base + r.cut / pieces;
       if (threadIdx.x == 0) *s_flag = atomicAdd(count, 1u) == (unsigned)(pieces - 1);
       __syncthreads();
       if (!*s_flag) {
@@ -1440,29 +1371,11 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(FfnArgs fa) {
   if (pair && tid == 0) first = (int)atomicAdd(&fa.queue[x0 * kQueueStride], 1u);
   build_row_tiles(fa.slot_offset, fa.slot_widx, fa.S, fa.n_cap, R, s_tmp);
   if (tid == 0) s_claim = first;
-  PhaseUnits u0, u1;
   const int nfull = __builtin_amdgcn_readfirstlane(R.full[fa.S]);
   const int nsmall = __builtin_amdgcn_readfirstlane(R.n_short + R.n_thin);
-  {
-    const int rows = nfull + nsmall;
-    const int t0 = rows * ((fa.p[0].N + 255) / 256), t1 = rows * ((fa.p[1].N + 255) / 256);
-    const bool ws = fa.part != nullptr;
-    // the first of two GEMMs is cut only if it makes less than a round (its
-    // partial round is filled by the second); the last round of the second
-    // follows from the work of both
-    const int r0 = t0 < G ? t0 : (pair ? 0 : t0 % G);
-    int r1 = t1 < G ? t1 : t1 % G;
-    if (pair && t0 >= G && t1 >= G) {
-      // both in tiles of the second GEMM, by their k-steps
-      const float rounds = ((float)t0 * (float)fa.p[0].K / (float)fa.p[1].K + (float)t1) / (float)G;
-      r1 = (int)((rounds - floorf(rounds)) * (float)G);
-      if (16 * r1 > 7 * G) r1 = 0;
-    }
-    u0 = phase_units(nfull, nsmall, fa.p[0].N, fa.p[0].K, G, r0, ws);
-    u1 = phase_units(nfull, nsmall, fa.p[1].N, fa.p[1].K, G, r1, ws);
-    if (!(fa.phases & 1)) u0.total = 0;
-    if (!(fa.phases & 2)) u1.total = 0;
-  }
+  const LaunchUnits lu =
+      launch_units(nfull, nsmall, fa.p[0].N, fa.p[0].K, fa.p[1].N, fa.p[1].K, fa.phases, G, fa.part != nullptr);
+  const PhaseUnits &u0 = lu.u0, &u1 = lu.u1;
   HandOver ho{-1, 0u, false};
   const unsigned done_tile = 2u * (unsigned)u0.nt, done_all = done_tile * (unsigned)(nfull + nsmall);
 
@@ -2111,17 +2024,13 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradArgs a) {
 // ---------------------------------------------------------------------------
 int persistent_grid() { return num_cus(); }
 
-// Row-GEMM workspace (optional): counters, then the pieces' partial tiles.
-size_t rows_workspace_bytes() { return 4096 + (size_t)persistent_grid() * 256 * 256 * 4; }
-
 // Launches the row GEMMs set in a.phases. e0, e1: optional timing events set
 // when the kernel starts and ends (they ride on the dispatch itself, so no
 // event command sits in the stream).
 template <bool FWD>
 void launch_rows(FfnArgs a, void* ws, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   const int G = persistent_grid();
-  const size_t parts = kRowsPartOff + (size_t)2 * kCutUnits * kPieceBytes;
-  if (ws && G <= 256 && rows_workspace_bytes() >= parts) {
+  if (ws && rows_workspace_fits(G)) {
     a.arrived = (unsigned*)((char*)ws + kRowsArrivedOff);
     a.queue = (unsigned*)((char*)ws + kRowsQueueOff);
     a.row_done = (unsigned*)((char*)ws + kRowsDoneOff);
@@ -2178,8 +2087,8 @@ static int check_ffn(const char* who, foremoe_dtype dtype, int32_t d, int32_t F,
 static int check_rows_ws(const char* who, const void* workspace, size_t ws_bytes) {
   if (!workspace) return FOREMOE_OK;
   REQUIRE(((uintptr_t)workspace & 255) == 0, "%s: workspace must be 256-byte aligned", who);
-  REQUIRE(ws_bytes >= rows_workspace_bytes(), "%s: workspace of %zu bytes, %zu needed", who, ws_bytes,
-          rows_workspace_bytes());
+  const size_t need = rows_workspace_bytes(persistent_grid());
+  REQUIRE(ws_bytes >= need, "%s: workspace of %zu bytes, %zu needed", who, ws_bytes, need);
   return FOREMOE_OK;
 }
 
@@ -2596,7 +2505,7 @@ static int check_wgrad_shape(const char* who, foremoe_dtype dtype, int32_t d, in
   return FOREMOE_OK;
 }
 
-size_t foremoe_ffn_workspace_size(void) { return rows_workspace_bytes(); }
+size_t foremoe_ffn_workspace_size(void) { return rows_workspace_bytes(persistent_grid()); }
 
 size_t foremoe_wgrad_workspace_size(int32_t d, int32_t F) {
   if (d < 1 || F < 1) return 0;
