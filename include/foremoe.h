@@ -182,8 +182,9 @@ int foremoe_assign_replicas(const int32_t* counts, const foremoe_plan* plan,
  * or foremoe_histogram_src (plan->n_src >= 2, sources from
  * plan->src_token_begin) into counts [n_src * E], followed by
  * foremoe_assign_replicas with the same plan, workspace and stream, in two
- * launches instead of three: one wavefront per key scans the key's column and
- * splits it over its replicas, and the last workgroup to finish turns the
+ * launches instead of three: one wavefront per key (a workgroup where pairs
+ * are many and keys few) scans the key's column and splits it over its
+ * replicas, and the last workgroup to finish turns the
  * slots' counts into offsets (a ticket in workspace status word 63 and an
  * error count in word 62, see above). Same argument rules and
  * errors as the two calls it replaces.

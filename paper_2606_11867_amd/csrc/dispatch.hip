@@ -329,44 +329,102 @@ __global__ __launch_bounds__(kAssignThreads) void assign_kernel(const int32_t* _
 }
 
 // ---------------------------------------------------------------------------
-// Step 1b and step 2 in one launch: one wavefront per key adds up the key's
-// per-block counts, splits them over its replicas as assign_kernel does, and
-// leaves the counts of the virtual slots that hold them in vslot_offset; the
-// last workgroup to finish (a ticket in the workspace header) turns those
-// into offsets. Workgroups may run on different XCDs, whose L2 caches are not
-// coherent with each other: slot counts and the error count are stored and
-// loaded with device scope, and have reached memory before their workgroup
-// takes its ticket; the block bases, read only by later kernels, are stored
-// after. No workgroup waits for another.
+// Step 1b and step 2 in one launch: one wavefront per key (WIDE: one
+// workgroup) adds up the key's per-block counts, splits them over its replicas
+// as assign_kernel does, and leaves the counts of the virtual slots that hold
+// them in vslot_offset; the last workgroup to finish (a ticket in the
+// workspace header) turns those into offsets. Workgroups may run on different
+// XCDs, whose L2 caches are not coherent with each other: slot counts and the
+// error count are stored and loaded with device scope, and have reached memory
+// before their workgroup takes its ticket; the block bases, read only by later
+// kernels, are stored after (WIDE: the last ones). No workgroup waits for
+// another.
 //
 // Latency-bound: a launch is about four dependent round trips to memory.
 // With the whole split in the last workgroup, from the counts of all keys, it
 // was slower, and above 256 keys its tables did not fit beside the scan, so
 // that those ran three kernels. Steps 1-3 (us, before -> now): 16384 x 8 ids, 128
 // keys 38.8 -> 37.8; 1024 keys (8 sources) 54.0 -> 48.6.
+//
+// WIDE, for many blocks: one wavefront walks its key's column twice (the
+// total, then the bases), a workgroup once, 1024 blocks at a time. Counts,
+// scan and split (us, one wavefront -> one workgroup per key): 8 keys, 1024
+// blocks 18.4 -> 10.2; 128 keys, 256 / 320 / 1024 / 16384 blocks 10.3 / 12.0 /
+// 21 / 298 -> 10.4 / 11.0 / 13.4 / 104; 256 keys, 320 / 512 / 16384 blocks
+// 12.3 / 14.8 / 312 -> 13.1 / 13.6 / 131. With 1024 keys, which fill the chip
+// as wavefronts, 35 -> 36 at 1024 blocks and 407 -> 490 at 16384: not taken.
 // ---------------------------------------------------------------------------
+template <bool WIDE>
 __global__ __launch_bounds__(kHistThreads) void hist_scan_split_kernel(
     int32_t* __restrict__ partial, int64_t nblocks, int nkeys, int32_t* __restrict__ counts, uint32_t* ticket,
     PlanDev P, int32_t* __restrict__ rep_begin, int32_t* __restrict__ slot_count, int32_t* __restrict__ slot_offset,
     int32_t* vslot_offset, int32_t* __restrict__ rep_slot, int32_t* __restrict__ status) {
-  constexpr int kHeld = 4;  // chunks of 64 blocks whose counts stay in registers
-  __shared__ int s_rs[kWaves][FOREMOE_MAX_REPLICAS];
+  constexpr int kKeys = WIDE ? 1 : kWaves;         // keys per workgroup
+  constexpr int kHeld = 4;                         // counts a thread keeps in registers
+  constexpr int kStep = WIDE ? kHistThreads : 64;  // blocks per load of a key's threads
+  __shared__ int s_rs[kKeys][FOREMOE_MAX_REPLICAS];
+  __shared__ int s_sum[kHeld][kWaves];
   __shared__ int s_tmp[kWaves];
   __shared__ int s_off[FOREMOE_MAX_SLOTS + 1];
   __shared__ int s_last;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int e = blockIdx.x * kWaves + w, NS = P.n_src * P.S;
+  const int kw = WIDE ? 0 : w, pos = WIDE ? tid : lane;
+  const int e = blockIdx.x * kKeys + kw, NS = P.n_src * P.S;
   int32_t* col = partial + e;
   const int64_t ld = nkeys + 1;
   int v[kHeld];
-  if (e <= nkeys) {
+  auto load = [&](int64_t b0) {
 #pragma unroll
     for (int c = 0; c < kHeld; ++c) {
-      const int64_t b = c * 64 + lane;
+      const int64_t b = b0 + c * kStep + pos;
       v[c] = b < nblocks ? col[b * ld] : 0;
     }
+  };
+  if (e <= nkeys) load(0);
+  int n = 0;       // pairs of the key
+  int64_t b0 = 0;  // WIDE: first block of the batch in v
+  // WIDE: counts become block bases, batch by batch; the last batch is stored
+  // after the ticket
+  auto store = [&]() {
+#pragma unroll
+    for (int c = 0; c < kHeld; ++c) {
+      const int64_t b = b0 + c * kStep + pos;
+      if (b < nblocks) col[b * ld] = v[c];
+    }
+  };
+  if constexpr (WIDE) {
+    for (;;) {
+      int own[kHeld];
+#pragma unroll
+      for (int c = 0; c < kHeld; ++c) {
+        own[c] = v[c];
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int t = __shfl_up(v[c], o, 64);
+          if (lane >= o) v[c] += t;
+        }
+        if (lane == 63) s_sum[c][w] = v[c];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int c = 0; c < kHeld; ++c) {
+        int before = n;
+#pragma unroll
+        for (int q = 0; q < kWaves; ++q) {
+          const int t = s_sum[c][q];
+          if (q < w) before += t;
+          n += t;
+        }
+        v[c] += before - own[c];
+      }
+      if (b0 + kHeld * kStep >= nblocks) break;
+      store();
+      b0 += kHeld * kStep;
+      __syncthreads();  // s_sum is free again
+      load(b0);
+    }
   }
-  if (e < nkeys) {
+  if (e < nkeys && (!WIDE || w == 0)) {
     const int src = e / P.E, ex = e - src * P.E, RS = P.R_max + 1;
     int err = 0;
     int R = P.expert_nrep[ex];
@@ -378,17 +436,18 @@ __global__ __launch_bounds__(kHistThreads) void hist_scan_split_kernel(
                                           : (P.expert_rep_weight ? P.expert_rep_weight + (int64_t)ex * P.R_max : nullptr);
     const int wv = lane < R ? (wt ? wt[lane] : 1) : 0;
     // the (virtual) slot of each replica; with duplicates the lowest wins
-    if (lane < FOREMOE_MAX_REPLICAS) s_rs[w][lane] = INT_MAX;
+    if (lane < FOREMOE_MAX_REPLICAS) s_rs[kw][lane] = INT_MAX;
     for (int j = lane; j < P.S; j += 64) {
       const int se = P.slot_expert[j], r = P.slot_replica[j];
-      if (se == ex && r >= 0 && r < P.R_max) atomicMin(&s_rs[w][r], j * P.n_src + src);
+      if (se == ex && r >= 0 && r < P.R_max) atomicMin(&s_rs[kw][r], j * P.n_src + src);
     }
-    int n = 0;
+    if constexpr (!WIDE) {
 #pragma unroll
-    for (int c = 0; c < kHeld; ++c) n += v[c];
-    for (int64_t b = kHeld * 64 + lane; b < nblocks; b += 64) n += col[b * ld];
+      for (int c = 0; c < kHeld; ++c) n += v[c];
+      for (int64_t b = kHeld * 64 + lane; b < nblocks; b += 64) n += col[b * ld];
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o, 64);
+      for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o, 64);
+    }
     long long incl = wv;  // weights up to and including this replica
 #pragma unroll
     for (int o = 1; o < FOREMOE_MAX_REPLICAS; o <<= 1) {
@@ -402,7 +461,7 @@ __global__ __launch_bounds__(kHistThreads) void hist_scan_split_kernel(
     const bool eq = bad || total <= 0;
     const int hi = lane < R ? (int)(((long long)n * (eq ? lane + 1 : incl)) / (eq ? (long long)R : total)) : n;
     const int up = __shfl_up(hi, 1, 64), lo = lane == 0 ? 0 : up;
-    const int jj = lane < P.R_max ? s_rs[w][lane] : INT_MAX;
+    const int jj = lane < P.R_max ? s_rs[kw][lane] : INT_MAX;
     const bool held = lane < R && jj != INT_MAX;  // else the replica is remote
     if (held) __hip_atomic_store(vslot_offset + jj, hi - lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (lane == 0 && err) atomicAdd(ticket - 1, (uint32_t)err);
@@ -419,7 +478,10 @@ __global__ __launch_bounds__(kHistThreads) void hist_scan_split_kernel(
   __syncthreads();
   if (tid == 0) s_last = atomicAdd(ticket, 1u) == gridDim.x - 1;
   // exclusive block bases of the key
-  if (e <= nkeys) {
+  if constexpr (WIDE) {
+    store();
+    if (e == nkeys && tid == 0) status[FOREMOE_WS_INVALID_IDS] = n;
+  } else if (e <= nkeys) {
     int carry = 0;
     auto scan = [&](int64_t b, int c) {
       int incl = c;
@@ -1012,7 +1074,11 @@ static int histogram_assign_impl(const int32_t* ids, int64_t T, int32_t K, const
   int32_t* vslot = (int32_t*)((char*)ws + kWsVSlotOff);
   hipLaunchKernelGGL(hist_count_kernel, dim3((unsigned)nb), dim3(kHistThreads), 0, st, ids, npairs, km, nkeys,
                      key_bits(nkeys), partial, rank, SplitClear{ticket, vslot, P.n_src * P.S});
-  hipLaunchKernelGGL(hist_scan_split_kernel, dim3(nkeys / kWaves + 1), dim3(kHistThreads), 0, st, partial, nb, nkeys,
+  // (measured at the kernel: the lines cross at about 300 blocks with 128 keys,
+  // between 320 and 512 with 256)
+  const bool wide = nkeys <= 256 && nb > 256 + nkeys / 2;
+  hipLaunchKernelGGL(wide ? hist_scan_split_kernel<true> : hist_scan_split_kernel<false>,
+                     dim3(wide ? nkeys + 1 : nkeys / kWaves + 1), dim3(kHistThreads), 0, st, partial, nb, nkeys,
                      counts, ticket, P, rep_begin, slot_count, slot_offset, vslot,
                      (int32_t*)((char*)ws + kWsRepSlotOff), status);
   return check_launch("foremoe_histogram_assign");

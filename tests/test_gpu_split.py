@@ -1,7 +1,8 @@
 """foremoe_histogram_assign (counts, replica split and offsets in two
 launches) against foremoe_histogram(_src) and foremoe_assign_replicas, bit
 for bit, over key counts around a workgroup's four keys and the 256 and 1024
-limits, more blocks than stay in registers, and faulty plans."""
+limits, more blocks than stay in registers, few keys with many blocks (a
+workgroup per key), and faulty plans."""
 import numpy as np
 import pytest
 import torch
@@ -34,7 +35,11 @@ def _plan(rng, E, S, R_max, n_src, T, gpu, faulty, weights):
     (1, 1, 1, 1, 3, 1, "none"), (3, 1, 5, 2, 100, 2, "expert"), (4, 1, 0, 16, 64, 3, "none"),
     (5, 1, 300, 16, 700, 5, "expert"), (255, 1, 40, 4, 5000, 8, "expert"), (256, 1, 1024, 2, 1000, 8, "none"),
     (257, 1, 30, 3, 2000, 8, "expert"), (1024, 1, 64, 16, 40000, 4, "expert"), (128, 8, 24, 8, 20001, 8, "src"),
-    (16, 64, 16, 2, 4000, 8, "src"), (7, 3, 11, 5, 333, 2, "expert")])
+    (16, 64, 16, 2, 4000, 8, "src"), (7, 3, 11, 5, 333, 2, "expert"),
+    # a workgroup per key: its first block count, the edge of a batch of 1024 blocks, several batches
+    (128, 1, 24, 4, 20480, 8, "expert"), (128, 1, 24, 4, 20500, 8, "expert"), (1, 1, 1, 1, 140000, 1, "none"),
+    (8, 1, 5, 2, 65536, 8, "expert"), (8, 1, 5, 2, 65537, 8, "none"), (256, 1, 40, 3, 160000, 8, "expert"),
+    (32, 8, 12, 4, 70000, 8, "src")])
 def test_histogram_assign_matches_separate_calls(gpu, E, n_src, S, R_max, T, K, weights, faulty):
     from paper_2606_11867_amd import api
     print(f"\n[case] split E={E} n_src={n_src} S={S} R_max={R_max} T={T} K={K} {weights} faulty={faulty}", flush=True)
