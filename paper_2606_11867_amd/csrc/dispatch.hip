@@ -328,6 +328,15 @@ __global__ __launch_bounds__(kAssignThreads) void assign_kernel(const int32_t* _
   assign_block<kAssignThreads, MAXK>(counts, P, rep_begin, slot_count, slot_offset, vslot_offset, rep_slot, status);
 }
 
+// What a lane wrote to LDS before is seen by the wavefront's other lanes after.
+// (The lanes run together and LDS keeps their order; this keeps the compiler
+// from moving or forwarding accesses across.)
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------------------
 // Step 1b and step 2 in one launch: one wavefront per key (WIDE: one
 // workgroup) adds up the key's per-block counts, splits them over its replicas
@@ -437,6 +446,7 @@ __global__ __launch_bounds__(kHistThreads) void hist_scan_split_kernel(
     const int wv = lane < R ? (wt ? wt[lane] : 1) : 0;
     // the (virtual) slot of each replica; with duplicates the lowest wins
     if (lane < FOREMOE_MAX_REPLICAS) s_rs[kw][lane] = INT_MAX;
+    wave_sync();
     for (int j = lane; j < P.S; j += 64) {
       const int se = P.slot_expert[j], r = P.slot_replica[j];
       if (se == ex && r >= 0 && r < P.R_max) atomicMin(&s_rs[kw][r], j * P.n_src + src);
@@ -461,6 +471,7 @@ __global__ __launch_bounds__(kHistThreads) void hist_scan_split_kernel(
     const bool eq = bad || total <= 0;
     const int hi = lane < R ? (int)(((long long)n * (eq ? lane + 1 : incl)) / (eq ? (long long)R : total)) : n;
     const int up = __shfl_up(hi, 1, 64), lo = lane == 0 ? 0 : up;
+    wave_sync();
     const int jj = lane < P.R_max ? s_rs[kw][lane] : INT_MAX;
     const bool held = lane < R && jj != INT_MAX;  // else the replica is remote
     if (held) __hip_atomic_store(vslot_offset + jj, hi - lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -39,7 +39,10 @@ def _plan(rng, E, S, R_max, n_src, T, gpu, faulty, weights):
     # a workgroup per key: its first block count, the edge of a batch of 1024 blocks, several batches
     (128, 1, 24, 4, 20480, 8, "expert"), (128, 1, 24, 4, 20500, 8, "expert"), (1, 1, 1, 1, 140000, 1, "none"),
     (8, 1, 5, 2, 65536, 8, "expert"), (8, 1, 5, 2, 65537, 8, "none"), (256, 1, 40, 3, 160000, 8, "expert"),
-    (32, 8, 12, 4, 70000, 8, "src")])
+    (32, 8, 12, 4, 70000, 8, "src"),
+    # fewer slots than replicas: most lanes that look a replica up claim no slot themselves
+    (6, 1, 1, 16, 300, 4, "expert"), (2, 1, 3, 16, 300, 2, "none"), (2, 5, 2, 12, 400, 2, "src"),
+    (2, 1, 3, 16, 80000, 2, "expert")])
 def test_histogram_assign_matches_separate_calls(gpu, E, n_src, S, R_max, T, K, weights, faulty):
     from paper_2606_11867_amd import api
     print(f"\n[case] split E={E} n_src={n_src} S={S} R_max={R_max} T={T} K={K} {weights} faulty={faulty}", flush=True)
