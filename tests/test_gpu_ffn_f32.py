@@ -113,3 +113,29 @@ def test_f32_ffn_many_slots_and_bad_weight_index(gpu):
         ref = A / (1 + np.exp(-A)) * U
         # |silu'| < 1.1, |silu(A)| <= |A|
         _close("H", h[r], ref, _gamma(d) * (1.1 * mA * np.abs(U) + np.abs(A) * mU) * 1.1 + E * np.abs(ref) + 1e-6)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,F,parts", [(3, 1, 4), (33, 70, 2), (128, 40, 3), (65, 260, 16)])
+def test_f32_wgrad_parts_are_the_whole(gpu, d, F, parts):
+    """A part's tiles hold its own rows only (m = part + parts i): every part
+    writes its rows, with the bits of the undivided call, and no others."""
+    from paper_2606_11867_amd import api
+    print(f"\n[case] fp32 weight gradients d={d} F={F} in {parts} parts", flush=True)
+    rng = np.random.default_rng(d + F)
+    rows, G = [70, 0, 5, 130], 3
+    N = sum(rows)
+    f32 = lambda *s: torch.from_numpy(rng.standard_normal(s).astype(np.float32)).to(gpu)  # noqa: E731
+    i32 = lambda a: torch.tensor(np.asarray(a, np.int32), device=gpu)  # noqa: E731
+    rec = [dict(x_perm=f32(N, d), h=f32(N, F), dy_perm=f32(N, d), d_au=f32(N, 2 * F),
+                slot_offset=i32(np.concatenate([[0], np.cumsum(rows)])), slot_gidx=i32([0, 1, 2, 0]))]
+    whole = [f32(G, 2 * F, d), f32(G, d, F)]
+    got = [t.clone() for t in whole]
+    start = [t.clone() for t in whole]
+    api.grouped_ffn_wgrad_steps(rec, *whole)
+    for part in range(parts):
+        api.grouped_ffn_wgrad_steps(rec, *got, part=part, parts=parts)
+        torch.cuda.synchronize()
+        for name, g, w, s in zip(("dW_gate_up", "dW_down"), got, whole, start):
+            done = torch.arange(g.shape[1], device=gpu) % parts <= part
+            assert torch.equal(g[:, done], w[:, done]) and torch.equal(g[:, ~done], s[:, ~done]), f"{name}, part {part}"
