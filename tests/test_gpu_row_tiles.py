@@ -10,6 +10,8 @@ import numpy as np
 import pytest
 import torch
 
+import row_units as R
+
 
 def _dev(a, gpu, dtype=torch.bfloat16):
     return torch.from_numpy(np.ascontiguousarray(a)).to(gpu).to(dtype)
@@ -71,6 +73,15 @@ def _check(gpu, rows, d, F, W, use_ws, widx=None, misalign=0):
         for raw, t in ((hr, h), (yr, y), (ar, au), (dr, dau), (xr, dx)):  # nothing outside the rows
             assert bool((raw[:misalign] == 3.0).all()) and bool((raw[misalign + t.numel():] == 3.0).all())
         outs.append((h, y, au, dau, dx))
+    # products that neither form cuts along K have the same bits in both (the
+    # input gradients read the forward's A|U)
+    G = torch.cuda.get_device_properties(gpu).multi_processor_count
+    uncut = [all(fn(rows, d, F, phases=ph, G=G, ws=use_ws)[i].s == 1 for ph in (1 + i, 3))
+             for fn in (R.forward, R.dgrad) for i in (0, 1)]
+    for name, k, needs in (("H", 0, [0]), ("Y", 1, [0, 1]), ("A|U", 2, [0]), ("dA|dU", 3, [0, 2]),
+                           ("dX", 4, [0, 2, 3])):
+        if all(uncut[i] for i in needs):
+            assert torch.equal(outs[0][k], outs[1][k]), f"{name}: one launch and two differ"
     gu64, dn64 = _f64(gu), _f64(dn)
     for pair, (h, y, au, dau, dx) in enumerate(outs):
         for j, w in enumerate(widx):
@@ -107,8 +118,27 @@ LAYOUTS = {
     "odd-width": ([5, 200, 700, 40, 0, 90], 384, 640),
     "thin-only": ([3, 0, 17, 64], 1024, 256),
     "row-groups": ([2304, 40, 300], 3328, 1664),
-    "rounds": ([3000, 1500, 100, 60, 900], 1152, 896),
+    "one-round": ([3000, 1500, 100, 60, 900], 1152, 896),
+    # both products of both directions in more than a round of units, with
+    # every tile height; more than a round with row groups
+    "rounds": ([1300, 900, 500] + [10 + 2 * i for i in range(52)], 1280, 1280),
+    "row-group-rounds": ([2304, 300] + [30] * 12, 3328, 1664),
 }
+
+
+@pytest.mark.parametrize("name", ["rounds", "row-group-rounds"])
+def test_layouts_are_more_than_a_round(name):
+    """On 256 CUs (host arithmetic)."""
+    rows, d, F = LAYOUTS[name]
+    grouped = 0
+    for fn in (R.forward, R.dgrad):
+        u0, u1, t = fn(rows, d, F, G=256)
+        assert t.full and t.thin and (t.short or name != "rounds")
+        for u in (u0, u1):
+            if name == "rounds" or u.nt >= 12:
+                assert u.total > 256 and u.total % 256, u
+            grouped += u.nt >= 12
+    assert grouped == (3 if name == "row-group-rounds" else 0)
 
 
 @pytest.mark.gpu
@@ -189,3 +219,91 @@ def test_counters_that_were_not_zero(gpu, left_over):
     torch.cuda.synchronize()
     for name, a, b in zip(("H", "Y", "A|U"), got, want):
         assert torch.equal(a, b), name
+
+
+@pytest.mark.gpu
+def test_nan_next_to_a_tile_stays_out(gpu):
+    """NaN and infinities in what the half-empty last column tiles of an odd
+    width read and must not store (the next weight row's first columns), and
+    in the rows of other slots."""
+    from paper_2606_11867_amd import api
+    rows, d, F, W = [40, 100, 300, 17], 384, 384, 2
+    print(f"\n[case] NaN beside the tiles, rows {rows}, d={d}, F={F}", flush=True)
+    g = torch.Generator(device=gpu).manual_seed(9)
+    bf = lambda *s, scale=1.0: torch.randn(*s, generator=g, device=gpu).mul_(scale).bfloat16()  # noqa: E731
+    N = sum(rows)
+    x, dy, au = bf(N, d), bf(N, d), bf(N, 2 * F)
+    gu, dn = bf(W, 2 * F, d, scale=d ** -0.5), bf(W, d, F, scale=F ** -0.5)
+    off = torch.tensor([0] + list(np.cumsum(rows)), dtype=torch.int32, device=gpu)
+    widx = torch.tensor([0, 1, 0, 1], dtype=torch.int32, device=gpu)
+    for ws in (api.ffn_workspace(gpu), None):
+        _, y0, _ = api.grouped_ffn_fwd(x, off, widx, gu, dn, ws=ws)
+        dau0, dx0 = api.grouped_ffn_dgrad(dy, au, off, widx, gu, dn, ws=ws)
+        # input gradients: the first 128 columns of every weight row
+        gu1, dn1 = gu.clone(), dn.clone()
+        gu1[:, :, :128], dn1[:, :, :128] = float("nan"), float("inf")
+        dau, _ = api.grouped_ffn_dgrad(dy, au, off, widx, gu, dn1, ws=ws)
+        _, dx = api.grouped_ffn_dgrad(dy, au, off, widx, gu1, dn, ws=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(dau[:, 128:F], dau0[:, 128:F]) and torch.equal(dau[:, F + 128:], dau0[:, F + 128:])
+        assert not bool(dau[:, :128].isfinite().all())
+        assert torch.equal(dx[:, 128:], dx0[:, 128:]) and bool(dx[:, :128].isnan().all())
+        # rows of the slots before and after slot 1
+        x1, dy1 = x.clone(), dy.clone()
+        other = torch.ones(N, dtype=torch.bool, device=gpu)
+        other[rows[0]:rows[0] + rows[1]] = False
+        x1[other], dy1[other] = float("nan"), float("inf")
+        _, y, _ = api.grouped_ffn_fwd(x1, off, widx, gu, dn, ws=ws)
+        _, dx = api.grouped_ffn_dgrad(dy1, au, off, widx, gu, dn, ws=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(y[~other], y0[~other]) and torch.equal(dx[~other], dx0[~other])
+
+
+@pytest.mark.gpu
+def test_launches_of_both_products_side_by_side(gpu):
+    """Two launches of both products on two streams with a workspace each, and
+    a weight gradient on a third: the workgroups of each are partly resident
+    while others wait. Every result is that of the calls one after another."""
+    from paper_2606_11867_amd import api
+    d, F, W = 1024, 512, 4
+    print("\n[case] launches of both products on two streams, weight gradients on a third", flush=True)
+    g = torch.Generator(device=gpu).manual_seed(4)
+    bf = lambda *s, scale=1.0: torch.randn(*s, generator=g, device=gpu).mul_(scale).bfloat16()  # noqa: E731
+    gu, dn = bf(W, 2 * F, d, scale=d ** -0.5), bf(W, d, F, scale=F ** -0.5)
+    sets = []
+    for rows in ([4000, 3000, 70, 1500], [100, 5000, 2500, 40]):
+        N = sum(rows)
+        sets.append(dict(off=torch.tensor([0] + list(np.cumsum(rows)), dtype=torch.int32, device=gpu), x=bf(N, d),
+                         dy=bf(N, d), au=bf(N, 2 * F), ws=api.ffn_workspace(gpu)))
+    widx = torch.arange(W, dtype=torch.int32, device=gpu)
+    wops = (sets[0]["x"], bf(sum([4000, 3000, 70, 1500]), F), sets[0]["dy"], sets[0]["au"], sets[0]["off"], widx)
+    wws = api.wgrad_workspace(d, F, gpu)
+    dw = lambda: [torch.zeros(s, device=gpu) for s in ((W, 2 * F, d), (W, d, F))]  # noqa: E731
+
+    def ffn(s):
+        out = []
+        for _ in range(4):
+            out = [*api.grouped_ffn_fwd(s["x"], s["off"], widx, gu, dn, ws=s["ws"]),
+                   *api.grouped_ffn_dgrad(s["dy"], s["au"], s["off"], widx, gu, dn, ws=s["ws"])]
+        return out
+
+    def wgrad(out):
+        for _ in range(4):
+            api.grouped_ffn_wgrad(*wops, *out, ws=wws)
+        return out
+
+    want = [ffn(s) for s in sets] + [wgrad(dw())]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(gpu) for _ in range(3)]
+    got_dw = dw()
+    torch.cuda.synchronize()
+    got = []
+    for st, fn, arg in zip(streams, (ffn, ffn, wgrad), (*sets, got_dw)):
+        with torch.cuda.stream(st):
+            got.append(fn(arg))
+    torch.cuda.synchronize()
+    for i, (a, b) in enumerate(zip(got, want)):
+        for j, (t, r) in enumerate(zip(a, b)):
+            assert torch.equal(t, r), f"stream {i}, output {j}"
+    for s in sets:
+        assert not bool(s["ws"][:65536].any()), "counters not back at zero"

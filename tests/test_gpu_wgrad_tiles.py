@@ -54,3 +54,39 @@ def test_wgrad_tiles(gpu, name, ws_kind):
             err = np.abs(got.double().cpu().numpy() - ref[key])
             bound = K * 2.0 ** -24 * mag[key]
             assert np.all(err <= bound), f"{key} parts={parts}: {np.max(err - bound):.3g} over its bound"
+
+
+@pytest.mark.gpu
+def test_nan_next_to_a_tile_stays_out(gpu):
+    """NaN and infinities in the operand columns that a half-empty last tile
+    of an odd width reads and must not store (the next row's first ones), and
+    in the rows of another group."""
+    from paper_2606_11867_amd import api
+    d, F, rows, G = 640, 384, [700, 130, 300], 3
+    print(f"\n[case] NaN beside the weight-gradient tiles, rows {rows}, d={d}, F={F}", flush=True)
+    g = torch.Generator(device=gpu).manual_seed(2)
+    bf = lambda *s: torch.randn(*s, generator=g, device=gpu).bfloat16()  # noqa: E731
+    N = sum(rows)
+    ops = [bf(N, d), bf(N, F), bf(N, d), bf(N, 2 * F)]  # x, h, dy, d_au
+    off = torch.tensor([0] + list(np.cumsum(rows)), dtype=torch.int32, device=gpu)
+    gidx = torch.arange(G, dtype=torch.int32, device=gpu)
+
+    def run(ops, ws):
+        dw = [torch.zeros(s, device=gpu) for s in ((G, 2 * F, d), (G, d, F))]
+        api.grouped_ffn_wgrad(*ops, off, gidx, *dw, ws=ws)
+        torch.cuda.synchronize()
+        return dw
+
+    for ws in (api.wgrad_workspace(d, F, gpu), None):
+        want = run(ops, ws)
+        bad = [t.clone() for t in ops]
+        for t, v in zip(bad, (float("nan"), float("inf"), float("-inf"), float("nan"))):
+            t[:, :128] = v
+        for name, a, b in zip(("dW_gate_up", "dW_down"), run(bad, ws), want):
+            assert torch.equal(a[:, 128:, 128:], b[:, 128:, 128:]), name
+            assert not bool(a[:, :128].isfinite().any()) and not bool(a[:, :, :128].isfinite().any()), name
+        bad = [t.clone() for t in ops]
+        for t in bad:
+            t[:700] = float("nan")  # group 0
+        for name, a, b in zip(("dW_gate_up", "dW_down"), run(bad, ws), want):
+            assert torch.equal(a[1:], b[1:]) and bool(a[0].isnan().all()), name
