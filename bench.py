@@ -855,19 +855,21 @@ def planner_report(w, api, dev, n_micro: int, N_r: int = 4, C_max: int = 8) -> d
 
 
 TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "traffic_qwen3_share.json")
+DISPATCH_SOURCES = ["paper_2606_11867_amd/csrc/dispatch.hip"]
+ROW_GEMM_SOURCES = ["paper_2606_11867_amd/csrc/grouped_gemm.hip", "paper_2606_11867_amd/csrc/row_units.h"]
 # the kernels of every phase; a name that serves two phases is dispatched
 # once for each per micro-step, in this order (one-stream and overlapped
 # schedules alike)
 PHASE_KERNELS = [
-    ("hist_count_kernel", ["histogram_assign"], "paper_2606_11867_amd/csrc/dispatch.hip"),
-    ("hist_scan_split_kernel", ["histogram_assign"], "paper_2606_11867_amd/csrc/dispatch.hip"),
-    ("permute_gather_kernel", ["permute"], "paper_2606_11867_amd/csrc/dispatch.hip"),
-    ("gemm_rows_kernel<true>", ["gate_up_fwd", "down_fwd"], "paper_2606_11867_amd/csrc/grouped_gemm.hip"),
-    ("combine_kernel", ["combine", "permute_bwd"], "paper_2606_11867_amd/csrc/dispatch.hip"),
-    ("combine_bwd_kernel", ["combine_bwd"], "paper_2606_11867_amd/csrc/dispatch.hip"),
-    ("gemm_rows_kernel<false>", ["down_dgrad", "gate_up_dgrad"], "paper_2606_11867_amd/csrc/grouped_gemm.hip"),
-    ("gemm_wgrad_kernel", ["down_wgrad", "gate_up_wgrad"], "paper_2606_11867_amd/csrc/grouped_gemm.hip"),
-    ("wgrad_reduce_kernel", ["down_wgrad", "gate_up_wgrad"], "paper_2606_11867_amd/csrc/grouped_gemm.hip"),
+    ("hist_count_kernel", ["histogram_assign"], DISPATCH_SOURCES),
+    ("hist_scan_split_kernel", ["histogram_assign"], DISPATCH_SOURCES),
+    ("permute_gather_kernel", ["permute"], DISPATCH_SOURCES),
+    ("gemm_rows_kernel<true>", ["gate_up_fwd", "down_fwd"], ROW_GEMM_SOURCES),
+    ("combine_kernel", ["combine", "permute_bwd"], DISPATCH_SOURCES),
+    ("combine_bwd_kernel", ["combine_bwd"], DISPATCH_SOURCES),
+    ("gemm_rows_kernel<false>", ["down_dgrad", "gate_up_dgrad"], ROW_GEMM_SOURCES),
+    ("gemm_wgrad_kernel", ["down_wgrad", "gate_up_wgrad"], ROW_GEMM_SOURCES),
+    ("wgrad_reduce_kernel", ["down_wgrad", "gate_up_wgrad"], ROW_GEMM_SOURCES),
 ]
 
 
@@ -932,7 +934,7 @@ def summarize_counters(folder: str) -> int:
             rec = per_phase[phase]
             rec["fetch" if counter == "FETCH_SIZE" else "write"].append(v * 1024.0 / cal[counter])
             rec["kernels"].add(key)
-            rec["sources"].add(src)
+            rec["sources"].update(src)
     T, K, d, F = cp["T"], cp["K"], cp["d"], cp["F"]
     M = cp.get("wgrad_group", 1)
     alg = collections.defaultdict(float)

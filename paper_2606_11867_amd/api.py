@@ -143,9 +143,9 @@ def assign_replicas(counts: torch.Tensor, plan: DevicePlan, ws: torch.Tensor):
 
 
 def histogram_assign(ids: torch.Tensor, plan: DevicePlan, ws: torch.Tensor):
-    """Steps 1 and 2 in one call (two launches for up to 256 keys): the
-    per-key counts (n_src * E keys for a per-source plan) and the replica
-    split, as histogram(_src) followed by assign_replicas."""
+    """Steps 1 and 2 in one call (two launches): the per-key counts
+    (n_src * E keys for a per-source plan) and the replica split, as
+    histogram(_src) followed by assign_replicas."""
     T, K = ids.shape
     dev = ids.device
     nkeys = plan.E * max(plan.n_src, 1)

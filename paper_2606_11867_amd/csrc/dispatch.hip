@@ -583,13 +583,11 @@ struct RowReader {
   }
 };
 
-// STREAM: with the nontemporal hint.
-template <bool STREAM>
-__device__ __forceinline__ void store16(void* p, uint4 v) {
+// A 16-byte store with the nontemporal hint.
+__device__ __forceinline__ void stream16(void* p, uint4 v) {
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   const u32x4 t = {v.x, v.y, v.z, v.w};
-  if constexpr (STREAM) __builtin_nontemporal_store(t, reinterpret_cast<u32x4*>(p));
-  else *reinterpret_cast<u32x4*>(p) = t;
+  __builtin_nontemporal_store(t, reinterpret_cast<u32x4*>(p));
 }
 
 __global__ __launch_bounds__(256) void permute_gather_kernel(
@@ -677,7 +675,7 @@ __global__ __launch_bounds__(256) void permute_gather_kernel(
 #pragma unroll
           for (int u = 0; u < kVecPerLane; ++u) {
             const int64_t vi = v0 + u * 64 + lane;
-            if (vi < vec_per_row) store16<false>(x_perm + (int64_t)rows[r] * vec_per_row + vi, a[r][u]);
+            if (vi < vec_per_row) x_perm[(int64_t)rows[r] * vec_per_row + vi] = a[r][u];
           }
         }
       }
@@ -714,7 +712,7 @@ struct Vec<uint16_t> {
 #pragma unroll
     for (int i = 0; i < M / 2; ++i) w[i] = pack_bf2(f[2 * i], f[2 * i + 1]);
     if constexpr (M == 8) {
-      store16<true>(p, make_uint4(w[0], w[1], w[2], w[3]));
+      stream16(p, make_uint4(w[0], w[1], w[2], w[3]));
     } else {
       *reinterpret_cast<uint2*>(p) = make_uint2(w[0], w[1]);
     }
@@ -734,8 +732,8 @@ struct Vec<float> {
   __device__ static void store(float* p, const float* f) {
 #pragma unroll
     for (int i = 0; i < M; i += 4)
-      store16<true>(p + i, make_uint4(__float_as_uint(f[i]), __float_as_uint(f[i + 1]), __float_as_uint(f[i + 2]),
-                                __float_as_uint(f[i + 3])));
+      stream16(p + i, make_uint4(__float_as_uint(f[i]), __float_as_uint(f[i + 1]), __float_as_uint(f[i + 2]),
+                                 __float_as_uint(f[i + 3])));
   }
 };
 

@@ -1028,7 +1028,10 @@ struct Queues {
 // tiles for 32 products, against 8 x 4 with groups: 12). Measured, column
 // tiles first -> groups (us): nt = 112 (Mixtral-8x7B gate/up) 2055 -> 1848,
 // nt = 28 (DeepSeek-V3 gate/up input gradient) 563 -> 524, nt = 16 923 -> 907;
-// nt = 6 (Qwen3 gate/up) 113 -> 120, nt = 3 71 -> 75, nt = 8 68.5 -> 69.3.
+// nt = 6 (Qwen3 gate/up) 113 -> 120, nt = 3 71 -> 75. Between them, over down
+// forward and gate/up input gradient (F = 2048) of 16284 uneven, 8 x 1024,
+// 8192 and 16 x 2048 rows: nt = 8 to 11 groups 0.97 to 1.02 of the speed, 12 to
+// 15 0.98 to 1.04, on average 1.01.
 #ifndef FM_ROW_GROUP_MIN_NT
 #define FM_ROW_GROUP_MIN_NT 12
 #endif

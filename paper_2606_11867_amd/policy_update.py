@@ -235,7 +235,9 @@ class PolicyUpdate:
             pipelined: bool = False, side_gathers: int = 0, fwd_after_side: bool = False,
             next_ms: Optional[MicroStep] = None, early_hist: bool = False) -> list:
         """The operations of micro-step i on inputs ms, in order, as (phase,
-        thunk) pairs (phase None: a stream dependency). ev maps phases to
+        thunk) pairs (phase None: a stream dependency; "ffn_fwd" and
+        "ffn_dgrad" are gate_up_fwd with down_fwd, and down_dgrad with
+        gate_up_dgrad, in one launch). ev maps phases to
         (begin, end) timing events (hip_events.Event or torch's): row GEMMs
         carry theirs on the kernel launch, the other phases are bracketed by event records on the stream
         the phase runs on. side_gathers (with overlap): 1 runs permute_bwd,

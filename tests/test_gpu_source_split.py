@@ -58,7 +58,7 @@ def run_both(ids, plan, x, n_cap, dtype, gpu, fused=False):
     idd = torch.from_numpy(ids).to(gpu)
     dp = api.DevicePlan.from_host(plan, gpu)
     ws = api.workspace(T, K, plan.E * plan.n_src, gpu)
-    if fused:  # foremoe_histogram_assign: two launches up to 256 keys, else three
+    if fused:  # foremoe_histogram_assign: two launches
         counts, rep_begin, slot_count, slot_offset = api.histogram_assign(idd, dp, ws)
         counts = counts.reshape(plan.n_src, plan.E)
     else:
