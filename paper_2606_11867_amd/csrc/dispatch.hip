@@ -772,73 +772,83 @@ __device__ __forceinline__ TokenPairs token_pairs(const int32_t* __restrict__ pa
 // pairs are loaded together before accumulating.
 //
 // HBM-bound, and mostly by its stores where few tokens have a local pair (y
-// is dense). One item per wavefront (combine_grid) keeps the stores in
-// flight close together in memory, and they carry the nontemporal hint (in
-// a loop of 4096 workgroups without it, us): DeepSeek-V3 EP=32 share (32768
-// tokens of 14 KiB, 7872 local pairs) combine 130 -> 72, permute_bwd
+// is dense). One item per wavefront keeps the stores in flight close together
+// in memory, and they carry the nontemporal hint (in a loop of 4096 workgroups
+// without it, us): DeepSeek-V3 EP=32 share (32768 tokens of 14 KiB, 7872 local
+// pairs) combine 130 -> 72, permute_bwd
 // 127 -> 80; Qwen3 share 21.8 -> 20.3 and 21.4 -> 20.1. Without the hint 122
 // and 102. combine_bwd's stores carry it too (76 -> 65 and 57.6 -> 54.5; the
 // input-gradient GEMM that reads its rows next is no slower); the permute's
 // do not (dispatch the same, the policy update 0.5% slower with it).
 // ---------------------------------------------------------------------------
 template <typename Tin, typename Tout>
-__global__ __launch_bounds__(256) void combine_kernel(const Tin* __restrict__ y_perm, const int32_t* __restrict__ pair_to_row,
-                                                      const float* __restrict__ gates, int64_t T, int K, int d,
-                                                      int64_t n_cap, int nchunk, Tout* __restrict__ y) {
+__device__ __forceinline__ void combine_item(const Tin* __restrict__ y_perm, const int32_t* __restrict__ pair_to_row,
+                                             const float* __restrict__ gates, int K, int d, int64_t n_cap, int nchunk,
+                                             Tout* __restrict__ y, int64_t item) {
   constexpr int VE = Vec<Tin>::N;
   const int lane = threadIdx.x & 63;
   const int nvec = d / VE;
   const uint32_t row_bytes = (uint32_t)d * (uint32_t)sizeof(Tin);
-  const int64_t items = T * nchunk, stride = (int64_t)gridDim.x * 4;
-  for (int64_t item = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); item < items;
-       item += stride) {
-    const int64_t t = nchunk == 1 ? item : item / nchunk;
-    const int v0 = (int)(item - t * nchunk) * 64 * kGatherChunk;
-    const TokenPairs tp = token_pairs(pair_to_row, gates, t, K, n_cap);
-    float acc[kGatherChunk][VE];
+  const int64_t t = item / nchunk;
+  const int v0 = (int)(item - t * nchunk) * 64 * kGatherChunk;
+  const TokenPairs tp = token_pairs(pair_to_row, gates, t, K, n_cap);
+  float acc[kGatherChunk][VE];
 #pragma unroll
-    for (int u = 0; u < kGatherChunk; ++u)
+  for (int u = 0; u < kGatherChunk; ++u)
 #pragma unroll
-      for (int i = 0; i < VE; ++i) acc[u][i] = 0.f;
-    uint64_t m = tp.valid;
-    while (m) {
-      int ks[kPairGroup];
-      int n = 0;
+    for (int i = 0; i < VE; ++i) acc[u][i] = 0.f;
+  uint64_t m = tp.valid;
+  while (m) {
+    int ks[kPairGroup];
+    int n = 0;
 #pragma unroll
-      for (int q = 0; q < kPairGroup; ++q) {
-        ks[q] = m ? __builtin_ctzll(m) : -1;
-        if (m) {
-          m &= m - 1;
-          ++n;
-        }
-      }
-      uint4 raw[kPairGroup][kGatherChunk];
-#pragma unroll
-      for (int q = 0; q < kPairGroup; ++q) {
-        const int row = __builtin_amdgcn_readfirstlane(q < n ? __shfl(tp.row, ks[q], 64) : 0);
-        const RowReader rd(y_perm + (int64_t)row * d, q < n ? row_bytes : 0u);
-#pragma unroll
-        for (int u = 0; u < kGatherChunk; ++u) raw[q][u] = rd.load((uint32_t)((v0 + u * 64 + lane) * 16));
-      }
-#pragma unroll
-      for (int q = 0; q < kPairGroup; ++q) {
-        if (q >= n) break;
-        const float g = __shfl(tp.gate, ks[q], 64);
-#pragma unroll
-        for (int u = 0; u < kGatherChunk; ++u) {
-          float v[VE];
-          Vec<Tin>::widen(raw[q][u], v);
-#pragma unroll
-          for (int i = 0; i < VE; ++i) acc[u][i] += g * v[i];
-        }
+    for (int q = 0; q < kPairGroup; ++q) {
+      ks[q] = m ? __builtin_ctzll(m) : -1;
+      if (m) {
+        m &= m - 1;
+        ++n;
       }
     }
-    Tout* dst = y + t * d;
+    uint4 raw[kPairGroup][kGatherChunk];
 #pragma unroll
-    for (int u = 0; u < kGatherChunk; ++u) {
-      const int vi = v0 + u * 64 + lane;
-      if (vi < nvec) Vec<Tout>::template store<VE>(dst + (int64_t)vi * VE, acc[u]);
+    for (int q = 0; q < kPairGroup; ++q) {
+      const int row = __builtin_amdgcn_readfirstlane(q < n ? __shfl(tp.row, ks[q], 64) : 0);
+      const RowReader rd(y_perm + (int64_t)row * d, q < n ? row_bytes : 0u);
+#pragma unroll
+      for (int u = 0; u < kGatherChunk; ++u) raw[q][u] = rd.load((uint32_t)((v0 + u * 64 + lane) * 16));
     }
+#pragma unroll
+    for (int q = 0; q < kPairGroup; ++q) {
+      if (q >= n) break;
+      const float g = __shfl(tp.gate, ks[q], 64);
+#pragma unroll
+      for (int u = 0; u < kGatherChunk; ++u) {
+        float v[VE];
+        Vec<Tin>::widen(raw[q][u], v);
+#pragma unroll
+        for (int i = 0; i < VE; ++i) acc[u][i] += g * v[i];
+      }
+    }
+  }
+  Tout* dst = y + t * d;
+#pragma unroll
+  for (int u = 0; u < kGatherChunk; ++u) {
+    const int vi = v0 + u * 64 + lane;
+    if (vi < nvec) Vec<Tout>::template store<VE>(dst + (int64_t)vi * VE, acc[u]);
+  }
+}
+
+// LOOP: the grid is capped and strides over the items (combine_loops).
+template <typename Tin, typename Tout, bool LOOP>
+__global__ __launch_bounds__(256) void combine_kernel(const Tin* __restrict__ y_perm, const int32_t* __restrict__ pair_to_row,
+                                                      const float* __restrict__ gates, int64_t T, int K, int d,
+                                                      int64_t n_cap, int nchunk, Tout* __restrict__ y) {
+  int64_t item = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if constexpr (LOOP) {
+    for (; item < T * nchunk; item += (int64_t)gridDim.x * 4)
+      combine_item(y_perm, pair_to_row, gates, K, d, n_cap, nchunk, y, item);
+  } else {
+    if (item < T * nchunk) combine_item(y_perm, pair_to_row, gates, K, d, n_cap, nchunk, y, item);
   }
 }
 
@@ -943,16 +953,22 @@ int gather_grid(int64_t items) {
   return (int)blocks;
 }
 
-// Workgroups of the combine: one item per wavefront, or 16 workgroups per CU
-// that loop over the items where rows are narrow (half of a wavefront's lanes
-// idle: starting wavefronts then costs more than scattered stores; 2^20
-// tokens, fp32, rows of 1 / 8 / 32 / 64 vectors: 213 / 215 / 356 / 429 us with
-// one item per wavefront, 182 / 183 / 328 / 431 with the loop) or where the
-// launch would reach 2^32 threads, which HIP refuses.
-int64_t combine_grid(int64_t items, int d, foremoe_dtype dtype) {
-  const int nvec = d / (dtype == FOREMOE_BF16 ? 8 : 4);
-  const int64_t blocks = (items + 3) / 4;
-  return nvec <= 32 || blocks >= ((int64_t)1 << 24) ? gather_grid(items) : blocks;
+// Whether the combine loops: one item per wavefront is faster but where rows
+// are narrow (half of a wavefront's lanes idle: starting wavefronts then costs
+// more than scattered stores; 2^20 tokens, fp32, rows of 1 / 8 / 32 / 64
+// vectors: 213 / 215 / 356 / 429 us with one item per wavefront, 182 / 183 /
+// 328 / 431 with the loop), and HIP refuses launches of 2^32 threads.
+bool combine_loops(int64_t items, int d, foremoe_dtype dtype) {
+  return d / (dtype == FOREMOE_BF16 ? 8 : 4) <= 32 || (items + 3) / 4 >= ((int64_t)1 << 24);
+}
+
+template <typename Tin, typename Tout>
+void run_combine(const void* y_perm, const int32_t* pair_to_row, const float* gates, int64_t T, int K, int d,
+                 int64_t n_cap, int nchunk, bool loop, void* y, hipStream_t st) {
+  const int64_t items = T * nchunk;
+  hipLaunchKernelGGL((loop ? combine_kernel<Tin, Tout, true> : combine_kernel<Tin, Tout, false>),
+                     dim3((unsigned)(loop ? gather_grid(items) : (items + 3) / 4)), dim3(256), 0, st,
+                     (const Tin*)y_perm, pair_to_row, gates, T, K, d, n_cap, nchunk, (Tout*)y);
 }
 
 }  // namespace
@@ -1181,16 +1197,13 @@ static int launch_combine(const void* y_perm, foremoe_dtype in_dtype, const int3
                           int64_t T, int32_t K, int32_t d, int64_t n_cap, void* y, foremoe_dtype out_dtype,
                           hipStream_t st) {
   const int nchunk = gather_chunks(d, in_dtype);
-  const dim3 grid((unsigned)combine_grid(T * nchunk, d, in_dtype)), block(256);
+  const bool loop = combine_loops(T * nchunk, d, in_dtype);
   if (in_dtype == FOREMOE_BF16 && out_dtype == FOREMOE_BF16)
-    hipLaunchKernelGGL((combine_kernel<uint16_t, uint16_t>), grid, block, 0, st, (const uint16_t*)y_perm, pair_to_row,
-                       gates, T, K, d, n_cap, nchunk, (uint16_t*)y);
+    run_combine<uint16_t, uint16_t>(y_perm, pair_to_row, gates, T, K, d, n_cap, nchunk, loop, y, st);
   else if (in_dtype == FOREMOE_BF16 && out_dtype == FOREMOE_F32)
-    hipLaunchKernelGGL((combine_kernel<uint16_t, float>), grid, block, 0, st, (const uint16_t*)y_perm, pair_to_row,
-                       gates, T, K, d, n_cap, nchunk, (float*)y);
+    run_combine<uint16_t, float>(y_perm, pair_to_row, gates, T, K, d, n_cap, nchunk, loop, y, st);
   else if (in_dtype == FOREMOE_F32 && out_dtype == FOREMOE_F32)
-    hipLaunchKernelGGL((combine_kernel<float, float>), grid, block, 0, st, (const float*)y_perm, pair_to_row, gates,
-                       T, K, d, n_cap, nchunk, (float*)y);
+    run_combine<float, float>(y_perm, pair_to_row, gates, T, K, d, n_cap, nchunk, loop, y, st);
   else
     return set_error(FOREMOE_EUNSUPPORTED, "combine: fp32 input with bf16 output is not supported");
   return FOREMOE_OK;
