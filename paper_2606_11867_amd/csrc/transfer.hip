@@ -33,11 +33,6 @@ namespace {
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kXferThreads = 256;
-// Gradients of up to 256 MiB (the Infinity Cache) in a copy-in are left to the
-// caches: the receive buffer and the targets were written shortly before.
-// Gradients of 64 records of 1.5 MiB, half of them added: 43.5 us with the
-// nontemporal hint, 37.5 without; of 20 records of 18 MiB 149 and 162.
-constexpr uint64_t kCachedGrads = (uint64_t)256 << 20;
 constexpr uint32_t kXferChunk = kXferThreads * 16;  // bytes a workgroup moves: one 16-byte vector per thread
 
 __device__ __forceinline__ u32x4 xfer_load(const char* p) {
@@ -121,8 +116,6 @@ __device__ __forceinline__ u32x4 add4(u32x4 a, u32x4 b) {
   return r;
 }
 
-// STREAM: the gradients stream past the caches (kCachedGrads).
-template <bool STREAM>
 __global__ __launch_bounds__(kXferThreads) void copy_in_kernel(RecordParts rp, XferRecords rec, CopyInPlan pl,
                                                                const char* buf, char* wgu, char* wdn, float* ggu,
                                                                float* gdn) {
@@ -144,11 +137,9 @@ __global__ __launch_bounds__(kXferThreads) void copy_in_kernel(RecordParts rp, X
   const char* rec0 = buf + rp.gu_p + rp.dn_p + off;  // this vector in record 0
   char* dst = off < rp.gu_g ? (char*)ggu + (uint64_t)tgt * rp.gu_g + off
                             : (char*)gdn + (uint64_t)tgt * rp.dn_g + (off - rp.gu_g);
-  auto load = [](const char* p) { return STREAM ? xfer_load(p) : *reinterpret_cast<const u32x4*>(p); };
-  u32x4 acc = load(start >= 0 ? rec0 + (uint64_t)start * rbytes : dst);
-  for (int k = a0; k < a1; ++k) acc = add4(acc, load(rec0 + (uint64_t)pl.ord[k] * rbytes));
-  if constexpr (STREAM) xfer_store(dst, acc);
-  else *reinterpret_cast<u32x4*>(dst) = acc;
+  u32x4 acc = xfer_load(start >= 0 ? rec0 + (uint64_t)start * rbytes : dst);
+  for (int k = a0; k < a1; ++k) acc = add4(acc, xfer_load(rec0 + (uint64_t)pl.ord[k] * rbytes));
+  xfer_store(dst, acc);
 }
 
 // One workgroup per chunk of the longest part list, for each of `rows` rows.
@@ -232,7 +223,6 @@ int foremoe_copy_in(const void* buf, size_t buf_bytes, int32_t n, const int32_t*
   REQUIRE(buf && ((uintptr_t)buf & 15) == 0, "copy_in: receive buffer NULL or not 16-byte aligned");
   XferRecords rec{};
   CopyInPlan pl{};
-  int n_grad = 0;  // records whose gradients are read
   if (what & FOREMOE_XFER_PARAMS) {
     REQUIRE(widx, "copy_in: widx is NULL");
     std::vector<char> seen(W > 0 ? W : 1, 0);
@@ -267,11 +257,9 @@ int foremoe_copy_in(const void* buf, size_t buf_bytes, int32_t n, const int32_t*
       pl.grp_off[pl.n_grp] = k;
       for (int i = start + 1; i < n; ++i)
         if (gidx[i] == g) pl.ord[k++] = i;  // only adds follow the last assign
-      n_grad += start >= 0;
       ++pl.n_grp;
     }
     pl.grp_off[pl.n_grp] = k;
-    n_grad += k;
     REQUIRE(pl.n_grp == 0 || (dw_gate_up && dw_down), "copy_in: gradient arrays NULL");
   }
   REQUIRE((((uintptr_t)w_gate_up | (uintptr_t)w_down | (uintptr_t)dw_gate_up | (uintptr_t)dw_down) & 15) == 0,
@@ -279,11 +267,9 @@ int foremoe_copy_in(const void* buf, size_t buf_bytes, int32_t n, const int32_t*
   const int rows = pl.n_par + pl.n_grp;
   if (rows == 0) return FOREMOE_OK;
   const uint64_t most = std::max(rp.gu_p + rp.dn_p, rp.gu_g + rp.dn_g);
-  // gradients touched: one of every record added or assigned, and the targets
-  const bool stream_grads = (uint64_t)(n_grad + pl.n_grp) * (rp.gu_g + rp.dn_g) > kCachedGrads;
-  hipLaunchKernelGGL(stream_grads ? copy_in_kernel<true> : copy_in_kernel<false>, xfer_grid(most, rows),
-                     dim3(kXferThreads), 0, (hipStream_t)stream, rp, rec, pl, (const char*)buf, (char*)w_gate_up,
-                     (char*)w_down, dw_gate_up, dw_down);
+  hipLaunchKernelGGL(copy_in_kernel, xfer_grid(most, rows), dim3(kXferThreads), 0,
+                     (hipStream_t)stream, rp, rec, pl, (const char*)buf, (char*)w_gate_up, (char*)w_down, dw_gate_up,
+                     dw_down);
   return check_launch("foremoe_copy_in");
 }
 

@@ -166,29 +166,3 @@ def test_record_past_the_launch_limit(gpu):
     torch.cuda.synchronize()
     for (arr, at, off), w in zip(marks, want):
         assert torch.equal(arr[at:at + win], w), f"copy-in, byte {off}"
-
-
-@pytest.mark.parametrize("d,F,n", [(2048, 768, 16), (512, 256, 16)], ids=["past-the-cache", "cached"])
-def test_copy_in_gradients_either_side_of_the_cache(gpu, d, F, n):
-    """Gradients beyond 256 MiB stream past the caches, fewer do not: the same
-    sums, bit for bit, assigned and added in record order."""
-    from paper_2606_11867_amd import api
-    print(f"\n[case] copy_in of {n} gradient records d={d} F={F}", flush=True)
-    g = torch.Generator(device=gpu).manual_seed(n + d)
-    r = lambda *s: torch.randn(*s, generator=g, device=gpu)  # noqa: E731
-    gu, dn = torch.zeros((1, 2 * F, d), dtype=torch.bfloat16, device=gpu), torch.zeros((1, d, F), dtype=torch.bfloat16,
-                                                                                       device=gpu)
-    src, dst = (r(n, 2 * F, d), r(n, d, F)), (r(n, 2 * F, d), r(n, d, F))
-    buf = api.copy_out(gu, dn, *src, [0] * n, list(range(n)), 2)
-    # records 0 and 1 both added to target 3; the others, by turns assigned
-    # and added, to targets of their own
-    gidx = [3, 3, 5, 0, 1, 2] + list(range(6, n))
-    mode = [1, 1] + [i % 2 for i in range(2, n)]
-    want = [t.clone() for t in dst]
-    for i in range(n):
-        for w, s in zip(want, src):
-            w[gidx[i]] = s[i] if mode[i] == 0 else w[gidx[i]] + s[i]
-    api.copy_in(buf, [0] * n, gidx, mode, 2, gu, dn, *dst)
-    torch.cuda.synchronize()
-    for a, b in zip(dst, want):
-        assert torch.equal(a, b)
