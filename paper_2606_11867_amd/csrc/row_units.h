@@ -65,14 +65,15 @@ FM_INLINE PhaseUnits phase_units(int nfull, int nsmall, int N, int K, int G, int
   // Then, with the workspace, along K: as many pieces as keep at most
   // cut_units busy, none shorter than 16 k-steps (8 for the small tiles,
   // whose partial sums are a quarter). Beside halves a small tile counts as
-  // two: the halves bound such a round, and pieces gain little on it (layer
-  // of 512 tokens, 12 tiles of 256 rows and 48 small ones, K = 2048, in 2
-  // pieces 59.8 us, uncut 61.4) for sums in another fp32 order than the tiles
-  // alone give.
+  // two unless K is long: the halves bound such a round, and pieces of 16
+  // k-steps gain little on it (layer of 512 tokens, 12 tiles of 256 rows and 48
+  // small ones, K = 2048, in 2 pieces 59.8 us, uncut 61.4) for sums in another
+  // fp32 order than the tiles alone give. Long ones gain more (Mixtral-8x7B
+  // share, 8192 rows, K = 14336 880 -> 935 us without, K = 28672 1682 -> 1792).
   u.s = 1;
   const int n = u.full_cut * u.h + rs;
   if (ws && n > 0 && (u.full_cut == 0 || (u.h == 2 && u.kt >= 32))) {
-    int s = cut_units(G) / (u.h * r);
+    int s = cut_units(G) / (u.kt >= 64 ? n : u.h * r);
     s = s < kSplitMax ? s : kSplitMax;
     const int most = u.kt / (u.full_cut ? 16 : 8);
     s = s < most ? s : most;
