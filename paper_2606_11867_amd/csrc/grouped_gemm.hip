@@ -67,12 +67,48 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 enum Epi { kEpiStore = 0, kEpiSwigluFwd = 1, kEpiSwigluBwd = 2 };
 
-// Correctly rounded fp32 divisions. The hardware reciprocal would be a few
-// instructions cheaper, but it is 1 ulp off and flushes subnormal results:
-// for a below -87.3 SiLU and its gradient, numbers near 1e-37 in bf16, would
-// become 0.
-__device__ __forceinline__ float silu_f(float a) { return a / (1.0f + __expf(-a)); }
-__device__ __forceinline__ float sigmoid_f(float a) { return 1.0f / (1.0f + __expf(-a)); }
+// SiLU a / D and sigmoid 1 / D with D = 1 + exp(-a), correctly rounded in fp32.
+// The hardware reciprocal alone is 1 ulp off; one Newton step on it (on the
+// quotient) gives the division's bits for every fp32 number a where neither
+// D nor |a| reaches 2^126 (all of them were compared), in a third of its
+// instructions. Beyond, where the reciprocal flushes its subnormal result (a
+// below -87.3, with SiLU near 1e-37 in bf16) or the step has infinities, the
+// division itself; one check for the N values of every lane. Down input
+// gradient of 8 slots of 512 rows (d = 1024, F = 512), us: reciprocal alone
+// 20.9, this 21.2, divisions 22.7; Qwen3 share's gate/up forward 115.2 / 117.2
+// / 119.8.
+constexpr float kDivideFrom = 0x1p126f;
+
+template <int N>
+__device__ __forceinline__ void silu_n(const float* a, float* s) {
+  float D[N], m = 0.f;
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    D[e] = 1.0f + __expf(-a[e]);
+    m = fmaxf(m, fmaxf(D[e], fabsf(a[e])));
+    const float r = __builtin_amdgcn_rcpf(D[e]), q = a[e] * r;
+    s[e] = copysignf(fmaf(fmaf(-q, D[e], a[e]), r, q), a[e]);  // (a zero's sign)
+  }
+  if (__builtin_expect(__ballot(m >= kDivideFrom) != 0, 0)) {
+#pragma unroll
+    for (int e = 0; e < N; ++e) s[e] = a[e] / D[e];
+  }
+}
+template <int N>
+__device__ __forceinline__ void sigmoid_n(const float* a, float* s) {
+  float D[N], m = 0.f;
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    D[e] = 1.0f + __expf(-a[e]);
+    m = fmaxf(m, D[e]);
+    const float r = __builtin_amdgcn_rcpf(D[e]);
+    s[e] = fmaf(fmaf(-D[e], r, 1.0f), r, r);
+  }
+  if (__builtin_expect(__ballot(m >= kDivideFrom) != 0, 0)) {
+#pragma unroll
+    for (int e = 0; e < N; ++e) s[e] = 1.0f / D[e];
+  }
+}
 
 __device__ __forceinline__ int lane64() { return threadIdx.x & 63; }
 // The same, recomputed where it stands: a kernel with several tile shapes in
@@ -818,8 +854,10 @@ __device__ __forceinline__ void rows_epilogue(const RowsArgs& a, const CoreT& co
           for (int e = 0; e < 4; ++e) {
             av[e] = core.acc[i][jj][g * 4 + e];
             uv[e] = core.acc[i][jj + H][g * 4 + e];
-            hv[e] = silu_f(av[e]) * uv[e];
           }
+          silu_n<4>(av, hv);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) hv[e] *= uv[e];
           SR::put4(sh, l32, col, hv[0], hv[1], hv[2], hv[3]);
           SR::put4(sa, l32, col, av[0], av[1], av[2], av[3]);
           SR::put4(su, l32, col, uv[0], uv[1], uv[2], uv[3]);
@@ -866,13 +904,14 @@ __device__ __forceinline__ void rows_epilogue(const RowsArgs& a, const CoreT& co
       for (int it = 0; it < SR::NI; ++it) {
         const int r = SR::row_of(lane, it);
         // dH at columns nc .. nc + 7; saved A in [0, F), U in [F, 2F)
-        float dh[8], A8[8], U8[8], da[8], du[8];
+        float dh[8], A8[8], U8[8], sg8[8], da[8], du[8];
         SR::get8(ep, r, SR::col_of(lane), dh);
         unpack8(xa[it], A8);
         unpack8(xu[it], U8);
+        sigmoid_n<8>(A8, sg8);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float sg = sigmoid_f(A8[e]);
+          const float sg = sg8[e];
           da[e] = dh[e] * U8[e] * (sg + A8[e] * sg * (1.0f - sg));
           du[e] = dh[e] * A8[e] * sg;
         }
