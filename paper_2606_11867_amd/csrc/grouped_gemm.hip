@@ -1381,13 +1381,13 @@ __device__ __forceinline__ void run_unit(const FfnArgs& fa, const PhaseUnits& u,
 // to 5586 each; K = 2048, 768) the launches are 1.6 and 2.1 rounds of tiles
 // long, so idle CUs in the last round cost most. Measured on one box, before
 // -> now (us):
-//   Qwen3 forward, both GEMMs       197 -> 165   (116 + 66 -> 110 + 63 apart)
-//   Qwen3 input gradients           199 -> 187   (73 + 113 -> 67 + 110 apart)
-//   Mixtral-8x7B forward           3040 -> 2830  (row groups, tile heights)
-//   DeepSeek-V3 input gradients     924 -> 860
-//   12 slots of 26 rows, d = 2048, F = 768: gate/up 30.4 -> 22.5 (64-row
+//   Qwen3 forward, both GEMMs       197 -> 171   (114 + 68 -> 111 + 65 apart)
+//   Qwen3 input gradients           194 -> 183   (73 + 113 -> 68 + 112 apart)
+//   Mixtral-8x7B forward           2992 -> 2829  (row groups, tile heights)
+//   DeepSeek-V3 input gradients     896 -> 831
+//   12 slots of 26 rows, d = 2048, F = 768: gate/up 31.0 -> 23.9 (64-row
 //   tiles with three stages in flight, 64 weight rows per CU and k-step at
-//   5 TB/s), down 15.3 -> 14.3
+//   5 TB/s), down 16.4 -> 14.1
 // before: 256-row tiles only, a GEMM per launch, a fixed share of tiles, and
 // bf16 rounding in integer arithmetic in the epilogues (15000-23000 cycles).
 // One GEMM alone from the counters instead of the fixed share: 2-3 us slower
